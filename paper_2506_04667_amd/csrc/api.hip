@@ -155,7 +155,7 @@ moe_status run_gate(const moe_config* c, const Plan& p, void* ws, const void* x,
     g.rows_dev = nullptr; g.rows_fixed = c->T; g.rows_cap = c->T;
     g.groups = 1; g.max_rows = c->T;
     g.N = c->E; g.K = c->H;
-    g.act = MOE_ACT_IDENTITY; g.dtype = c->dtype; g.b_is_nk = true; g.c_f32 = true;
+    g.act = MOE_ACT_IDENTITY; g.dtype = c->dtype; g.b_is_nk = true; g.c_f32 = true; g.fp32_mfma = true;
     e = moe::launch_grouped_gemm(g, s);
     if (e != hipSuccess) return MOE_ERR_HIP;
     return hip_status(moe::launch_topk(logits, c->T, c->E, c->k, topk_expert, topk_weight, s));
@@ -450,10 +450,10 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     moe::GemmArgs wg{};
     wg.rows_dev = nullptr; wg.groups = 1; wg.dtype = dt; wg.act = MOE_ACT_IDENTITY; wg.c_f32 = true;
     wg.A = xT; wg.lda = b.T_pad; wg.a_rows_total = H; wg.rows_fixed = H; wg.rows_cap = H; wg.max_rows = H;
-    wg.B = dL; wg.ldb = b.ldL; wg.C = dWg; wg.ldc = E; wg.N = E; wg.K = T;
+    wg.B = dL; wg.ldb = b.ldL; wg.C = dWg; wg.ldc = E; wg.N = E; wg.K = b.wg_slice_k;   // rows of both beyond T are zero
     if (b.wg_slices > 1) {
         float* part = (float*)ws_at(ws, b.off_wg_part);
-        wg.groups = b.wg_slices; wg.K = b.wg_slice_k;
+        wg.groups = b.wg_slices;
         wg.a_group_stride = b.wg_slice_k;                // slice g of every row of x^T
         wg.b_group_stride = (long long)b.wg_slice_k * b.ldL;
         wg.C = part; wg.c_group_stride = (long long)H * E;

@@ -1,6 +1,7 @@
 // Grouped tile GEMM on CDNA4 matrix cores: the two FFN tasks of every expert
-// (C1 <- phi1(A B1 + D1), C2 <- C1 B2 + D2, Sec. 3.1 task abstraction) and the gate
-// projection share this kernel.  One workgroup computes one (group, row tile,
+// (C1 <- phi1(A B1 + D1), C2 <- C1 B2 + D2, Sec. 3.1 task abstraction) in 16-bit storage at
+// shapes that the weight-streaming kernel does not take, and the gate projection of shapes that
+// the fused gate does not take (in fp32 on the fp32 instruction, as there).  One workgroup computes one (group, row tile,
 // column tile) task; tasks whose row tile lies beyond the group's live rows exit at
 // once, so only ceil(rows/BM) row tiles per expert are ever computed (the in-place
 // padding idea of Sec. 3.2.1) and no task list or host round trip is needed.
@@ -25,8 +26,6 @@
 //                         (k contiguous per lane) is produced by the LDS transpose read
 //                         ds_read_b64_tr_b16: within 16 lanes, lane i receives, as element j,
 //                         element (i % 4) of the 8-byte row addressed by lane 4 j + i / 4.
-//   [k][n] B, fp32:       chunk c of row k lives at c ^ (((k >> 2) & 1) << 3) so that the two
-//                         half-waves (k and k + 4) use disjoint banks.
 //
 // Workgroup ids are mapped so that all tiles of one expert run on the same XCD
 // (ids are dealt round-robin to the 8 XCDs, each with its own L2): the column
@@ -70,7 +69,7 @@ __global__ __launch_bounds__(WM * WN * 64) void grouped_gemm_kernel(GemmArgs a) 
     const int rows = a.rows_dev ? min(a.rows_dev[grp], a.rows_cap) : a.rows_fixed;
     if (row0 >= rows) return;
 
-    gemm_tile<S, NT, WM, WN, TM, TN>(a, smem, grp, row0, n0, rows, 0, (a.K + C::BK - 1) / C::BK, nullptr);
+    gemm_tile<S, NT, WM, WN, TM, TN>(a, smem, grp, row0, n0, rows);
 }
 
 // the kernel's LDS limit on the current device (once per device)
@@ -96,39 +95,24 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Tile choice from the row bound alone (live row counts are only known on the device).  A CU works through
+// the tiles it is given at the same rate however many of them are resident, so the time of a launch is about
+// ceil(tiles / CUs) x tile area / efficiency: 256 x 256 (one per CU) or 128 x 128 (two per CU, about 0.94 of the
+// large tile's efficiency).
+bool large_tile(const GemmArgs& a) {
+    const long long cus = device_cu_count();
+    auto cost = [&](int b, double eff) {
+        const long long tiles = (long long)a.groups * ((a.max_rows + b - 1) / b) * ((a.N + b - 1) / b);
+        return (double)((tiles + cus - 1) / cus) * (double)(b * b) / eff;
+    };
+    return a.N > 128 && a.max_rows > 128 && cost(256, 1.0) <= cost(128, 0.94);
+}
+
 template <class S>
 hipError_t launch_t(const GemmArgs& a, hipStream_t stream) {
-    // Tile choice from the row bound alone (live row counts are only known on the device).  A CU works through
-    // the tiles it is given at the same rate however many of them are resident, so the time of a launch is about
-    // ceil(tiles / CUs) x tile area / efficiency: 256 x 256 (one per CU), 128 x 128 (two per CU, about 0.94 of
-    // the large tile's efficiency) and, for fp32 storage, 128 x 64 (three per CU, about 0.85), which evens out
-    // launches with fewer 128 x 128 tiles than two per CU.
-    const long long cus = device_cu_count();
-    auto cost = [&](int bm, int bn, double eff) {
-        const long long tiles = (long long)a.groups * ((a.max_rows + bm - 1) / bm) * ((a.N + bn - 1) / bn);
-        return (double)((tiles + cus - 1) / cus) * (double)(bm * bn) / eff;
-    };
-    int pick = 1;                                        // 0: 256 x 256, 1: 128 x 128, 2: 128 x 64, 3: 64 x 128
-    double best = cost(128, 128, 0.94);
-    if (a.N > 128 && a.max_rows > 128 && cost(256, 256, 1.0) <= best) {
-        pick = 0;
-        best = cost(256, 256, 1.0);
-    }
-    if constexpr (S::kBytes == 4) {
-        if (!a.b_is_nk && a.N > 64 && cost(128, 64, 0.85) < best) {
-            pick = 2;
-            best = cost(128, 64, 0.85);
-        }
-        if (!a.b_is_nk && a.max_rows > 64 && cost(64, 128, 0.85) < best) pick = 3;
-    }
-    if (a.b_is_nk) {
-        return pick == 0 ? launch_cfg<S, true, 2, 4, 4, 2>(a, stream) : launch_cfg<S, true, 2, 2, 2, 2>(a, stream);
-    }
-    if constexpr (S::kBytes == 4) {
-        if (pick == 2) return launch_cfg<S, false, 2, 2, 2, 1>(a, stream);
-        if (pick == 3) return launch_cfg<S, false, 1, 4, 2, 1>(a, stream);
-    }
-    return pick == 0 ? launch_cfg<S, false, 2, 4, 4, 2>(a, stream) : launch_cfg<S, false, 2, 2, 2, 2>(a, stream);
+    const bool large = large_tile(a);
+    if (a.b_is_nk) return large ? launch_cfg<S, true, 2, 4, 4, 2>(a, stream) : launch_cfg<S, true, 2, 2, 2, 2>(a, stream);
+    return large ? launch_cfg<S, false, 2, 4, 4, 2>(a, stream) : launch_cfg<S, false, 2, 2, 2, 2>(a, stream);
 }
 
 template <class S>
@@ -137,17 +121,14 @@ hipError_t prepare_t() {
     if (e == hipSuccess) e = prepare_cfg<S, true, 2, 2, 2, 2>();
     if (e == hipSuccess) e = prepare_cfg<S, false, 2, 4, 4, 2>();
     if (e == hipSuccess) e = prepare_cfg<S, false, 2, 2, 2, 2>();
-    if constexpr (S::kBytes == 4) {
-        if (e == hipSuccess) e = prepare_cfg<S, false, 2, 2, 2, 1>();
-        if (e == hipSuccess) e = prepare_cfg<S, false, 1, 4, 2, 1>();
-    }
     return e;
 }
 
 }  // namespace
 
 hipError_t prepare_grouped_gemm() {
-    hipError_t e = prepare_t<F32>();
+    hipError_t e = prepare_cfg<F32, true, 2, 4, 4, 2>();
+    if (e == hipSuccess) e = prepare_cfg<F32, true, 2, 2, 2, 2>();
     if (e == hipSuccess) e = prepare_t<BF16>();
     if (e == hipSuccess) e = prepare_t<F16>();
     return e;
@@ -157,8 +138,11 @@ hipError_t launch_grouped_gemm(const GemmArgs& a, hipStream_t stream) {
     if (a.groups <= 0 || a.max_rows <= 0 || a.N <= 0) return hipSuccess;
     if (stream_gemm_eligible(a)) return launch_grouped_gemm_stream(a, stream);
     if (f32_stream_eligible(a)) return launch_gemm_f32_stream(a, stream);
+    if (f32_gemm_eligible(a)) return launch_gemm_f32(a, stream);
     switch (a.dtype) {
-        case 0: return launch_t<F32>(a, stream);
+        case 0:                                          // gate logits only
+            if (!a.b_is_nk) return hipErrorInvalidValue;
+            return large_tile(a) ? launch_cfg<F32, true, 2, 4, 4, 2>(a, stream) : launch_cfg<F32, true, 2, 2, 2, 2>(a, stream);
         case 1: return launch_t<BF16>(a, stream);
         default: return launch_t<F16>(a, stream);
     }

@@ -1,7 +1,7 @@
 // Expert FFN tasks in fp32 storage (Sec. 3.1 task abstraction; Eq. ffn): a persistent kernel over the live work only.
 //
-// fp32 MFMAs are sixteen times slower per element than 16-bit ones, so with a 256 x 256 tile these GEMMs are bound by
-// the matrix cores, and what a launch of whole tiles loses is balance: a layer with few experts has about as many
+// Even as six bf16 products per fp32 one (gemm_f32_body.h) these GEMMs are bound by the matrix cores with a 256 x 256
+// tile, and what a launch of whole tiles loses is balance: a layer with few experts has about as many
 // tiles as the chip has CUs (or far fewer), an expert's last row tile may hold a handful of live rows, and tiles
 // beyond an expert's live rows are launched only to exit.  Here the work is cut the other way round.  The live
 // (expert, 256-row tile) units come from a list built on the device once routing is known, each with its weight:
@@ -14,16 +14,17 @@
 // in the order of the workgroups that made them (a fixed order: results are the same run to run) and applies bias
 // and activation.  No workgroup ever waits for another.
 #include "ffn_units.h"
-#include "gemm_body.h"
+#include "gemm_f32_body.h"
 
 namespace moe {
 namespace {
 
-// 256 x 256 tile: 8 wavefronts (2 x 4), each 128 x 64 (4 x 2 MFMA tiles of 32 x 32); one workgroup per CU
-constexpr int F_WM = 2, F_WN = 4, F_TM = 4, F_TN = 2;
-using FCfg = Cfg<F32, false, F_WM, F_WN, F_TM, F_TN>;
+// 256 x 256 tile: 8 wavefronts (2 x 4), each 128 x 64; one workgroup per CU
+constexpr int F_WM = 2, F_WN = 4, F_TM = 8, F_TN = 4;
+using FCfg = F32Cfg<false, F_WM, F_WN, F_TM, F_TN>;
 constexpr int F_BM = FCfg::BM, F_BN = FCfg::BN, F_BK = FCfg::BK, F_THREADS = FCfg::THREADS;
-constexpr int F_LDS = 2 * FCfg::STAGE_BYTES;
+constexpr int F_LDS = FCfg::LDS > F32Low::LDS ? FCfg::LDS : F32Low::LDS;
+static_assert(F32Low::BN == F_BN && F32Low::BK == F_BK && F32Low::THREADS == F_THREADS, "both bodies compute pieces of the same tiles");
 
 // upper bound of the workgroups worth launching: the iterations at full capacity, at most kF32MaxWorkgroups
 long long f32_workgroups_bound(int groups, int max_rows, int N, int K) {
@@ -51,25 +52,15 @@ __device__ __forceinline__ F32Work work_of(const F32StreamArgs& a) {
 // passed in, so that the body's accesses stay LDS instructions.
 __device__ __noinline__ void f32_tile_piece(const GemmArgs& g, int grp, int row0, int n0, int rows, int kt0, int kt1, float* partial) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    gemm_tile<F32, false, F_WM, F_WN, F_TM, F_TN>(g, smem, grp, row0, n0, rows, kt0, kt1, partial);
+    f32_tile<false, F_WM, F_WN, F_TM, F_TN>(g, smem, uniform(grp), uniform(row0), uniform(n0), uniform(rows), uniform(kt0), uniform(kt1), partial);
+}
+__device__ __noinline__ void f32_low_piece(const GemmArgs& g, int grp, int row0, int n0, int rows, int kt0, int kt1, float* partial) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    f32_tile_low<false>(g, smem, uniform(grp), uniform(row0), uniform(n0), uniform(rows), uniform(kt0), uniform(kt1), partial);
 }
 
-#ifdef MOE_F32_STREAM_CLOCKS
-}  // namespace
-}  // namespace moe
-static __device__ long long f32_dbg[256 * 4];
-extern "C" int moe_debug_f32_clocks(long long* host) {
-    return (int)hipMemcpyFromSymbol(host, HIP_SYMBOL(f32_dbg), sizeof(long long) * 256 * 4);
-}
-namespace moe {
-namespace {
-#endif
 
 __global__ __launch_bounds__(F_THREADS) void ffn_f32_stream_kernel(F32StreamArgs a) {
-#ifdef MOE_F32_STREAM_CLOCKS
-    const long long t_start = wall_clock64();
-    int n_pieces = 0, n_light = 0;
-#endif
     const int w = blockIdx.x, G = gridDim.x;
     const F32Work k = work_of(a);
     const long long begin = k.boundary(w, G), end = k.boundary(w + 1, G);
@@ -83,22 +74,12 @@ __global__ __launch_bounds__(F_THREADS) void ffn_f32_stream_kernel(F32StreamArgs
         const int rows = min(a.g.rows_dev[grp], a.g.rows_cap);
         const bool whole = kt0 == 0 && kt1 == k.nk;
         float* partial = whole ? nullptr : a.partials + ((size_t)w * 2 + (first ? 0 : 1)) * (F_BM * F_BN);
-        f32_tile_piece(a.g, grp, rt * F_BM, ct * F_BN, rows, kt0, kt1, partial);
-#ifdef MOE_F32_STREAM_CLOCKS
-        ++n_pieces;
-        if (rows - rt * F_BM <= 128) n_light += kt1 - kt0;
-#endif
+        // a unit of at most 64 rows counts a quarter of a full one: it takes the tile body that is that fast
+        if (rows - rt * F_BM <= F32Low::BM) f32_low_piece(a.g, grp, rt * F_BM, ct * F_BN, rows, kt0, kt1, partial);
+        else f32_tile_piece(a.g, grp, rt * F_BM, ct * F_BN, rows, kt0, kt1, partial);
         it += kt1 - kt0;
         first = false;
     }
-#ifdef MOE_F32_STREAM_CLOCKS
-    if (threadIdx.x == 0 && w < 256) {
-        f32_dbg[w * 4 + 0] = wall_clock64() - t_start;
-        f32_dbg[w * 4 + 1] = end - begin;
-        f32_dbg[w * 4 + 2] = n_pieces;
-        f32_dbg[w * 4 + 3] = n_light;
-    }
-#endif
 }
 
 // Workgroups (w, 0 .. kFixupSplit - 1) add up the tile that range w begins but does not finish: its own piece, then those of the
@@ -120,7 +101,8 @@ __global__ __launch_bounds__(F_THREADS) void ffn_f32_fixup_kernel(F32StreamArgs 
     {
         const f32x4* p = (const f32x4*)(a.partials + ((size_t)w * 2 + (begin == tb ? 0 : 1)) * (F_BM * F_BN));
 #pragma unroll
-        for (int i = 0; i < V; ++i) sum[i] = p[part + i * F_THREADS + threadIdx.x];
+        for (int i = 0; i < V; ++i)
+            if (row0 + (part + i * F_THREADS) / (F_BN / 4) < rows) sum[i] = p[part + i * F_THREADS + threadIdx.x];
     }
     long long vb = end;                                 // workgroup v's range is [vb, ve)
     for (int v = w + 1; v < G && vb < te; ++v) {
@@ -129,6 +111,7 @@ __global__ __launch_bounds__(F_THREADS) void ffn_f32_fixup_kernel(F32StreamArgs 
             const f32x4* p = (const f32x4*)(a.partials + (size_t)v * 2 * (F_BM * F_BN));   // the tile is v's first piece
 #pragma unroll
             for (int i = 0; i < V; ++i) {
+                if (row0 + (part + i * F_THREADS) / (F_BN / 4) >= rows) continue;
                 const f32x4 t = p[part + i * F_THREADS + threadIdx.x];
                 sum[i][0] += t[0]; sum[i][1] += t[1]; sum[i][2] += t[2]; sum[i][3] += t[3];
             }
@@ -165,7 +148,103 @@ int f32_grid(int groups, int max_rows, int N, int K) {
     return (int)(g < bound ? g : bound);
 }
 
+// One workgroup per (group, row tile, column tile); tiles beyond a group's live rows exit at once.  All tiles of a group
+// run on one XCD when there are enough groups, as in the 16-bit kernel (gemm.hip).
+template <bool NT, int WM, int WN, int TM, int TN>
+__global__ __launch_bounds__(WM * WN * 64, 2) void f32_gemm_kernel(GemmArgs a) {
+    using C = F32Cfg<NT, WM, WN, TM, TN>;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int ncol = (a.N + C::BN - 1) / C::BN, nrow = (a.max_rows + C::BM - 1) / C::BM;
+    const int per_group = nrow * ncol;
+    int id = blockIdx.x, grp;
+    if (a.groups >= kXcds) {
+        const int s = id / kXcds;
+        grp = (s / per_group) * kXcds + id % kXcds;
+        id = s % per_group;
+    } else {
+        grp = id / per_group;
+        id %= per_group;
+    }
+    if (grp >= a.groups) return;
+    const int row0 = id / ncol * C::BM, n0 = id % ncol * C::BN;
+    const int rows = a.rows_dev ? min(a.rows_dev[grp], a.rows_cap) : a.rows_fixed;
+    if (row0 >= rows) return;
+    f32_tile<NT, WM, WN, TM, TN>(a, smem, grp, row0, n0, rows, 0, (a.K + C::BK - 1) / C::BK, nullptr);
+}
+
+// the same for groups of at most 64 rows
+template <bool NT>
+__global__ __launch_bounds__(F32Low::THREADS, 2) void f32_gemm_low_kernel(GemmArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int ncol = (a.N + F32Low::BN - 1) / F32Low::BN;
+    const int grp = blockIdx.x / ncol, n0 = blockIdx.x % ncol * F32Low::BN;
+    const int rows = a.rows_dev ? min(a.rows_dev[grp], a.rows_cap) : a.rows_fixed;
+    if (rows <= 0) return;
+    f32_tile_low<NT>(a, smem, grp, 0, n0, rows, 0, (a.K + F32Low::BK - 1) / F32Low::BK, nullptr);
+}
+
+template <bool NT>
+hipError_t prepare_f32_low() {
+    static DeviceFlags limit_raised = {};
+    return raise_lds_limit(reinterpret_cast<const void*>(f32_gemm_low_kernel<NT>), F32Low::LDS, limit_raised);
+}
+
+template <bool NT>
+hipError_t launch_f32_low(const GemmArgs& a, hipStream_t stream) {
+    if (hipError_t e = prepare_f32_low<NT>(); e != hipSuccess) return e;
+    const long long blocks = (long long)a.groups * ((a.N + F32Low::BN - 1) / F32Low::BN);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(f32_gemm_low_kernel<NT>, dim3((unsigned)blocks), dim3(F32Low::THREADS), F32Low::LDS, stream, a);
+    return hipGetLastError();
+}
+
+template <bool NT, int WM, int WN, int TM, int TN>
+hipError_t prepare_f32_cfg() {
+    static DeviceFlags limit_raised = {};
+    return raise_lds_limit(reinterpret_cast<const void*>(f32_gemm_kernel<NT, WM, WN, TM, TN>), F32Cfg<NT, WM, WN, TM, TN>::LDS, limit_raised);
+}
+
+template <bool NT, int WM, int WN, int TM, int TN>
+hipError_t launch_f32_cfg(const GemmArgs& a, hipStream_t stream) {
+    using C = F32Cfg<NT, WM, WN, TM, TN>;
+    if (hipError_t e = prepare_f32_cfg<NT, WM, WN, TM, TN>(); e != hipSuccess) return e;
+    const long long ncol = (a.N + C::BN - 1) / C::BN, nrow = (a.max_rows + C::BM - 1) / C::BM;
+    const long long groups = a.groups >= kXcds ? (long long)(a.groups + kXcds - 1) / kXcds * kXcds : a.groups;
+    const long long blocks = groups * nrow * ncol;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((f32_gemm_kernel<NT, WM, WN, TM, TN>), dim3((unsigned)blocks), dim3(C::THREADS), C::LDS, stream, a);
+    return hipGetLastError();
+}
+
+// Tile choice from the row bound alone (live counts are only known on the device): a launch takes about
+// ceil(tiles / CUs) x tile area / efficiency.  256 x 256 fills a CU by itself; two 128 x 128 or four 64 x 64 tiles share
+// one and read each operand from LDS two and four times as often per product.
+template <bool NT>
+hipError_t launch_f32_t(const GemmArgs& a, hipStream_t stream) {
+    const long long cus = device_cu_count();
+    auto cost = [&](int b, double eff) {
+        const long long tiles = (long long)a.groups * ((a.max_rows + b - 1) / b) * ((a.N + b - 1) / b);
+        return (double)((tiles + cus - 1) / cus) * (double)(b * b) / eff;
+    };
+    const double c256 = cost(256, 1.0), c128 = cost(128, 0.85), c64 = cost(64, 0.55);
+    // groups of at most 64 rows: the 64 x 256 tile reads each weight from LDS once, but needs four times fewer workgroups
+    const double low = (double)((a.groups * ((a.N + 255ll) / 256) + cus - 1) / cus) * (64 * 256) / 0.7;
+    if (a.max_rows <= F32Low::BM && low <= c64) return launch_f32_low<NT>(a, stream);
+    if (c64 < c128 && c64 < c256) return launch_f32_cfg<NT, 2, 2, 2, 2>(a, stream);
+    if (c128 < c256) return launch_f32_cfg<NT, 2, 2, 4, 4>(a, stream);
+    return launch_f32_cfg<NT, 2, 4, 8, 4>(a, stream);
+}
+
 }  // namespace
+
+bool f32_gemm_eligible(const GemmArgs& a) {
+    return a.dtype == 0 && !a.fp32_mfma && a.K % 8 == 0 && a.K >= 8 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.a_group_stride % 4 == 0 &&
+           a.b_group_stride % 4 == 0 && a.c_group_stride % 4 == 0 && (long long)a.ldb * 4 * (a.b_is_nk ? 256 : 32) < (1ll << 32);
+}
+
+hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t stream) {
+    return a.b_is_nk ? launch_f32_t<true>(a, stream) : launch_f32_t<false>(a, stream);
+}
 
 size_t f32_units_ints(int groups, int max_rows) { return (size_t)f32_units_total_ints(groups, max_rows); }
 size_t f32_partials_bytes(int groups, int max_rows, int H, int I) {
@@ -178,17 +257,30 @@ hipError_t launch_f32_units(const int32_t* rows_dev, int rows_cap, int groups, i
     return hipGetLastError();
 }
 
-hipError_t prepare_gemm_f32() {
+static hipError_t prepare_f32_stream() {
     static DeviceFlags limit_raised = {};
     return raise_lds_limit(reinterpret_cast<const void*>(ffn_f32_stream_kernel), F_LDS, limit_raised);
+}
+
+hipError_t prepare_gemm_f32() {
+    hipError_t e = prepare_f32_stream();
+    if (e == hipSuccess) e = prepare_f32_cfg<false, 2, 4, 8, 4>();
+    if (e == hipSuccess) e = prepare_f32_cfg<false, 2, 2, 4, 4>();
+    if (e == hipSuccess) e = prepare_f32_cfg<false, 2, 2, 2, 2>();
+    if (e == hipSuccess) e = prepare_f32_cfg<true, 2, 4, 8, 4>();
+    if (e == hipSuccess) e = prepare_f32_cfg<true, 2, 2, 4, 4>();
+    if (e == hipSuccess) e = prepare_f32_cfg<true, 2, 2, 2, 2>();
+    if (e == hipSuccess) e = prepare_f32_low<false>();
+    if (e == hipSuccess) e = prepare_f32_low<true>();
+    return e;
 }
 
 // Worth it when whole tiles would not fill the chip evenly: fewer than four rounds of 256 x 256 tiles over the CUs at
 // full capacity (with more, the plain launch of whole tiles is as fast: its rounding loss is small and it needs no
 // second pass), but enough work that the second launch does not show (eight iterations per CU).
 bool f32_stream_eligible(const GemmArgs& a) {
-    if (a.dtype != 0 || a.b_is_nk || a.c_f32 || !a.units || !a.partials || !a.rows_dev) return false;
-    if (a.N % 4 != 0 || a.K % 4 != 0 || a.ldc % 4 != 0) return false;
+    if (!f32_gemm_eligible(a) || a.b_is_nk || a.c_f32 || !a.units || !a.partials || !a.rows_dev) return false;
+    if (a.N % 4 != 0 || a.ldc % 4 != 0) return false;
     const long long units = (long long)a.groups * f32_units_nrow(a.max_rows), ncol = (a.N + F_BN - 1) / F_BN;
     if (units > 0x7fffffffLL / ncol) return false;
     const long long tiles = units * ncol, cus = device_cu_count();
@@ -196,7 +288,7 @@ bool f32_stream_eligible(const GemmArgs& a) {
 }
 
 hipError_t launch_gemm_f32_stream(const GemmArgs& g, hipStream_t stream) {
-    if (hipError_t e = prepare_gemm_f32(); e != hipSuccess) return e;
+    if (hipError_t e = prepare_f32_stream(); e != hipSuccess) return e;
     F32StreamArgs a{};
     a.g = g;
     a.list = g.units;

@@ -34,6 +34,7 @@ struct GemmArgs {
     int dtype;                                              // storage of A, B (and of C, bias unless c_f32)
     bool b_is_nk;
     bool c_f32;                                             // C and bias are fp32 (gate logits)
+    bool fp32_mfma;                                         // fp32 storage: multiply on the fp32 instruction (gate logits, as in the fused gate)
 };
 hipError_t launch_grouped_gemm(const GemmArgs& a, hipStream_t stream);
 
@@ -77,6 +78,9 @@ size_t f32_units_ints(int groups, int max_rows);
 size_t f32_partials_bytes(int groups, int max_rows, int H, int I);   // shared by the H -> I and the I -> H GEMM
 hipError_t launch_f32_units(const int32_t* rows_dev, int rows_cap, int groups, int max_rows, int32_t* units, hipStream_t stream);
 hipError_t prepare_gemm_f32();
+// fp32 GEMMs as one workgroup per tile (the equal-span kernel's tile body, three tile sizes)
+bool f32_gemm_eligible(const GemmArgs& a);
+hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t stream);
 
 // WgT[n][h] = Wg[h][n] for n < E, zero rows for E <= n < E_pad.
 hipError_t launch_transpose_pad(const void* Wg, void* WgT, int H, int E, int E_pad, int dtype,

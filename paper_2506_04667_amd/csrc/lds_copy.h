@@ -29,6 +29,11 @@ __device__ __forceinline__ void copy_to_lds_stream(const unsigned char* base, ui
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_addr), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 
+// The same copy with a whole address per lane, for rows that may lie further apart than 32-bit offsets reach.
+__device__ __forceinline__ void copy_to_lds_lane(const unsigned char* lane_addr, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(lane_addr) : "memory", "m0");
+}
+
 // own copies older than the newest N have landed; own LDS reads are complete; then meet the other waves
 template <int N>
 __device__ __forceinline__ void wait_copies_and_barrier() {

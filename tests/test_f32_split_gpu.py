@@ -1,0 +1,85 @@
+"""The fp32 GEMMs that multiply three bf16 pieces per value: tile edges, K tails and the ends of the fp32 range.
+
+Bound on the products left out: with a = a1 + a2 + a3, |a2| < 2^-7 |a|, |a3| <= 2^-16 |a|, each of a2 b3 and a3 b2 is below
+2^-22.9 |a b| and a3 b3 below 2^-32 |a b|, of either sign; fp32 accumulation of n terms in any order is within
+n 2^-24 sum |a b| (in the mean sqrt(n) 2^-24).  The layer's bar for fp32 storage (1e-5 of value and rms) holds for it as
+for native fp32 products, and the mean error has to stay within that of one fp32 rounding per term."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_04667_amd import binding as moe
+from paper_2506_04667_amd.inputs import WORKLOADS, make_inputs, scaled
+
+import parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("case", [
+    # rows around the 64-row tile body and K / N tails, by tile: many experts with at most 64 slots (64 x 256 tiles)
+    dict(T=1100, H=1032, I=1048, E=64, k=2, capacity_factor=1.8),
+    # 64 x 64 tiles: one row up to 65, K of one short K-tile
+    dict(T=1, H=8, I=24, E=2, k=1, capacity_factor=1.0),
+    dict(T=65, H=40, I=72, E=1, k=1, capacity_factor=1.0),
+    dict(T=128, H=64, I=136, E=2, k=2, capacity_factor=1.0),
+    # 128 x 128 tiles with ragged columns; live rows 1 .. 128 of a tile
+    dict(T=900, H=776, I=1160, E=9, k=3, capacity_factor=1.3),
+    # 256 x 256 tiles, every count of live rows, whole tiles (more than 4 x 256 tiles at capacity)
+    dict(T=5000, H=96, I=2056, E=24, k=4, capacity_factor=4.0, zipf_s=0.7),
+])
+def test_forward_tiles(oracle, case):
+    w = scaled(WORKLOADS["small_f32"], name="f32_split", seed=91, dtype="f32", act="gelu_erf", with_bias=True, **case)
+    print("case", w, flush=True)
+    cpu = make_inputs(w)
+    dev = parity.to_device(cpu)
+    b, host = parity.gpu_forward(w, dev)
+    parity.check_layer(oracle, w, cpu, b, host)
+    b2, _ = parity.gpu_forward(w, dev)
+    assert torch.equal(b.out, b2.out)
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 64, 65, 128, 129, 256])
+def test_products_are_as_accurate_as_fp32(rows):
+    # one expert, identity activation: y = (x W1) W2 against float64.  A sum of n products with one fp32 rounding each has
+    # a relative error (2-norm) of about sqrt(n) 2^-24 / sqrt(3) of the typical partial sum: below sqrt(K) 2^-24 per GEMM
+    H, I = 512, 1040
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    n = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen)
+    x, W1, W2 = n(rows, H), n(1, H, I) / math.sqrt(H), n(1, I, H) / math.sqrt(I)
+    cfg = moe.make_config(rows, H, I, 1, 1, 1.0, "identity", "f32")
+    b = moe.Buffers(cfg)
+    b.alloc_staged()
+    b.xe[0, :rows] = x
+    b.expert_demand.fill_(rows)
+    moe.moe_expert_ffn(cfg, b.workspace, b.xe, b.expert_demand, W1, None, W2, None, b.y)
+    ref = x.double() @ W1[0].double() @ W2[0].double()
+    rel = float((b.y[0, :rows].double() - ref).norm() / ref.norm())
+    assert rel < (math.sqrt(H) + math.sqrt(I)) * 2.0 ** -24, rel
+
+
+@pytest.mark.parametrize("big,small", [(3.4e38, 1e-38), (-3.4028234e38, 2.0 ** -126), (1.0, 2.0 ** -100), (2.0 ** 100, 2.0 ** -120)])
+def test_ends_of_the_range(big, small):
+    # the largest finite values stay finite (their first piece is cut off, not rounded up), and one product per sum is
+    # good to 2^-21: no piece but a subnormal one is lost
+    H = I = 64
+    rows = 70
+    cfg = moe.make_config(rows, H, I, 1, 1, 1.0, "identity", "f32")
+    b = moe.Buffers(cfg)
+    b.alloc_staged()
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.zeros(rows, H, device="cuda")
+    x[:, 5] = big * torch.empty(rows, device="cuda").uniform_(0.5, 1.0, generator=gen)
+    W1 = torch.zeros(1, H, I, device="cuda")
+    W1[0, 5] = small * torch.empty(I, device="cuda").uniform_(0.5, 1.0, generator=gen)
+    W2 = torch.eye(I, device="cuda")[None].contiguous()
+    b.xe[0, :rows] = x
+    b.expert_demand.fill_(rows)
+    moe.moe_expert_ffn(cfg, b.workspace, b.xe, b.expert_demand, W1, None, W2, None, b.y)
+    ref = x.double() @ W1[0].double()
+    got = b.y[0, :rows].double()
+    assert torch.isfinite(got).all()
+    # pieces of `small` below 2^-126 may be flushed: an absolute error of 2^-126 |x| per product
+    assert bool(((got - ref).abs() <= 2.0 ** -21 * ref.abs() + 2.0 ** -126 * abs(big) + 2.0 ** -149).all()), float(((got - ref).abs() / ref.abs()).max())
