@@ -115,6 +115,15 @@ __global__ __launch_bounds__(256) void bwd_act_kernel(const void* __restrict__ a
     }
 }
 
+// the value that lane j (uniform) holds, whether or not that lane takes part in the current pass: a shuffle reads 0 from
+// lanes that are switched off, as most are in the last pass over a row whose length is not a multiple of 64 chunks
+__device__ __forceinline__ int lane_value(int v, int j) { return __builtin_amdgcn_readlane(v, j); }
+__device__ __forceinline__ float lane_value(float v, int j) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j)); }
+__device__ __forceinline__ long long lane_value(long long v, int j) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)v, j), hi = __builtin_amdgcn_readlane((int)(v >> 32), j);
+    return (long long)(((uint64_t)hi << 32) | lo);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
@@ -165,8 +174,8 @@ __global__ __launch_bounds__(256) void bwd_gate_kernel(const void* __restrict__ 
     for (int c = lane; c < ld; c += 64) {
         float v = 0.0f;
         for (int j = 0; j < k; ++j) {
-            const int e = __shfl(e_l, j);
-            const float d = __shfl(dl_l, j);
+            const int e = lane_value(e_l, j);
+            const float d = lane_value(dl_l, j);
             if (e == c) v = d;
         }
         store_from_float<S>(dL, (size_t)t * ld + c, v);
@@ -324,12 +333,12 @@ __global__ __launch_bounds__(256) void bwd_dx_kernel(const void* __restrict__ dx
 #pragma unroll
         for (int q = 0; q < VEC; ++q) acc[q] = 0.0f;
         for (int j = 0; j < k; ++j) {
-            const long long row = __shfl(row_lane, j);
+            const long long row = lane_value(row_lane, j);
             if (row >= 0) fma_chunk(acc, 1.0f, __builtin_nontemporal_load(dv + (size_t)row * row_chunks + c));
         }
         for (int j = 0; j < k; ++j) {
-            const int e = __shfl(e_lane, j);
-            const float d = __shfl(dl_lane, j);
+            const int e = lane_value(e_lane, j);
+            const float d = lane_value(dl_lane, j);
             if (e >= 0) fma_chunk(acc, d, wv[(size_t)e * row_chunks + c]);
         }
 #pragma unroll
