@@ -321,7 +321,7 @@ struct BwdPlan {
     int wg_slices, wg_slice_k;                           // dWg = x^T dL as wg_slices partial products over wg_slice_k tokens each
     size_t off_wg_part;
     size_t off_counts, off_units, off_slot_token, off_slot_weight, off_slot, off_demand, off_dl, off_dL, off_wgt, off_xe,
-        off_gy, off_a, off_h, off_dh, off_y, off_hT, off_xeT, off_xT, off_wrows, off_wunits1, off_wunits2, total;
+        off_ge, off_a, off_h, off_dh, off_da, off_dxe, off_row_p, off_hT, off_xeT, off_xT, off_wrows, off_wunits1, off_wunits2, total;
 };
 
 moe_status make_bwd_plan(const moe_config* c, BwdPlan* b) {
@@ -351,11 +351,13 @@ moe_status make_bwd_plan(const moe_config* c, BwdPlan* b) {
     b->off_wg_part = take(b->wg_slices > 1 ? (size_t)b->wg_slices * H * E * 4 : 0);
     b->off_wgt = take((size_t)p.E_pad * H * el);
     b->off_xe = take(rows * H * el);
-    b->off_gy = take(rows * H * el);
+    b->off_ge = take(rows * H * el);
     b->off_a = take(rows * I * el);
     b->off_h = take(rows * I * el);
-    b->off_dh = take(rows * I * el);
-    b->off_y = take(rows * H * el);
+    b->off_dh = take(rows * I * 4);
+    b->off_da = c->dtype == MOE_F32 ? b->off_dh : take(rows * I * el);
+    b->off_dxe = take(rows * H * el);
+    b->off_row_p = take(rows * 4);
     b->off_hT = take(rows * I * el);
     b->off_xeT = take(rows * H * el);
     b->off_xT = take(H * (size_t)b->T_pad * el);
@@ -380,44 +382,40 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     int32_t* slot = (int32_t*)ws_at(ws, b.off_slot);
     int32_t* demand = (int32_t*)ws_at(ws, b.off_demand);
     float* dl = (float*)ws_at(ws, b.off_dl);
-    void *dL = ws_at(ws, b.off_dL), *wgt = ws_at(ws, b.off_wgt), *xe = ws_at(ws, b.off_xe), *gy = ws_at(ws, b.off_gy);
-    void *a = ws_at(ws, b.off_a), *h = ws_at(ws, b.off_h), *dh = ws_at(ws, b.off_dh), *y = ws_at(ws, b.off_y);
+    void *dL = ws_at(ws, b.off_dL), *wgt = ws_at(ws, b.off_wgt), *xe = ws_at(ws, b.off_xe), *ge = ws_at(ws, b.off_ge);
+    void *a = ws_at(ws, b.off_a), *h = ws_at(ws, b.off_h), *da = ws_at(ws, b.off_da), *dxe = ws_at(ws, b.off_dxe);
+    float *dh = (float*)ws_at(ws, b.off_dh), *row_p = (float*)ws_at(ws, b.off_row_p);
     void *hT = ws_at(ws, b.off_hT), *xeT = ws_at(ws, b.off_xeT), *xT = ws_at(ws, b.off_xT);
 #define MOE_TRY(call) do { if ((call) != hipSuccess) return MOE_ERR_HIP; } while (0)
     // the routing tables again, from the selection the forward pass made (slots are a function of it)
     MOE_TRY(moe::launch_route(topk_expert, topk_weight, T, E, k, C, c->drop_policy == MOE_DROP_CHOICE_MAJOR, counts, false, slot,
                               demand, slot_token, slot_weight, units, false, s));
     MOE_TRY(moe::launch_transpose_pad(Wg, wgt, H, E, p.E_pad, dt, s));
-    MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, slot_weight, H, E, C, C_pad, dt, xe, gy, s));
+    MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, H, E, C, C_pad, dt, xe, ge, s));
     // grouped GEMMs over the experts' live rows
     moe::GemmArgs g{};
     g.rows_dev = demand; g.rows_fixed = 0; g.rows_cap = C; g.groups = E; g.max_rows = C;
     g.dtype = dt; g.act = MOE_ACT_IDENTITY; g.a_rows_total = C_pad;
     const long long rH = (long long)C_pad * H, rI = (long long)C_pad * I, HI = (long long)H * I;
-    // forward again, keeping the pre-activation: a = xe W1 + b1, h = phi(a), y = h W2 + b2
+    // the pre-activation again: a = xe W1 + b1
     moe::GemmArgs f1 = g;
     f1.A = xe; f1.a_group_stride = rH; f1.lda = H; f1.B = W1; f1.b_group_stride = HI; f1.ldb = I;
     f1.C = a; f1.c_group_stride = rI; f1.ldc = I; f1.bias = b1; f1.bias_group_stride = I; f1.N = I; f1.K = H; f1.units = units;
     MOE_TRY(moe::launch_grouped_gemm(f1, s));
-    MOE_TRY(moe::launch_bwd_act(a, nullptr, demand, E, C, C_pad, I, c->act, dt, false, h, s));
-    moe::GemmArgs f2 = g;
-    f2.A = h; f2.a_group_stride = rI; f2.lda = I; f2.B = W2; f2.b_group_stride = HI; f2.ldb = H;
-    f2.C = y; f2.c_group_stride = rH; f2.ldc = H; f2.bias = b2; f2.bias_group_stride = H; f2.N = H; f2.K = I; f2.units = units;
-    MOE_TRY(moe::launch_grouped_gemm(f2, s));
-    // gate: dL/dw from <dout, y>, then the softmax Jacobian
-    MOE_TRY(moe::launch_bwd_gate(dout, y, topk_expert, topk_weight, slot, T, b.T_pad, H, k, E, C, C_pad, b.ldL, dt, dl, dL, s));
-    // dh = gy W2^T (W2[e] read as [N = I][K = H]); da = dh * phi'(a); dxe = da W1^T (W1[e] as [N = H][K = I])
+    // dh = dout W2^T in fp32 (W2[e] read as [N = I][K = H]); h = w phi(a), da = w dh phi'(a); dxe = da W1^T (W1[e] as [N = H][K = I])
     moe::GemmArgs d1 = g;
-    d1.A = gy; d1.a_group_stride = rH; d1.lda = H; d1.B = W2; d1.b_group_stride = HI; d1.ldb = H; d1.b_is_nk = true;
-    d1.C = dh; d1.c_group_stride = rI; d1.ldc = I; d1.N = I; d1.K = H;
+    d1.A = ge; d1.a_group_stride = rH; d1.lda = H; d1.B = W2; d1.b_group_stride = HI; d1.ldb = H; d1.b_is_nk = true;
+    d1.C = dh; d1.c_group_stride = rI; d1.ldc = I; d1.N = I; d1.K = H; d1.c_f32 = true;
     MOE_TRY(moe::launch_grouped_gemm(d1, s));
-    MOE_TRY(moe::launch_bwd_act(a, dh, demand, E, C, C_pad, I, c->act, dt, true, dh, s));
+    MOE_TRY(moe::launch_bwd_act(a, dh, ge, b2, demand, slot_weight, E, C, C_pad, H, I, c->act, dt, h, da, row_p, s));
+    // gate: w dL/dw of every kept pair is in row_p; the softmax Jacobian
+    MOE_TRY(moe::launch_bwd_gate(row_p, topk_expert, topk_weight, slot, T, b.T_pad, k, E, C, C_pad, b.ldL, dt, dl, dL, s));
     moe::GemmArgs d2 = g;
-    d2.A = dh; d2.a_group_stride = rI; d2.lda = I; d2.B = W1; d2.b_group_stride = HI; d2.ldb = I; d2.b_is_nk = true;
-    d2.C = y; d2.c_group_stride = rH; d2.ldc = H; d2.N = H; d2.K = I;       // dxe takes y's place
+    d2.A = da; d2.a_group_stride = rI; d2.lda = I; d2.B = W1; d2.b_group_stride = HI; d2.ldb = I; d2.b_is_nk = true;
+    d2.C = dxe; d2.c_group_stride = rH; d2.ldc = H; d2.N = H; d2.K = I;
     MOE_TRY(moe::launch_grouped_gemm(d2, s));
-    // weight gradients as row-major GEMMs over all C_pad rows (rows beyond the live ones are zero in gy and da):
-    // dW2[e] = h[e]^T gy[e], dW1[e] = xe[e]^T da[e]
+    // weight gradients as row-major GEMMs over all C_pad rows (rows beyond the live ones are zero):
+    // dW2[e] = h[e]^T ge[e], dW1[e] = xe[e]^T da[e]
     MOE_TRY(moe::launch_bwd_transpose(h, hT, E, C_pad, I, C_pad, dt, s));
     MOE_TRY(moe::launch_bwd_transpose(xe, xeT, E, C_pad, H, C_pad, dt, s));
     // 16-bit storage: row counts and lists of row tiles, so that the persistent weight-streaming kernel takes them (each
@@ -436,15 +434,15 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     moe::GemmArgs w2 = w;
     if (wunits2) { w2.rows_dev = wrows + E; w2.units = wunits2; }
     w2.A = hT; w2.a_group_stride = rI; w2.a_rows_total = I; w2.rows_fixed = I; w2.rows_cap = I; w2.max_rows = I;
-    w2.B = gy; w2.b_group_stride = rH; w2.ldb = H; w2.C = dW2; w2.c_group_stride = HI; w2.ldc = H; w2.N = H;
+    w2.B = ge; w2.b_group_stride = rH; w2.ldb = H; w2.C = dW2; w2.c_group_stride = HI; w2.ldc = H; w2.N = H;
     MOE_TRY(moe::launch_grouped_gemm(w2, s));
     moe::GemmArgs w1 = w;
     if (wunits1) { w1.rows_dev = wrows; w1.units = wunits1; }
     w1.A = xeT; w1.a_group_stride = rH; w1.a_rows_total = H; w1.rows_fixed = H; w1.rows_cap = H; w1.max_rows = H;
-    w1.B = dh; w1.b_group_stride = rI; w1.ldb = I; w1.C = dW1; w1.c_group_stride = HI; w1.ldc = I; w1.N = I;
+    w1.B = da; w1.b_group_stride = rI; w1.ldb = I; w1.C = dW1; w1.c_group_stride = HI; w1.ldc = I; w1.N = I;
     MOE_TRY(moe::launch_grouped_gemm(w1, s));
-    MOE_TRY(moe::launch_bwd_colsum(gy, demand, E, C, C_pad, H, dt, db2, s));
-    MOE_TRY(moe::launch_bwd_colsum(dh, demand, E, C, C_pad, I, dt, db1, s));
+    MOE_TRY(moe::launch_bwd_colsum(ge, slot_weight, demand, E, C, C_pad, H, dt, db2, s));
+    MOE_TRY(moe::launch_bwd_colsum(da, nullptr, demand, E, C, C_pad, I, dt, db1, s));
     // gate weights: dWg = x^T dL, dgate_bias = column sums of dl
     MOE_TRY(moe::launch_bwd_transpose(x, xT, 1, T, H, b.T_pad, dt, s));
     moe::GemmArgs wg{};
@@ -464,7 +462,7 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     }
     MOE_TRY(moe::launch_bwd_gate_bias(topk_expert, dl, T, k, E, dgate_bias, s));
     // dx: the kept choices' rows of dxe plus the gate path
-    MOE_TRY(moe::launch_bwd_dx(y, wgt, topk_expert, slot, dl, T, H, k, E, C, C_pad, dt, dx, s));
+    MOE_TRY(moe::launch_bwd_dx(dxe, wgt, topk_expert, slot, dl, T, H, k, E, C, C_pad, dt, dx, s));
 #undef MOE_TRY
     return MOE_OK;
 }

@@ -57,61 +57,25 @@ __device__ __forceinline__ u32x4 floats_to_chunk(const float (&f)[S::kVec]) {
     return v;
 }
 
-// One workgroup per slot row (e, s), s < C_pad: xe[e, s, :] = x[token, :] and gy[e, s, :] = w * dout[token, :]
+// One workgroup per slot row (e, s), s < C_pad: xe[e, s, :] = x[token, :] and ge[e, s, :] = dout[token, :]
 // for a live slot, zeros for an empty one (so that the rows beyond an expert's live rows contribute nothing to
 // the weight-gradient products, which run over all C_pad rows).  16 bytes per lane.
 template <class S>
 __global__ __launch_bounds__(256) void bwd_gather_kernel(const void* __restrict__ x, const void* __restrict__ dout,
-                                                         const int32_t* __restrict__ slot_token, const float* __restrict__ slot_weight,
-                                                         int H, int C, int C_pad, void* __restrict__ xe, void* __restrict__ gy) {
-    constexpr int VEC = S::kVec;
+                                                         const int32_t* __restrict__ slot_token, int H, int C, int C_pad,
+                                                         void* __restrict__ xe, void* __restrict__ ge) {
     const size_t row = blockIdx.x;
     const int e = (int)(row / C_pad), s = (int)(row % C_pad);
     const int tok = s < C ? slot_token[(size_t)e * C + s] : -1;
-    const float w = tok >= 0 ? slot_weight[(size_t)e * C + s] : 0.0f;
-    const int row_chunks = H / VEC;
+    const int row_chunks = H / S::kVec;
     for (int c = threadIdx.x; c < row_chunks; c += 256) {
         u32x4 xv = {0u, 0u, 0u, 0u}, gv = {0u, 0u, 0u, 0u};
         if (tok >= 0) {
             xv = load_once(x, (size_t)tok * row_chunks + c);
-            float f[VEC];
-            chunk_to_floats<S>(load_once(dout, (size_t)tok * row_chunks + c), f);
-#pragma unroll
-            for (int q = 0; q < VEC; ++q) f[q] *= w;
-            gv = floats_to_chunk<S>(f);
+            gv = load_once(dout, (size_t)tok * row_chunks + c);
         }
         ((u32x4*)xe)[row * row_chunks + c] = xv;
-        ((u32x4*)gy)[row * row_chunks + c] = gv;
-    }
-}
-
-// Over [E, C_pad, I]: MODE 0: out = phi(a); MODE 1: out = g * phi'(a); rows at or beyond the expert's live rows give 0.
-template <class S, int MODE>
-__global__ __launch_bounds__(256) void bwd_act_kernel(const void* __restrict__ a, const void* __restrict__ g,
-                                                      const int32_t* __restrict__ expert_demand, int C, int C_pad, int I, int act,
-                                                      void* __restrict__ out) {
-    constexpr int VEC = S::kVec;
-    const size_t row = blockIdx.x;
-    const int e = (int)(row / C_pad), s = (int)(row % C_pad);
-    const bool live = s < min(expert_demand[e], C);
-    const int row_chunks = I / VEC;
-    for (int c = threadIdx.x; c < row_chunks; c += 256) {
-        u32x4 o = {0u, 0u, 0u, 0u};
-        if (live) {
-            float av[VEC], v[VEC];
-            chunk_to_floats<S>(load_once(a, row * row_chunks + c), av);
-            if constexpr (MODE == 0) {
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) v[q] = apply_act(av[q], act);
-            } else {
-                float gf[VEC];
-                chunk_to_floats<S>(load_once(g, row * row_chunks + c), gf);
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) v[q] = gf[q] * act_grad(av[q], act);
-            }
-            o = floats_to_chunk<S>(v);
-        }
-        ((u32x4*)out)[row * row_chunks + c] = o;
+        ((u32x4*)ge)[row * row_chunks + c] = gv;
     }
 }
 
@@ -130,46 +94,92 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-// One wavefront per token (k <= 64): dL/dw_ij = <dout_i, y_ij> for kept pairs (0 for dropped ones), then the
-// Jacobian of the softmax over the k selected logits: dl_ij = w_ij (dL/dw_ij - sum_j' w_ij' dL/dw_ij').
+// One workgroup per slot row (e, s), s < C_pad: with w the row's combine weight and dh = dout W2^T (fp32),
+//   h = w phi(a),  da = w dh phi'(a)  (fp32 storage: may be in the place of dh),
+//   p[e, s] = w (<phi(a), dh> + <dout, b2>)  =  w <dout, phi(a) W2 + b2>,
+// the weight times the gradient with respect to it.  dh is there anyway, so the gate's Jacobian needs neither
+// y = phi(a) W2 + b2 nor another pass over dout (a sixth of the backward pass's matrix work: at T = 16384, H = I = 2048,
+// E = 128, bf16 that product, the dot products with its rows and a separate pass for h were 0.36 of 3.2 ms; at T = 2048,
+// H = 1024, I = 4096, E = 16, fp32 0.43 of 2.02 ms).  The weight goes to h and da in fp32, so dout itself is the other operand
+// of dW2 and is not rounded again.  Rows at or beyond the expert's live rows give h = da = 0 (p is not written).  The row's sum is
+// added in a fixed order.
+template <class S>
+__global__ __launch_bounds__(256) void bwd_act_kernel(const void* __restrict__ a, const float* dh, const void* __restrict__ ge,
+                                                      const void* __restrict__ b2, const int32_t* __restrict__ expert_demand,
+                                                      const float* __restrict__ slot_weight, int C, int C_pad, int H, int I, int act,
+                                                      void* __restrict__ h, void* da, float* __restrict__ p) {
+    constexpr int VEC = S::kVec;
+    __shared__ float part[4];
+    const size_t row = blockIdx.x;
+    const int e = (int)(row / C_pad), s = (int)(row % C_pad);
+    const bool live = s < min(expert_demand[e], C);
+    const float w = live ? slot_weight[(size_t)e * C + s] : 0.0f;
+    const int row_chunks = I / VEC;
+    float sum = 0.0f;
+    for (int c = threadIdx.x; c < row_chunks; c += 256) {
+        u32x4 o = {0u, 0u, 0u, 0u}, d = {0u, 0u, 0u, 0u};
+        if (live) {
+            float av[VEC], gf[VEC], hv[VEC];
+            chunk_to_floats<S>(load_once(a, row * row_chunks + c), av);
+#pragma unroll
+            for (int q = 0; q < VEC; q += 4) {
+                const f32x4 g4 = __builtin_nontemporal_load((const f32x4*)(dh + row * I + (size_t)c * VEC + q));
+                gf[q] = g4[0]; gf[q + 1] = g4[1]; gf[q + 2] = g4[2]; gf[q + 3] = g4[3];
+            }
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                const float v = apply_act(av[q], act);
+                sum = fmaf(v, gf[q], sum);
+                hv[q] = w * v;
+                gf[q] *= w * act_grad(av[q], act);
+            }
+            o = floats_to_chunk<S>(hv);
+            d = floats_to_chunk<S>(gf);
+        }
+        ((u32x4*)h)[row * row_chunks + c] = o;
+        ((u32x4*)da)[row * row_chunks + c] = d;
+    }
+    if (!live) return;                                  // the same for the whole workgroup
+    if (b2) {
+        const int out_chunks = H / VEC;
+        for (int c = threadIdx.x; c < out_chunks; c += 256) {
+            float gf[VEC], bv[VEC];
+            chunk_to_floats<S>(load_once(ge, row * out_chunks + c), gf);
+            chunk_to_floats<S>(((const u32x4*)b2)[(size_t)e * out_chunks + c], bv);
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) sum = fmaf(gf[q], bv[q], sum);
+        }
+    }
+    sum = wave_sum(sum);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) p[row] = w * (part[0] + part[1] + part[2] + part[3]);
+}
+
+// One wavefront per token (k <= 64): p_ij = w_ij dL/dw_ij of kept pairs (0 for dropped ones), then the Jacobian of the
+// softmax over the k selected logits: dl_ij = w_ij (dL/dw_ij - sum_j' w_ij' dL/dw_ij') = p_ij - w_ij sum_j' p_ij'.
 // Writes dl[T, k] (fp32) and the dense matrix dL[T, ld] (storage type, zero where the token did not select the
 // expert), which turns dWg = x^T dL into a GEMM.
 template <class S>
-__global__ __launch_bounds__(256) void bwd_gate_kernel(const void* __restrict__ dout, const void* __restrict__ y,
-                                                       const int32_t* __restrict__ topk_expert, const float* __restrict__ topk_weight,
-                                                       const int32_t* __restrict__ slot, int T, int T_pad, int H, int k, int E, int C,
-                                                       int C_pad, int ld, float* __restrict__ dl, void* __restrict__ dL) {
+__global__ __launch_bounds__(256) void bwd_gate_kernel(const float* __restrict__ p, const int32_t* __restrict__ topk_expert,
+                                                       const float* __restrict__ topk_weight, const int32_t* __restrict__ slot,
+                                                       int T, int T_pad, int k, int E, int C, int C_pad, int ld,
+                                                       float* __restrict__ dl, void* __restrict__ dL) {
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (t >= T) {                                       // rows T .. T_pad - 1 of dL exist for the GEMM's sake: zeros
         if (t < T_pad)
             for (int c = lane; c < ld; c += 64) store_from_float<S>(dL, (size_t)t * ld + c, 0.0f);
         return;
     }
-    const int row_chunks = H / S::kVec;
-    int e_l = -1, s_l = -1;
-    float w_l = 0.0f, dw_l = 0.0f;
+    int e_l = -1;
+    float w_l = 0.0f, p_l = 0.0f;
     if (lane < k) {
         e_l = topk_expert[(size_t)t * k + lane];
-        s_l = slot[(size_t)t * k + lane];
         w_l = topk_weight[(size_t)t * k + lane];
+        const int s = slot[(size_t)t * k + lane];
+        if (s >= 0 && s < C && e_l >= 0 && e_l < E) p_l = p[(size_t)e_l * C_pad + s];
     }
-    for (int j = 0; j < k; ++j) {
-        const int e = __shfl(e_l, j), s = __shfl(s_l, j);
-        if (s < 0 || s >= C || e < 0 || e >= E) continue;      // wave-uniform
-        const size_t row = (size_t)e * C_pad + s;
-        float part = 0.0f;
-        for (int c = lane; c < row_chunks; c += 64) {   // 16 bytes of both rows per lane and step
-            float dv[S::kVec], yv[S::kVec];
-            chunk_to_floats<S>(load_once(dout, (size_t)t * row_chunks + c), dv);
-            chunk_to_floats<S>(load_once(y, row * row_chunks + c), yv);
-#pragma unroll
-            for (int q = 0; q < S::kVec; ++q) part = fmaf(dv[q], yv[q], part);
-        }
-        const float d = wave_sum(part);
-        if (lane == j) dw_l = d;
-    }
-    const float mean = wave_sum(w_l * dw_l);
-    const float dl_l = w_l * (dw_l - mean);
+    const float dl_l = p_l - w_l * wave_sum(p_l);
     if (lane < k) dl[(size_t)t * k + lane] = dl_l;
     for (int c = lane; c < ld; c += 64) {
         float v = 0.0f;
@@ -211,12 +221,13 @@ __global__ __launch_bounds__(256) void bwd_transpose_kernel(const elem* __restri
     }
 }
 
-// out[e][c] = sum over the live rows r of in[e][r][c] (fp32).  A workgroup of four wavefronts owns 64 chunks of 16
+// out[e][c] = sum over the live rows r of weight[e][r] in[e][r][c] (fp32; WEIGHTED false: of in[e][r][c]).  A workgroup of four wavefronts owns 64 chunks of 16
 // bytes of the columns of one expert; wavefront w adds the rows w, w + 4, ... in ascending order, four loads in flight
 // per lane, and the four partial sums are added in wavefront order: a fixed order, the same from run to run.
-template <class S>
-__global__ __launch_bounds__(256) void bwd_colsum_kernel(const void* __restrict__ in, const int32_t* __restrict__ expert_demand, int C,
-                                                         int C_pad, int cols, float* __restrict__ out) {
+template <class S, bool WEIGHTED>
+__global__ __launch_bounds__(256) void bwd_colsum_kernel(const void* __restrict__ in, const float* __restrict__ weight,
+                                                         const int32_t* __restrict__ expert_demand, int C, int C_pad, int cols,
+                                                         float* __restrict__ out) {
     constexpr int VEC = S::kVec;
     __shared__ float part[3][64][VEC];
     const int e = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -227,18 +238,13 @@ __global__ __launch_bounds__(256) void bwd_colsum_kernel(const void* __restrict_
     for (int q = 0; q < VEC; ++q) acc[q] = 0.0f;
     if (c < row_chunks) {
         const u32x4* p = (const u32x4*)in + (size_t)e * C_pad * row_chunks + c;
-        auto add = [&](const u32x4& v) {
-            if constexpr (S::kBytes == 4) {
+        const float* const wrow = WEIGHTED ? weight + (size_t)e * C : nullptr;
+        auto add = [&](const u32x4& v, int r) {
+            float f[VEC];
+            chunk_to_floats<S>(v, f);
+            const float w = WEIGHTED ? wrow[r] : 1.0f;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) { const uint32_t u = v[q]; acc[q] += __builtin_bit_cast(float, u); }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t u = v[q];
-                    acc[2 * q] += bits16_to_float<S>((uint16_t)(u & 0xffffu));
-                    acc[2 * q + 1] += bits16_to_float<S>((uint16_t)(u >> 16));
-                }
-            }
+            for (int q = 0; q < VEC; ++q) acc[q] = WEIGHTED ? fmaf(w, f[q], acc[q]) : acc[q] + f[q];
         };
         int r = wave;
         for (; r + 12 < n; r += 16) {
@@ -246,9 +252,9 @@ __global__ __launch_bounds__(256) void bwd_colsum_kernel(const void* __restrict_
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = __builtin_nontemporal_load(p + (size_t)(r + 4 * i) * row_chunks);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) add(v[i]);
+            for (int i = 0; i < 4; ++i) add(v[i], r + 4 * i);
         }
-        for (; r < n; r += 4) add(__builtin_nontemporal_load(p + (size_t)r * row_chunks));
+        for (; r < n; r += 4) add(__builtin_nontemporal_load(p + (size_t)r * row_chunks), r);
     }
     if (wave > 0) {
 #pragma unroll
@@ -359,33 +365,33 @@ hipError_t launch_bwd_fill_rows(int32_t* rows, int E, int first, int second, hip
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, const float* slot_weight, int H, int E,
-                             int C, int C_pad, int dtype, void* xe, void* gy, hipStream_t s) {
+hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, int H, int E, int C, int C_pad, int dtype,
+                             void* xe, void* ge, hipStream_t s) {
     const dim3 g((unsigned)((size_t)E * C_pad)), b(256);
-    if (dtype == 0) hipLaunchKernelGGL(bwd_gather_kernel<F32>, g, b, 0, s, x, dout, slot_token, slot_weight, H, C, C_pad, xe, gy);
-    else if (dtype == 1) hipLaunchKernelGGL(bwd_gather_kernel<BF16>, g, b, 0, s, x, dout, slot_token, slot_weight, H, C, C_pad, xe, gy);
-    else hipLaunchKernelGGL(bwd_gather_kernel<F16>, g, b, 0, s, x, dout, slot_token, slot_weight, H, C, C_pad, xe, gy);
+    if (dtype == 0) hipLaunchKernelGGL(bwd_gather_kernel<F32>, g, b, 0, s, x, dout, slot_token, H, C, C_pad, xe, ge);
+    else if (dtype == 1) hipLaunchKernelGGL(bwd_gather_kernel<BF16>, g, b, 0, s, x, dout, slot_token, H, C, C_pad, xe, ge);
+    else hipLaunchKernelGGL(bwd_gather_kernel<F16>, g, b, 0, s, x, dout, slot_token, H, C, C_pad, xe, ge);
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_act(const void* a, const void* g_in, const int32_t* expert_demand, int E, int C, int C_pad, int I, int act,
-                          int dtype, bool grad, void* out, hipStream_t s) {
+hipError_t launch_bwd_act(const void* a, const float* dh, const void* ge, const void* b2, const int32_t* expert_demand,
+                          const float* slot_weight, int E, int C, int C_pad, int H, int I, int act, int dtype, void* h, void* da, float* p,
+                          hipStream_t s) {
     const dim3 g((unsigned)((size_t)E * C_pad)), b(256);
-#define MOE_BWD_ACT(S_, M_) hipLaunchKernelGGL((bwd_act_kernel<S_, M_>), g, b, 0, s, a, g_in, expert_demand, C, C_pad, I, act, out)
-    if (dtype == 0) { if (grad) MOE_BWD_ACT(F32, 1); else MOE_BWD_ACT(F32, 0); }
-    else if (dtype == 1) { if (grad) MOE_BWD_ACT(BF16, 1); else MOE_BWD_ACT(BF16, 0); }
-    else { if (grad) MOE_BWD_ACT(F16, 1); else MOE_BWD_ACT(F16, 0); }
+#define MOE_BWD_ACT(S_) hipLaunchKernelGGL(bwd_act_kernel<S_>, g, b, 0, s, a, dh, ge, b2, expert_demand, slot_weight, C, C_pad, H, I, act, h, da, p)
+    if (dtype == 0) MOE_BWD_ACT(F32);
+    else if (dtype == 1) MOE_BWD_ACT(BF16);
+    else MOE_BWD_ACT(F16);
 #undef MOE_BWD_ACT
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_gate(const void* dout, const void* y, const int32_t* topk_expert, const float* topk_weight, const int32_t* slot,
-                           int T, int T_pad, int H, int k, int E, int C, int C_pad, int ld, int dtype, float* dl, void* dL,
-                           hipStream_t s) {
+hipError_t launch_bwd_gate(const float* p, const int32_t* topk_expert, const float* topk_weight, const int32_t* slot, int T, int T_pad,
+                           int k, int E, int C, int C_pad, int ld, int dtype, float* dl, void* dL, hipStream_t s) {
     const dim3 g((unsigned)((T_pad + 3) / 4)), b(256);
-    if (dtype == 0) hipLaunchKernelGGL(bwd_gate_kernel<F32>, g, b, 0, s, dout, y, topk_expert, topk_weight, slot, T, T_pad, H, k, E, C, C_pad, ld, dl, dL);
-    else if (dtype == 1) hipLaunchKernelGGL(bwd_gate_kernel<BF16>, g, b, 0, s, dout, y, topk_expert, topk_weight, slot, T, T_pad, H, k, E, C, C_pad, ld, dl, dL);
-    else hipLaunchKernelGGL(bwd_gate_kernel<F16>, g, b, 0, s, dout, y, topk_expert, topk_weight, slot, T, T_pad, H, k, E, C, C_pad, ld, dl, dL);
+    if (dtype == 0) hipLaunchKernelGGL(bwd_gate_kernel<F32>, g, b, 0, s, p, topk_expert, topk_weight, slot, T, T_pad, k, E, C, C_pad, ld, dl, dL);
+    else if (dtype == 1) hipLaunchKernelGGL(bwd_gate_kernel<BF16>, g, b, 0, s, p, topk_expert, topk_weight, slot, T, T_pad, k, E, C, C_pad, ld, dl, dL);
+    else hipLaunchKernelGGL(bwd_gate_kernel<F16>, g, b, 0, s, p, topk_expert, topk_weight, slot, T, T_pad, k, E, C, C_pad, ld, dl, dL);
     return hipGetLastError();
 }
 
@@ -416,14 +422,16 @@ hipError_t launch_bwd_transpose(const void* in, void* out, int groups, int R, in
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_colsum(const void* in, const int32_t* expert_demand, int E, int C, int C_pad, int cols, int dtype, float* out,
-                             hipStream_t s) {
+hipError_t launch_bwd_colsum(const void* in, const float* weight, const int32_t* expert_demand, int E, int C, int C_pad, int cols,
+                             int dtype, float* out, hipStream_t s) {
     if (E > 65535) return hipErrorInvalidValue;
     const int chunks = cols / (dtype == 0 ? 4 : 8);      // 16-byte chunks per row (cols is a multiple of 8)
     const dim3 g((unsigned)((chunks + 63) / 64), (unsigned)E), b(256);
-    if (dtype == 0) hipLaunchKernelGGL(bwd_colsum_kernel<F32>, g, b, 0, s, in, expert_demand, C, C_pad, cols, out);
-    else if (dtype == 1) hipLaunchKernelGGL(bwd_colsum_kernel<BF16>, g, b, 0, s, in, expert_demand, C, C_pad, cols, out);
-    else hipLaunchKernelGGL(bwd_colsum_kernel<F16>, g, b, 0, s, in, expert_demand, C, C_pad, cols, out);
+#define MOE_BWD_COLSUM(S_, W_) hipLaunchKernelGGL((bwd_colsum_kernel<S_, W_>), g, b, 0, s, in, weight, expert_demand, C, C_pad, cols, out)
+    if (dtype == 0) { if (weight) MOE_BWD_COLSUM(F32, true); else MOE_BWD_COLSUM(F32, false); }
+    else if (dtype == 1) { if (weight) MOE_BWD_COLSUM(BF16, true); else MOE_BWD_COLSUM(BF16, false); }
+    else { if (weight) MOE_BWD_COLSUM(F16, true); else MOE_BWD_COLSUM(F16, false); }
+#undef MOE_BWD_COLSUM
     return hipGetLastError();
 }
 

@@ -137,23 +137,25 @@ hipError_t layer_stage_ms(double* ms, int n, hipStream_t stream);
 // ---- backward pass helpers (backward.hip); buffers per expert have C_pad rows ----------------------------
 // rows[0 .. E) = first, rows[E .. 2 E) = second
 hipError_t launch_bwd_fill_rows(int32_t* rows, int E, int first, int second, hipStream_t s);
-// xe[e, s, :] = x[token] and gy[e, s, :] = weight * dout[token] for live slots, zeros for empty ones (s < C_pad)
-hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, const float* slot_weight, int H, int E,
-                             int C, int C_pad, int dtype, void* xe, void* gy, hipStream_t s);
-// over [E, C_pad, I]: out = phi(a), or with grad: out = g_in * phi'(a); rows beyond an expert's live rows give 0
-hipError_t launch_bwd_act(const void* a, const void* g_in, const int32_t* expert_demand, int E, int C, int C_pad, int I, int act,
-                          int dtype, bool grad, void* out, hipStream_t s);
+// xe[e, s, :] = x[token] and ge[e, s, :] = dout[token] for live slots, zeros for empty ones (s < C_pad)
+hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, int H, int E, int C, int C_pad, int dtype,
+                             void* xe, void* ge, hipStream_t s);
+// over [E, C_pad, I], w = slot_weight[e, s]: h = w phi(a), da = w dh phi'(a), p[e, s] = w (<phi(a), dh> + <ge, b2>) (b2
+// optional; da may be dh in fp32 storage); rows beyond an expert's live rows give h = da = 0
+hipError_t launch_bwd_act(const void* a, const float* dh, const void* ge, const void* b2, const int32_t* expert_demand,
+                          const float* slot_weight, int E, int C, int C_pad, int H, int I, int act, int dtype, void* h, void* da, float* p,
+                          hipStream_t s);
 // dl[T, k] (fp32) and dL[T_pad, ld] (storage type, dense; rows at and beyond T zero): gradient with respect to the
-// selected gate logits (k <= 64)
-hipError_t launch_bwd_gate(const void* dout, const void* y, const int32_t* topk_expert, const float* topk_weight, const int32_t* slot,
-                           int T, int T_pad, int H, int k, int E, int C, int C_pad, int ld, int dtype, float* dl, void* dL, hipStream_t s);
+// selected gate logits (k <= 64) from p
+hipError_t launch_bwd_gate(const float* p, const int32_t* topk_expert, const float* topk_weight, const int32_t* slot, int T, int T_pad,
+                           int k, int E, int C, int C_pad, int ld, int dtype, float* dl, void* dL, hipStream_t s);
 // out[i] = sum over g < slices of part[g * n + i], in ascending g (n a multiple of 4, 16-byte aligned buffers)
 hipError_t launch_bwd_sum_slices(const float* part, int slices, long long n, float* out, hipStream_t s);
 // out[g][c][r] = in[g][r][c], r < R, c < Cc; rows of out have ld_out entries, zero at and beyond R
 hipError_t launch_bwd_transpose(const void* in, void* out, int groups, int R, int Cc, int ld_out, int dtype, hipStream_t s);
-// out[e][c] = sum over live rows of in[e][r][c] (fp32)
-hipError_t launch_bwd_colsum(const void* in, const int32_t* expert_demand, int E, int C, int C_pad, int cols, int dtype, float* out,
-                             hipStream_t s);
+// out[e][c] = sum over live rows of weight[e][r] in[e][r][c] (fp32); weight == nullptr: of in[e][r][c]
+hipError_t launch_bwd_colsum(const void* in, const float* weight, const int32_t* expert_demand, int E, int C, int C_pad, int cols,
+                             int dtype, float* out, hipStream_t s);
 hipError_t launch_bwd_gate_bias(const int32_t* topk_expert, const float* dl, int T, int k, int E, float* dgate_bias, hipStream_t s);
 // dx[t, :] = sum of the kept choices' rows of dxe + sum over choices of dl * WgT[expert, :]
 hipError_t launch_bwd_dx(const void* dxe, const void* WgT, const int32_t* topk_expert, const int32_t* slot, const float* dl, int T, int H,
