@@ -326,8 +326,14 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
             for (int i = 0; i < (ONE ? 1 : A_ITEMS); ++i) store_a(i, n_off);
         }
         if constexpr (ONE && q == kA2) store_a(1, n_off);
-        // the rows of the next block with products (of the next K-tile after the last one; then read past barrier X)
+        // the rows of the next block with products; after the last one they are the next K-tile's, whose planes are only
+        // written once barrier X is passed: a wavefront that is done with its products before reads them there
         constexpr int next = q % TM + 1 < LIVE ? q + 1 : q < TM ? TM : NB;
+        constexpr bool late = LIVE > 0 && TM + LIVE - 1 < kX;
+        if constexpr (late && q == kX) {
+#pragma unroll
+            for (int px = 0; px < 3; ++px) xf.p[px] = read_x(0, n_off, px);
+        }
         if constexpr (q % TM < LIVE) {
             // each piece of the rows is read for the next block once this one is done with it: ordered like this, every
             // read has at least half a block to arrive and no second set of registers is needed
@@ -336,7 +342,10 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
 #pragma unroll
                 for (int j = 0; j < HN; ++j) acc[t][h * HN + j] = mma_bf16(wf[h * HN + j].p[pw], xf.p[px], acc[t][h * HN + j]);
             };
-            auto fetch = [&](int px) __attribute__((always_inline)) { xf.p[px] = read_x(next % TM, next < NB ? s_off : n_off, px); };
+            auto fetch = [&](int px) __attribute__((always_inline)) {
+                if constexpr (next < NB || !late) xf.p[px] = read_x(next % TM, next < NB ? s_off : n_off, px);
+            };
+            static_assert(next < NB || late || q >= kX, "the next K-tile's planes are read after barrier X");
             mma(0, 2);
             fetch(2);
             mma(1, 1);
