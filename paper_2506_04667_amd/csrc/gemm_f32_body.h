@@ -81,9 +81,29 @@ __device__ __forceinline__ f32x4 mma_bf16(const u32x4& w, const u32x4& x, const 
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
 }
 
+__device__ __forceinline__ bool any_nan(const f32x4& v) { return v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]; }
+
+// Columns col .. col + 3 of a row, one fp32 product after the other, with bias, activation and store.  The pieces of an
+// infinity are an infinity and NaNs, so every sum it enters comes out NaN above, where fp32 products give an infinity (or
+// a NaN); an overflowing product's smaller terms can meet its infinity with the other sign too.  Sums that came out NaN
+// therefore pass through here before anybody sees them: seldom, so what counts is that the others do not pay.
+template <bool NT>
+__device__ __forceinline__ void f32_sums_again(const GemmArgs& a, int grp, int row, int col) {
+    const size_t src = a.a_row_index ? (size_t)a.a_row_index[(size_t)grp * a.a_index_stride + row] : (size_t)row;
+    const float* const x = (const float*)a.A + (a.a_row_index ? (size_t)0 : (size_t)grp * a.a_group_stride) + src * a.lda;
+    const float* const w = (const float*)a.B + (size_t)grp * a.b_group_stride;
+    for (int q = 0; q < 4 && col + q < a.N; ++q) {
+        const size_t n = col + q;
+        float s = 0.0f;
+        for (int k = 0; k < a.K && s == s; ++k) s = fmaf(x[k], NT ? w[n * a.ldb + k] : w[(size_t)k * a.ldb + n], s);
+        if (a.bias) s += ((const float*)a.bias)[(size_t)grp * a.bias_group_stride + n];
+        ((float*)a.C)[(size_t)grp * a.c_group_stride + (size_t)row * a.ldc + n] = apply_act(s, a.act);
+    }
+}
+
 // Bias, activation and store of a wavefront's sums: four consecutive columns of one row per lane and MFMA tile.  With
 // `partial` the raw sums of the row tiles with live rows go there instead.
-template <int WM, int TM, int TN, int BN>
+template <bool NT, int WM, int TM, int TN, int BN>
 __device__ __forceinline__ void f32_epilogue(const GemmArgs& a, f32x4 (&acc)[TM][TN], int grp, int row0, int n0, int rows, int wm, int wn,
                                              int live, int r16, int kq, float* __restrict__ partial) {
     auto tile_row = [&](int t) __attribute__((always_inline)) { return ((t >> 1) * WM + wm) * 32 + (t & 1) * 16; };
@@ -101,6 +121,8 @@ __device__ __forceinline__ void f32_epilogue(const GemmArgs& a, f32x4 (&acc)[TM]
     float* const c_base = (float*)a.C + (size_t)grp * a.c_group_stride;
     const bool vec = (N & 3) == 0 && (ldc & 3) == 0;    // whole 16-byte stores (the group stride is a multiple of 4 too)
     const float* const bias = a.bias ? (const float*)a.bias + (size_t)grp * a.bias_group_stride : nullptr;
+    static_assert(TM * TN <= 32, "one bit per MFMA tile");
+    uint32_t again = 0;
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const int col = n0 + (wn * TN + tn) * 16 + kq * 4;
@@ -114,6 +136,7 @@ __device__ __forceinline__ void f32_epilogue(const GemmArgs& a, f32x4 (&acc)[TM]
         for (int t = 0; t < TM; ++t) {
             const int row = row0 + tile_row(t) + r16;
             if (row >= rows) continue;
+            if (any_nan(acc[t][tn])) again |= 1u << (tn * TM + t);
             f32x4 v;
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = apply_act(acc[t][tn][q] + bv[q], act);
@@ -126,6 +149,10 @@ __device__ __forceinline__ void f32_epilogue(const GemmArgs& a, f32x4 (&acc)[TM]
                     if (col + q < N) c[q] = v[q];
             }
         }
+    }
+    for (; again; again &= again - 1) {
+        const int b = __builtin_ctz(again), t = b % TM, tn = b / TM;
+        f32_sums_again<NT>(a, grp, row0 + tile_row(t) + r16, n0 + (wn * TN + tn) * 16 + kq * 4);
     }
 }
 
@@ -411,7 +438,7 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
     else if (TM >= 8) main_loop(std::integral_constant<int, (TM >= 8 ? 6 : TM)>{});
     wait_copies_and_barrier<0>();
 
-    f32_epilogue<WM, TM, TN, BN>(a, acc, grp, row0, n0, rows, wm, wn, live, r16, kq, partial);
+    f32_epilogue<NT, WM, TM, TN, BN>(a, acc, grp, row0, n0, rows, wm, wn, live, r16, kq, partial);
 }
 
 // The same tile body for at most 64 rows (a decode step's experts, the last rows of a larger group): 64 x 256, 8 wavefronts
@@ -570,7 +597,7 @@ __device__ __forceinline__ void f32_tile_low(const GemmArgs& a, unsigned char* s
     if (live == TM) main_loop(std::integral_constant<int, TM>{});
     else main_loop(std::integral_constant<int, 2>{});
     wait_copies_and_barrier<0>();
-    f32_epilogue<1, TM, TN, BN>(a, acc, grp, row0, n0, rows, 0, wave, live, r16, kq, partial);
+    f32_epilogue<NT, 1, TM, TN, BN>(a, acc, grp, row0, n0, rows, 0, wave, live, r16, kq, partial);
 }
 
 }  // namespace

@@ -83,3 +83,32 @@ def test_ends_of_the_range(big, small):
     assert torch.isfinite(got).all()
     # pieces of `small` below 2^-126 may be flushed: an absolute error of 2^-126 |x| per product
     assert bool(((got - ref).abs() <= 2.0 ** -21 * ref.abs() + 2.0 ** -126 * abs(big) + 2.0 ** -149).all()), float(((got - ref).abs() / ref.abs()).max())
+
+
+# groups x rows, by tile body: 64 x 64, 64 x 256, 128 x 128, equal spans with cut tiles (twice: large and 64-row body), whole 256 x 256 tiles
+@pytest.mark.parametrize("E,rows,H,I", [(2, 9, 64, 72), (64, 33, 512, 512), (9, 300, 776, 264), (4, 300, 2048, 1024), (4, 50, 4096, 2048),
+                                        (40, 257, 200, 3336)])
+def test_infinities(E, rows, H, I):
+    # relu(x W1) W2 with positive W2: an infinite sum stays one, and the other rows and columns do not see it.  Infinities in one
+    # row of x and in one entry of W1 (columns of h that are +inf where x[:, 3] > 0 and 0 where it is negative)
+    cfg = moe.make_config(E * rows, H, I, E, 1, 1.0, "relu", "f32")
+    b = moe.Buffers(cfg)
+    b.alloc_staged()
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    n = lambda *s: torch.empty(s, device="cuda").normal_(generator=gen)
+    x, W1, W2 = n(E, rows, H), n(E, H, I) / math.sqrt(H), (n(E, I, H).abs() + 0.1) / I
+    x[0, rows // 2, H - 3] = float("inf")
+    x[E - 1, rows - 1, 0] = 3e38
+    W1[E - 1, 0] *= 4e3                                 # finite factors whose products overflow
+    W1[1, 3, I // 2] = float("inf")
+    b.xe[:, :rows] = x
+    b.expert_demand.fill_(rows)
+    moe.moe_expert_ffn(cfg, b.workspace, b.xe, b.expert_demand, W1, None, W2, None, b.y)
+    h = torch.stack([torch.relu((x[e].double() @ W1[e].double()).float()) for e in range(E)])     # overflow: to float's infinity
+    ref = torch.stack([h[e].double() @ W2[e].double() for e in range(E)])
+    got = b.y[:, :rows].double()
+    assert bool(torch.isinf(ref).any()) and not bool(torch.isnan(ref).any())
+    assert torch.equal(torch.isinf(got), torch.isinf(ref)) and not bool(torch.isnan(got).any())
+    fin = torch.isfinite(ref)
+    # both operands of the second product are positive, the first one's sums have a relative error of sqrt(K) 2^-24 of the rms
+    assert float((got - ref)[fin].norm() / ref[fin].norm()) < (math.sqrt(H) + math.sqrt(I)) * 2.0 ** -24
