@@ -405,21 +405,19 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     // dh = dout W2^T in fp32 (W2[e] read as [N = I][K = H]); h = w phi(a), da = w dh phi'(a); dxe = da W1^T (W1[e] as [N = H][K = I])
     moe::GemmArgs d1 = g;
     d1.A = ge; d1.a_group_stride = rH; d1.lda = H; d1.B = W2; d1.b_group_stride = HI; d1.ldb = H; d1.b_is_nk = true;
-    d1.C = dh; d1.c_group_stride = rI; d1.ldc = I; d1.N = I; d1.K = H; d1.c_f32 = true;
+    d1.units = units; d1.C = dh; d1.c_group_stride = rI; d1.ldc = I; d1.N = I; d1.K = H; d1.c_f32 = true;
     MOE_TRY(moe::launch_grouped_gemm(d1, s));
     MOE_TRY(moe::launch_bwd_act(a, dh, ge, b2, demand, slot_weight, E, C, C_pad, H, I, c->act, dt, h, da, row_p, s));
     // gate: w dL/dw of every kept pair is in row_p; the softmax Jacobian
     MOE_TRY(moe::launch_bwd_gate(row_p, topk_expert, topk_weight, slot, T, b.T_pad, k, E, C, C_pad, b.ldL, dt, dl, dL, s));
     moe::GemmArgs d2 = g;
     d2.A = da; d2.a_group_stride = rI; d2.lda = I; d2.B = W1; d2.b_group_stride = HI; d2.ldb = I; d2.b_is_nk = true;
-    d2.C = dxe; d2.c_group_stride = rH; d2.ldc = H; d2.N = H; d2.K = I;
+    d2.units = units; d2.C = dxe; d2.c_group_stride = rH; d2.ldc = H; d2.N = H; d2.K = I;
     MOE_TRY(moe::launch_grouped_gemm(d2, s));
-    // weight gradients as row-major GEMMs over all C_pad rows (rows beyond the live ones are zero):
-    // dW2[e] = h[e]^T ge[e], dW1[e] = xe[e]^T da[e]
-    MOE_TRY(moe::launch_bwd_transpose(h, hT, E, C_pad, I, C_pad, dt, s));
-    MOE_TRY(moe::launch_bwd_transpose(xe, xeT, E, C_pad, H, C_pad, dt, s));
+    // weight gradients over all C_pad rows (rows beyond the live ones are zero): dW2[e] = h[e]^T ge[e], dW1[e] = xe[e]^T da[e].
     // 16-bit storage: row counts and lists of row tiles, so that the persistent weight-streaming kernel takes them (each
-    // GEMM writes E H I floats from a contraction over only C_pad rows: its stores must overlap the next tile's loads)
+    // GEMM writes E H I floats from a contraction over only C_pad rows: its stores must overlap the next tile's loads), with
+    // h and xe read as they are stored, [slot][column]; where it does not take the shape they are transposed first.
     int32_t* wrows = (int32_t*)ws_at(ws, b.off_wrows);
     int32_t *wunits1 = nullptr, *wunits2 = nullptr;
     if (dt != MOE_F32) {
@@ -429,18 +427,22 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
         MOE_TRY(moe::launch_ffn_units(wrows, H, E, H, wunits1, s));
         MOE_TRY(moe::launch_ffn_units(wrows + E, I, E, I, wunits2, s));
     }
-    moe::GemmArgs w{};
-    w.rows_dev = nullptr; w.groups = E; w.dtype = dt; w.act = MOE_ACT_IDENTITY; w.c_f32 = true; w.K = C_pad; w.lda = C_pad;
-    moe::GemmArgs w2 = w;
-    if (wunits2) { w2.rows_dev = wrows + E; w2.units = wunits2; }
-    w2.A = hT; w2.a_group_stride = rI; w2.a_rows_total = I; w2.rows_fixed = I; w2.rows_cap = I; w2.max_rows = I;
-    w2.B = ge; w2.b_group_stride = rH; w2.ldb = H; w2.C = dW2; w2.c_group_stride = HI; w2.ldc = H; w2.N = H;
-    MOE_TRY(moe::launch_grouped_gemm(w2, s));
-    moe::GemmArgs w1 = w;
-    if (wunits1) { w1.rows_dev = wrows; w1.units = wunits1; }
-    w1.A = xeT; w1.a_group_stride = rH; w1.a_rows_total = H; w1.rows_fixed = H; w1.rows_cap = H; w1.max_rows = H;
-    w1.B = da; w1.b_group_stride = rI; w1.ldb = I; w1.C = dW1; w1.c_group_stride = HI; w1.ldc = I; w1.N = I;
-    MOE_TRY(moe::launch_grouped_gemm(w1, s));
+    auto weight_grad = [&](const void* rows, int M, const int32_t* counts_dev, int32_t* list, void* rowsT, const void* grad, int N, float* out) {
+        moe::GemmArgs w{};
+        w.groups = E; w.dtype = dt; w.act = MOE_ACT_IDENTITY; w.c_f32 = true; w.K = C_pad;
+        w.A = rows; w.a_is_km = true; w.lda = M; w.a_group_stride = (long long)C_pad * M; w.a_rows_total = C_pad;
+        w.rows_dev = counts_dev; w.units = list; w.rows_fixed = M; w.rows_cap = M; w.max_rows = M;
+        w.B = grad; w.b_group_stride = (long long)C_pad * N; w.ldb = N;
+        w.C = out; w.c_group_stride = HI; w.ldc = N; w.N = N;
+        if (!moe::stream_gemm_eligible(w)) {
+            if (hipError_t e = moe::launch_bwd_transpose(rows, rowsT, E, C_pad, M, C_pad, dt, s); e != hipSuccess) return e;
+            w.A = rowsT; w.a_is_km = false; w.lda = C_pad; w.a_rows_total = M;
+            if (!list) w.rows_dev = nullptr;
+        }
+        return moe::launch_grouped_gemm(w, s);
+    };
+    MOE_TRY(weight_grad(h, I, wrows + E, wunits2, hT, ge, H, dW2));
+    MOE_TRY(weight_grad(xe, H, wrows, wunits1, xeT, da, I, dW1));
     MOE_TRY(moe::launch_bwd_colsum(ge, slot_weight, demand, E, C, C_pad, H, dt, db2, s));
     MOE_TRY(moe::launch_bwd_colsum(da, nullptr, demand, E, C, C_pad, I, dt, db1, s));
     // gate weights: dWg = x^T dL, dgate_bias = column sums of dl

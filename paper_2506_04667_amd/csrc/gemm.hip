@@ -137,6 +137,7 @@ hipError_t prepare_grouped_gemm() {
 hipError_t launch_grouped_gemm(const GemmArgs& a, hipStream_t stream) {
     if (a.groups <= 0 || a.max_rows <= 0 || a.N <= 0) return hipSuccess;
     if (stream_gemm_eligible(a)) return launch_grouped_gemm_stream(a, stream);
+    if (a.a_is_km) return hipErrorInvalidValue;
     if (f32_stream_eligible(a)) return launch_gemm_f32_stream(a, stream);
     if (f32_gemm_eligible(a)) return launch_gemm_f32(a, stream);
     switch (a.dtype) {

@@ -5,11 +5,11 @@
 namespace moe {
 namespace {
 
-template <class S, int ACT0, int NPH>
+template <class S, int ACT0, int NPH, int LAYOUT>
 __global__ __launch_bounds__(THREADS) void ffn_gemm_stream_kernel(StreamArgs a) {
     const int xcd = blockIdx.x % kXcds, wg = blockIdx.x / kXcds, wgs = gridDim.x / kXcds;
     if constexpr (NPH == 1) {
-        stream_gemm<S, ACT0, 0, false, false>(a, xcd, wg, wgs);
+        stream_gemm<S, ACT0, 0, false, false, LAYOUT>(a, xcd, wg, wgs);
     } else {
         if (threadIdx.x == 0) check_xcd_placement(a, xcd);
         stream_gemm<S, ACT0, 0, true, false>(a, xcd, wg, wgs);
@@ -25,17 +25,17 @@ __global__ __launch_bounds__(1024) void ffn_units_kernel(const int32_t* __restri
 }
 
 // the kernel's LDS limit on the current device (once per device)
-template <class S, int ACT0, int NPH>
+template <class S, int ACT0, int NPH, int LAYOUT = 0>
 hipError_t prepare_stream_t() {
     static DeviceFlags limit_raised = {};
-    return raise_lds_limit(reinterpret_cast<const void*>(ffn_gemm_stream_kernel<S, ACT0, NPH>), LDS_BYTES, limit_raised);
+    return raise_lds_limit(reinterpret_cast<const void*>(ffn_gemm_stream_kernel<S, ACT0, NPH, LAYOUT>), LDS_BYTES, limit_raised);
 }
 
 // g2 == nullptr: one GEMM.  Otherwise g2's A is g1's C and both share rows/groups/units.
-template <class S, int ACT0, int NPH>
+template <class S, int ACT0, int NPH, int LAYOUT = 0>
 hipError_t launch_stream_t(const GemmArgs& g1, const GemmArgs* g2, bool never_met, hipStream_t stream) {
-    auto kernel = ffn_gemm_stream_kernel<S, ACT0, NPH>;
-    if (hipError_t e = prepare_stream_t<S, ACT0, NPH>(); e != hipSuccess) return e;
+    auto kernel = ffn_gemm_stream_kernel<S, ACT0, NPH, LAYOUT>;
+    if (hipError_t e = prepare_stream_t<S, ACT0, NPH, LAYOUT>(); e != hipSuccess) return e;
     // units the lists can hold: every large row tile of every group, and one small tile per group
     const int nrow_l = ffn_units_nrow_large(g1.max_rows);
     const long long cap = (long long)g1.groups * (nrow_l + 1);
@@ -65,6 +65,10 @@ hipError_t launch_stream_t(const GemmArgs& g1, const GemmArgs* g2, bool never_me
 template <class S, int NPH>
 hipError_t launch_stream_act(const GemmArgs& g1, const GemmArgs* g2, bool never_met, hipStream_t stream) {
     if constexpr (NPH == 1) {
+        if (g1.a_is_km) return launch_stream_t<S, kActF32Out, 1, kLayoutKM>(g1, nullptr, never_met, stream);
+        if (g1.b_is_nk)
+            return g1.c_f32 ? launch_stream_t<S, kActF32Out, 1, kLayoutNK>(g1, nullptr, never_met, stream)
+                            : launch_stream_t<S, 3, 1, kLayoutNK>(g1, nullptr, never_met, stream);
         if (g1.c_f32) return launch_stream_t<S, kActF32Out, 1>(g1, nullptr, never_met, stream);
     }
     switch (g1.act) {
@@ -83,6 +87,9 @@ hipError_t prepare_stream_s() {
     if (e == hipSuccess) e = prepare_stream_t<S, 2, 1>();
     if (e == hipSuccess) e = prepare_stream_t<S, 3, 1>();
     if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1>();
+    if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1, kLayoutKM>();
+    if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1, kLayoutNK>();
+    if (e == hipSuccess) e = prepare_stream_t<S, 3, 1, kLayoutNK>();
     if (e == hipSuccess) e = prepare_stream_t<S, 0, 2>();
     if (e == hipSuccess) e = prepare_stream_t<S, 1, 2>();
     if (e == hipSuccess) e = prepare_stream_t<S, 2, 2>();
@@ -122,18 +129,21 @@ void ffn_units_fault_words(int groups, int max_rows, long long* first, long long
     *first = ffn_units_nrow_large(max_rows) ? 0 : *second;
 }
 
-bool stream_gemm_shape_ok(int dtype, int N, int K, int lda, int ldb, int ldc, long long a_rows_total) {
-    return dtype != 0 && K % (2 * BK) == 0 && K >= 6 * BK && N % 8 == 0 && N >= 256 && lda % 8 == 0 && ldb % 8 == 0 &&
+bool stream_gemm_shape_ok(int dtype, int N, int K, int lda, int ldb, int ldc, long long a_rows_total, bool a_is_km, bool b_is_nk) {
+    return dtype != 0 && K % (2 * BK) == 0 && K >= (b_is_nk ? 8 : 6) * BK && N % 8 == 0 && N >= 256 && lda % 8 == 0 && ldb % 8 == 0 &&
            ldc % 8 == 0 &&
            // copies address an operand as a 64-bit base plus 32-bit byte offsets
-           a_rows_total * lda * 2 < (1ll << 32) && (long long)K * ldb * 2 < (1ll << 32);
+           (a_is_km ? (long long)K : a_rows_total) * lda * 2 < (1ll << 32) && (long long)(b_is_nk ? N : K) * ldb * 2 < (1ll << 32);
 }
 
 bool stream_gemm_eligible(const GemmArgs& a) {
-    // fp32 output (the weight gradients of the backward pass): identity epilogue only
-    if (a.c_f32 && a.act != 3) return false;
-    return !a.b_is_nk && a.rows_dev != nullptr && a.units != nullptr &&
-           stream_gemm_shape_ok(a.dtype, a.N, a.K, a.lda, a.ldb, a.ldc, a.a_rows_total);
+    // the epilogues that the backward pass's forms need: fp32 output (weight gradients, <phi(a), dh>) and [n][k] weights take the
+    // identity, [k][m] activations fp32 output from packed rows whose count is a multiple of 8
+    if ((a.c_f32 || a.b_is_nk) && a.act != 3) return false;
+    if (a.b_is_nk && a.bias) return false;
+    if (a.a_is_km && (!a.c_f32 || a.b_is_nk || a.a_row_index || a.rows_cap % 8 != 0)) return false;
+    return a.rows_dev != nullptr && a.units != nullptr &&
+           stream_gemm_shape_ok(a.dtype, a.N, a.K, a.lda, a.ldb, a.ldc, a.a_rows_total, a.a_is_km, a.b_is_nk);
 }
 
 hipError_t launch_grouped_gemm_stream(const GemmArgs& a, hipStream_t stream) {
@@ -141,7 +151,7 @@ hipError_t launch_grouped_gemm_stream(const GemmArgs& a, hipStream_t stream) {
 }
 
 bool ffn_fused_eligible(const GemmArgs& g1, const GemmArgs& g2) {
-    return stream_gemm_eligible(g1) && stream_gemm_eligible(g2) && !g1.c_f32 && !g2.c_f32 && g2.act == 3 && g2.a_row_index == nullptr &&
+    return stream_gemm_eligible(g1) && stream_gemm_eligible(g2) && !g1.b_is_nk && !g2.b_is_nk && !g1.c_f32 && !g2.c_f32 && g2.act == 3 && g2.a_row_index == nullptr &&
            g1.units == g2.units && g1.rows_dev == g2.rows_dev && g1.rows_cap == g2.rows_cap &&
            g1.groups == g2.groups && g1.max_rows == g2.max_rows && g1.dtype == g2.dtype;
 }

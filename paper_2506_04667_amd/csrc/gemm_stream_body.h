@@ -34,6 +34,15 @@
 //            c ^ (((k & 3) << 1) | (((k >> 3) & 1) << 3)); read back in MFMA operand
 //            order with ds_read_b64_tr_b16 (the four 16-lane groups of a wavefront
 //            read the four k-octets of a K-tile).
+// The backward pass's operands come in two more layouts (LAYOUT bits), read as stored instead of through a transposed
+// copy (the copies were 0.14 ms and the register-staged kernel that took [n][k] 0.96 ms of 2.91 ms at T = 16384,
+// H = I = 2048, E = 128):
+//   kLayoutNK  weights stored [n][k] (the data gradients): copied in pairs of K-tiles like the activations, so that a
+//              request is a full line (with 64-byte rows every line crossed from HBM twice: 498 us per GEMM at that shape),
+//              through a ring of 3 stages of 32 KB (256 n x 128 B), requested 3 pairs ahead.  The third stage takes the
+//              place of the epilogue's LDS area: this epilogue pairs up lanes instead.  One wait and barrier per pair;
+//   kLayoutKM  activations stored [k][m] (the weight gradients, whose k runs over an expert's slots): a stage holds
+//              64 k x 256 G B, swizzled and read with the transpose read like the weights' [k][n].
 // Rows at or beyond the live row count are fetched from the last live row (their
 // products land in output rows that are never stored); columns beyond N likewise.
 // Because every lane supplies its own global address, the activation rows can be
@@ -46,7 +55,7 @@
 // transposes 32 rows at a time through a wave-private LDS area and stores full
 // 128-byte row segments.
 //
-// Requires K % 64 == 0, K >= 192 and N % 8 == 0; other shapes use the generic kernel.
+// Requires K % 64 == 0, K >= 192 (kLayoutNK: 256) and N % 8 == 0; other shapes use the generic kernel.
 #pragma once
 #include "common.h"
 #include "kernels.h"
@@ -143,6 +152,9 @@ struct StreamArgs {
 };
 
 constexpr int kSpinLimit = 1 << 21;
+constexpr int kLayoutNK = 1, kLayoutKM = 2;
+constexpr int B_PAIR_STAGE = BN * 128, B_PAIR_STAGES = 3;               // kLayoutNK: 256 n x 64 k
+static_assert(B_REGION + B_PAIR_STAGES * B_PAIR_STAGE <= LDS_BYTES, "three pairs of [n][k] weights");
 constexpr int kActF32Out = 4;                           // template value of ACT: identity with C (and bias) in fp32
 
 // The work of one workgroup on one list for one GEMM (phase PH of the arguments, activation ACT): `list` =
@@ -151,7 +163,7 @@ constexpr int kActF32Out = 4;                           // template value of ACT
 // one to its unit's completion counter.  WAIT: before the first copy of a task is requested, its unit's counter
 // must have reached a.wait_target (the tiles this task reads are then in the XCD's L2).  `handicap`: see
 // ffn_small_list_handicap (0 for the large list).
-template <class S, int ACT, int PH, bool COUNT, bool WAIT, int G>
+template <class S, int ACT, int PH, bool COUNT, bool WAIT, int G, int LAYOUT>
 __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, int cap, int xcd, int wg_local, int wg_stride,
                                             int handicap) {
     typedef uint16_t elem;
@@ -160,6 +172,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     const int32_t* const units = list + 1;              // [0] = live units, [1 + q] = group * nrow + row tile
     int32_t* const done = list + 2 + cap;               // [q] wavefronts that have stored a ph[0] tile of unit q; zero at launch
     constexpr int BM = 128 * G, TM = 4 * G;             // rows of a tile; 16-row MFMA tiles per wavefront
+    constexpr bool NK = (LAYOUT & kLayoutNK) != 0, KM = (LAYOUT & kLayoutKM) != 0;
+    constexpr int B_COPIES = NK ? 4 : 2;                // 1 KB copies per wavefront and request of weights (NK: two K-tiles)
     constexpr int A_COPIES = 2 * G;                     // 1 KB copies per wavefront and activation stage
     static_assert(BM == (G == 2 ? kUnitRowsLarge : kUnitRowsSmall), "the unit list is cut in row tiles of this kernel");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -244,11 +258,16 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         base_a = uniform((const unsigned char*)((const elem*)P.A + (P.a_row_index ? (size_t)0 : (size_t)t.grp * P.a_group_stride)));
         base_b = uniform((const unsigned char*)((const elem*)P.B + (size_t)t.grp * P.b_group_stride));
     };
-    auto task_offsets = [&](const Task& t, uint32_t (&oa)[4], uint32_t (&ob)[2]) __attribute__((always_inline)) {
+    auto task_offsets = [&](const Task& t, uint32_t (&oa)[4], uint32_t (&ob)[B_COPIES]) __attribute__((always_inline)) {
         const int32_t* row_index = P.a_row_index;
         const int lda = P.lda, ldb = P.ldb, N = P.N;
 #pragma unroll
         for (int j = 0; j < A_COPIES; ++j) {
+            if constexpr (KM) {                         // 1 KB = 4 / G k-rows of 16 G chunks; rows is a multiple of 8
+                const int k = (wave * A_COPIES + j) * (4 / G) + lane / (16 * G), c = lane % (16 * G) ^ swz_b(k);
+                oa[j] = (uint32_t)k * (uint32_t)(lda * 2) + min(t.row0 + c * 8, t.rows - 8) * 2;
+                continue;
+            }
             const int r = (wave * A_COPIES + j) * 8 + (lane >> 3), p = lane & 7;
             const int c = p ^ swz_a(r);
             int grow = min(t.row0 + r, t.rows - 1);
@@ -256,7 +275,12 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
             oa[j] = (uint32_t)grow * (uint32_t)(lda * 2) + c * 16;
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < B_COPIES; ++j) {
+            if constexpr (NK) {
+                const int r = (wave * 4 + j) * 8 + (lane >> 3), c = (lane & 7) ^ swz_a(r);
+                ob[j] = (uint32_t)min(t.n0 + r, N - 1) * (uint32_t)(ldb * 2) + c * 16;
+                continue;
+            }
             const int k = (wave * 2 + j) * 2 + (lane >> 5), p = lane & 31;
             const int c = p ^ swz_b(k);
             const int n = min(t.n0 + c * 8, N - 8);
@@ -271,7 +295,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     wait_for_unit(cur);
     const unsigned char *a_base, *b_base;               // copy cursors: bases advance along K
     const unsigned char *na_base, *nb_base;             // bases of the task after `cur`
-    uint32_t a_off[4], b_off[2], na_off[4], nb_off[2];
+    uint32_t a_off[4], b_off[B_COPIES], na_off[4], nb_off[B_COPIES];
     task_bases(cur, a_base, b_base);
     task_offsets(cur, a_off, b_off);
     nxt = cur;
@@ -287,13 +311,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 #pragma unroll
         for (int j = 0; j < A_COPIES; ++j) na_off[j] = a_off[j];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) nb_off[j] = b_off[j];
+        for (int j = 0; j < B_COPIES; ++j) nb_off[j] = b_off[j];
     }
-    int a_left = nk / 2, b_left = nk;                   // requests left before a cursor moves to the next task
-    const size_t b_step = (size_t)BK * P.ldb * 2;       // bytes between K-tiles of the weights
+    const int b_requests = NK ? nk / 2 : nk;            // per task
+    int a_left = nk / 2, b_left = b_requests;                   // requests left before a cursor moves to the next task
+    const size_t a_step = KM ? (size_t)(2 * BK) * P.lda * 2 : (size_t)128;     // bytes between pairs of K-tiles of the activations
+    const size_t b_step = NK ? (size_t)128 : (size_t)BK * P.ldb * 2;       // bytes between K-tiles of the weights
     const uint32_t lds_base = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
     const uint32_t lds_a_wave = lds_base + wave * (A_COPIES * 1024);
-    const uint32_t lds_b_wave = lds_base + B_REGION + wave * 2048;
+    const uint32_t lds_b_wave = lds_base + B_REGION + wave * (B_COPIES * 1024);
 
     int a_issue_stage = 0, b_issue_stage = 0;
     auto issue_a = [&]() __attribute__((always_inline)) {                              // next pair of K-tiles of the activation rows
@@ -306,22 +332,23 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 #pragma unroll
             for (int j = 0; j < A_COPIES; ++j) a_off[j] = na_off[j];
         } else {
-            a_base += 128;
+            a_base += a_step;
         }
         a_issue_stage ^= 1;
     };
-    auto issue_b = [&]() __attribute__((always_inline)) {                              // next K-tile of the weights
-        const uint32_t d = lds_b_wave + b_issue_stage * B_STAGE;
-        copy_to_lds_stream(b_base, b_off[0], d);
-        copy_to_lds_stream(b_base, b_off[1], d + 1024);
+    auto issue_b = [&]() __attribute__((always_inline)) {                              // next K-tile (NK: pair) of the weights
+        const uint32_t d = lds_b_wave + b_issue_stage * (NK ? B_PAIR_STAGE : B_STAGE);
+#pragma unroll
+        for (int j = 0; j < B_COPIES; ++j) copy_to_lds_stream(b_base, b_off[j], d + j * 1024);
         if (--b_left == 0) {
-            b_left = nk;
+            b_left = b_requests;
             b_base = nb_base;
-            b_off[0] = nb_off[0]; b_off[1] = nb_off[1];
+#pragma unroll
+            for (int j = 0; j < B_COPIES; ++j) b_off[j] = nb_off[j];
         } else {
             b_base += b_step;
         }
-        b_issue_stage = b_issue_stage + 1 == B_STAGES ? 0 : b_issue_stage + 1;
+        b_issue_stage = b_issue_stage + 1 == (NK ? B_PAIR_STAGES : B_STAGES) ? 0 : b_issue_stage + 1;
     };
 
     f32x4 acc[TM][TN];                                  // [row tile of 16][column tile of 16]
@@ -339,21 +366,43 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     const int bk = kq * 8 + (r16 >> 2);                 // k of the first transpose read; the second is k + 4
     const int b_sw = swz_b(bk);
     int a_rd[2], b_rd[TN];                              // [half of the 64-wide activation stage]
+    constexpr int A_ROW_BYTES = BM * 2;                 // KM: a k-row of the stage
 #pragma unroll
-    for (int h = 0; h < 2; ++h) a_rd[h] = a_row * 128 + ((((h << 2) | kq) ^ a_sw) << 4);
+    for (int h = 0; h < 2; ++h) {
+        if constexpr (KM) a_rd[h] = (h * BK + bk) * A_ROW_BYTES + (((wm * TM * 2 + ((r16 & 3) >> 1)) ^ b_sw) << 4) + (r16 & 1) * 8;
+        else a_rd[h] = a_row * 128 + ((((h << 2) | kq) ^ a_sw) << 4);
+    }
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
+        if constexpr (NK) {                             // [half of the 64-wide stage]
+            b_rd[tn] = B_REGION + (wn * TN * 16 + r16) * 128 + (((((tn & 1) << 2) | kq) ^ swz_a(r16)) << 4);
+            continue;
+        }
         const int chunk = (wn * TN + tn) * 2 + ((r16 & 3) >> 1);
         b_rd[tn] = B_REGION + bk * B_ROW_BYTES + ((chunk ^ b_sw) << 4) + (r16 & 1) * 8;
     }
 
     // activations of row tiles 4 g .. 4 g + 3, K-tile in activation stage sa, half h: read i of 4
     auto read_x = [&](int i, int g, int sa, int h, XFrags& f) __attribute__((always_inline)) {
-        f.x[i] = *(const u32x4*)(smem + sa * A_STAGE + a_rd[h] + (g * 4 + i) * 16 * 128);
+        if constexpr (KM) {
+            const unsigned char* const p = smem + sa * A_STAGE + (a_rd[h] ^ ((g * 4 + i) << 5));   // a row tile is two chunks
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const u32x2 t = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + half * 4 * A_ROW_BYTES)));
+                f.x[i][2 * half] = t[0];
+                f.x[i][2 * half + 1] = t[1];
+            }
+        } else {
+            f.x[i] = *(const u32x4*)(smem + sa * A_STAGE + a_rd[h] + (g * 4 + i) * 16 * 128);
+        }
     };
-    // weights of the K-tile in weight stage sb: read i of 8 (column tile i / 2, k 0-3 or 4-7 of the lane's octet)
-    auto read_w = [&](int i, int sb, WFrags& f) __attribute__((always_inline)) {
+    // weights of the K-tile in weight stage sb (NK: in half h of it): read i of 8 (column tile i / 2, k 0-3 or 4-7 of the lane's octet)
+    auto read_w = [&](int i, int sb, int h, WFrags& f) __attribute__((always_inline)) {
         const int tn = i >> 1, half = i & 1;
+        if constexpr (NK) {                             // both halves with the first read
+            if (half == 0) f.w[tn] = *(const u32x4*)(smem + sb * B_PAIR_STAGE + b_rd[h] + tn * 16 * 128);
+            return;
+        }
         const u32x2 t = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                                                       (lds_s16x4*)(smem + sb * B_STAGE + b_rd[tn] + half * 4 * B_ROW_BYTES)));
         f.w[tn][2 * half] = t[0];
@@ -393,6 +442,28 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 #pragma unroll
                     for (int b = 0; b < 4; ++b) acc[tm][tn][b] = 0.0f;
                     if (row < cur.rows && col < N) *(f32x4*)((float*)P.C + c_base + (size_t)row * P.ldc + col) = v;
+                }
+            }
+            return;
+        }
+        if constexpr (NK) {
+            // no bias, identity: lanes 16 apart swap halves of two neighbouring tiles and store 8 columns each
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
+                const int row = cur.row0 + wm * (TM * 16) + tm * 16 + r16;
+#pragma unroll
+                for (int tn = 0; tn < TN; tn += 2) {
+                    u32x4 v;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const auto sw = __builtin_amdgcn_permlane16_swap(pack2<S>(acc[tm][tn][2 * q], acc[tm][tn][2 * q + 1]),
+                                                                         pack2<S>(acc[tm][tn + 1][2 * q], acc[tm][tn + 1][2 * q + 1]), false, false);
+                        v[q] = sw[0]; v[2 + q] = sw[1];
+                    }
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) acc[tm][tn][b] = acc[tm][tn + 1][b] = 0.0f;
+                    const int col = col_w + (tn + (kq & 1)) * 16 + (kq >> 1) * 8;
+                    if (row < cur.rows && col < N) *(u32x4*)((elem*)P.C + c_base + (size_t)row * P.ldc + col) = v;
                 }
             }
             return;
@@ -441,7 +512,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     };
     auto finish_task = [&]() __attribute__((always_inline)) {
         // Both copy cursors have moved on to `nxt` by now (they run at most 4 K-tiles ahead and K >= 6
-        // K-tiles), so the addresses of its successor can replace `nxt`'s.  The loads they need (the gather
+        // K-tiles; NK: 6 ahead and K >= 8), so the addresses of its successor can replace `nxt`'s.  The loads they need (the gather
         // table) are requested first and used after the tile is stored.
         Task after = nxt;
         ++nxt_j;
@@ -480,17 +551,28 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     // requests come after its first four, and the twelve reads of tile u+1's operands between the others,
     // with the activations double-buffered by tile (x0 even, x1 odd) instead of by half.
     // requests of the virtual steps -4 .. -1, in steady-state order: B0 A0 B1 B2 A1 B3
-    issue_b();
-    issue_a();
-    issue_b();
-    issue_b();
-    issue_a();
-    issue_b();
-    wait_copies_and_barrier<4>();                       // A0 and B0 (and more) have landed
+    // NK, where a request of weights is a pair of K-tiles: B0 A0 B1 A1 B2, in steady state A (pair q + 2) B (pair q + 3) in
+    // the odd tile of pair q, after waiting for pair q + 1: of the newer copies, only those of B (pair q + 2) may be in flight
+    if constexpr (NK) {
+        issue_b();
+        issue_a();
+        issue_b();
+        issue_a();
+        issue_b();
+        wait_copies_and_barrier<2 * B_COPIES + A_COPIES>();
+    } else {
+        issue_b();
+        issue_a();
+        issue_b();
+        issue_b();
+        issue_a();
+        issue_b();
+        wait_copies_and_barrier<4>();                   // A0 and B0 (and more) have landed
+    }
     WFrags w0, w1;                                      // weights of the even / odd tile of a pair
     XFrags x0, x1;                                      // activations of row tiles 0-3 / 4-7 (G = 1: of the even / odd tile)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) read_w(i, 0, w0);
+    for (int i = 0; i < 8; ++i) read_w(i, 0, 0, w0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) read_x(i, 0, 0, 0, x0);
     int sb = 0;                                         // weight stage of tile u
@@ -511,53 +593,55 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 #pragma unroll
         for (int i = 4; i < 16; ++i) {
             mma_one(i, 1, wf, x1);
-            if (i < 12) read_w(i - 4, sb_n, wn_f);
+            if (i < 12) read_w(i - 4, sb_n, h_n, wn_f);
             else read_x(i - 12, 0, sa_n, h_n, x0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // One pair of K-tiles (u even, u + 1).  STEADY: u <= U - 6, so every request below exists and the wait
-    // counts above hold; otherwise nothing more is requested and the waits are for everything in flight.
-    // LAST: u + 2 == U, nothing follows.
+    // One pair of K-tiles (u even, u + 1).  kSteady: u <= U - 6 (NK: U - 8), so every request below exists and the wait
+    // counts above hold; kRowsOnly (NK, u == U - 6): the weights have all been requested; otherwise nothing more is
+    // requested and the waits are for everything in flight.  kLast: u + 2 == U, nothing follows.
     // G = 1: the twelve MFMAs of a K-tile after its first four (operands wf, xf), with the twelve reads of
     // the next tile's operands (-> wn_f, xn_f) between them.
     auto single_tail = [&](const WFrags& wf, const XFrags& xf, WFrags& wn_f, XFrags& xn_f, int sb_n, int sa_n, int h_n) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 4; i < 16; ++i) {
             mma_one(i, 0, wf, xf);
-            if (i < 12) read_w(i - 4, sb_n, wn_f);
+            if (i < 12) read_w(i - 4, sb_n, h_n, wn_f);
             else read_x(i - 12, 0, sa_n, h_n, xn_f);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto pair_of_tiles = [&](int u, auto steady_tag, auto last_tag) __attribute__((always_inline)) {
-        constexpr bool STEADY = decltype(steady_tag)::value, LAST = decltype(last_tag)::value;
+    enum { kSteady, kRowsOnly, kDrain, kLast };
+    auto pair_of_tiles = [&](int u, auto mode_tag) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(mode_tag)::value;
+        constexpr bool STEADY = MODE == kSteady, LAST = MODE == kLast;
         constexpr int LAST_G = G - 1;                   // the half of a K-tile whose first four MFMAs cover the wait
         const int sa = (u >> 1) & 1;
         // ---- even tile u ----
         if (G == 2) first_half(w0, sa, 0);
-        const int sb1 = (sb + 1) & (B_STAGES - 1);
+        const int sb1 = NK ? sb : (sb + 1) & (B_STAGES - 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) mma_one(i, LAST_G, w0, G == 2 ? x1 : x0);   // these cover the wait for tile u+1
         __builtin_amdgcn_sched_barrier(0);
-        wait_copies_and_barrier<STEADY ? A_COPIES + 4 : 0>();
-        if (STEADY) issue_b();
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!NK) {                            // (the pair's weights arrive together)
+            wait_copies_and_barrier<STEADY ? A_COPIES + 4 : 0>();
+            if (STEADY) issue_b();
+            __builtin_amdgcn_sched_barrier(0);
+        }
         if (G == 2) second_half_tail(w0, w1, sb1, sa, 1);
         else single_tail(w0, x0, w1, x1, sb1, sa, 1);
         // ---- odd tile u + 1 ----
         if (G == 2) first_half(w1, sa, 1);
-        sb = (sb1 + 1) & (B_STAGES - 1);
+        sb = NK ? (sb == B_PAIR_STAGES - 1 ? 0 : sb + 1) : (sb1 + 1) & (B_STAGES - 1);
         if (!LAST) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) mma_one(i, LAST_G, w1, x1);
             __builtin_amdgcn_sched_barrier(0);
-            wait_copies_and_barrier<STEADY ? 4 : 0>();
-            if (STEADY) {
-                issue_a();
-                issue_b();
-            }
+            wait_copies_and_barrier<MODE <= kRowsOnly ? 4 : 0>();
+            if (MODE <= kRowsOnly) issue_a();
+            if (STEADY) issue_b();
             __builtin_amdgcn_sched_barrier(0);
             if (G == 2) second_half_tail(w1, w0, sb, sa ^ 1, 0);
             else single_tail(w1, x1, w0, x0, sb, sa ^ 1, 0);
@@ -574,9 +658,13 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         }
     };
     int u = 0;
-    for (; u <= U - 6; u += 2) pair_of_tiles(u, std::true_type{}, std::false_type{});
-    pair_of_tiles(u, std::false_type{}, std::false_type{});          // u == U - 4
-    pair_of_tiles(u + 2, std::false_type{}, std::true_type{});       // u == U - 2
+    for (; u <= U - (NK ? 8 : 6); u += 2) pair_of_tiles(u, std::integral_constant<int, kSteady>{});
+    if constexpr (NK) {
+        pair_of_tiles(u, std::integral_constant<int, kRowsOnly>{});  // u == U - 6
+        u += 2;
+    }
+    pair_of_tiles(u, std::integral_constant<int, kDrain>{});         // u == U - 4
+    pair_of_tiles(u + 2, std::integral_constant<int, kLast>{});      // u == U - 2
 }
 
 // One persistent workgroup per CU.  A workgroup first walks its share of the XCD's large-tile tasks, then its
@@ -587,7 +675,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 // NPH == 2 (both FFN GEMMs in one launch): the workgroup then walks its second-GEMM tasks the same way, each
 // waiting for its unit's first-GEMM tiles.  Since no workgroup waits for anything before all its own first-GEMM
 // tiles are stored, the waits always end (see wait_for_unit).
-template <class S, int ACT0, int PH, bool COUNT, bool WAIT>
+template <class S, int ACT0, int PH, bool COUNT, bool WAIT, int LAYOUT = 0>
 __device__ __forceinline__ void stream_gemm(const StreamArgs& a, int xcd, int wg, int wgs) {
     const int nrow_l = ffn_units_nrow_large(a.max_rows), nrow_s = ffn_units_nrow_small(a.max_rows);
     int32_t* const list_l = a.lists;
@@ -596,12 +684,12 @@ __device__ __forceinline__ void stream_gemm(const StreamArgs& a, int xcd, int wg
     int unit0, unit_step, ux_l, ux_s;
     ffn_xcd_share(true, n_l, nrow_l, xcd, unit0, unit_step, ux_l);
     ffn_xcd_share(false, n_s, nrow_s, xcd, unit0, unit_step, ux_s);
-    if (ux_l > 0) stream_body<S, ACT0, PH, COUNT, WAIT, 2>(a, list_l, a.groups * nrow_l, xcd, wg, wgs, 0);
+    if (ux_l > 0) stream_body<S, ACT0, PH, COUNT, WAIT, 2, LAYOUT>(a, list_l, a.groups * nrow_l, xcd, wg, wgs, 0);
     if (ux_s > 0) {
         if (ux_l > 0) __syncthreads();                  // every wavefront is done with the LDS stages of the first part
         const int ncol = (a.ph[PH].N + BN - 1) / BN;
         const int wg_s = ffn_small_list_rotation(wg, wgs, ux_l, ncol);
-        stream_body<S, ACT0, PH, COUNT, WAIT, 1>(a, list_s, a.groups, xcd, wg_s, wgs, ffn_small_list_handicap(wgs, ux_l, ncol));
+        stream_body<S, ACT0, PH, COUNT, WAIT, 1, LAYOUT>(a, list_s, a.groups, xcd, wg_s, wgs, ffn_small_list_handicap(wgs, ux_l, ncol));
     }
 }
 

@@ -33,6 +33,8 @@ struct GemmArgs {
     int act;                                                // moe_act, applied after the bias
     int dtype;                                              // storage of A, B (and of C, bias unless c_f32)
     bool b_is_nk;
+    bool a_is_km;                                           // A is stored [K][rows] (lda between k); the weight-streaming kernel only, and
+                                                            // every rows(g) a multiple of 8
     bool c_f32;                                             // C and bias are fp32 (gate logits)
     bool fp32_mfma;                                         // fp32 storage: multiply on the fp32 instruction (gate logits, as in the fused gate)
 };
@@ -51,7 +53,8 @@ int device_cu_count();
 // launch_grouped_gemm routes eligible shapes to it.
 bool stream_gemm_eligible(const GemmArgs& a);
 // the part of the eligibility that depends on the shape alone
-bool stream_gemm_shape_ok(int dtype, int N, int K, int lda, int ldb, int ldc, long long a_rows_total);
+bool stream_gemm_shape_ok(int dtype, int N, int K, int lda, int ldb, int ldc, long long a_rows_total, bool a_is_km = false,
+                          bool b_is_nk = false);
 hipError_t launch_grouped_gemm_stream(const GemmArgs& a, hipStream_t stream);
 // Scratch block of the streaming kernels, written by launch_ffn_units for the same rows_dev / rows_cap / groups /
 // max_rows: for each of the two row-tile sizes (256 and 128 rows) a fault word, the number of live (group, row
