@@ -113,9 +113,12 @@ __global__ __launch_bounds__(L_THREADS) void moe_layer_kernel(LayerArgs a) {
     // ---- slot assignment, part 2: slots and the routing table; the last workgroup also lists the live FFN units
     {
         int32_t* const run = (int32_t*)smem + wave_in_wg * a.E;        // one array of E ints per wavefront
-        for (int c = gwave; c < n_chunks; c += waves)
-            route_scatter_chunk(a.topk_expert, a.topk_weight, (long long)a.T * a.k, G_BM * a.k, a.T, false, a.E, a.k, a.C, a.counts, a.slot,
+        for (int c = gwave; c < n_chunks; c += waves) {
+            for (int e = threadIdx.x % kWave; e < a.E; e += kWave) run[e] = a.counts[(size_t)c * a.E + e];
+            wave_lds_sync();
+            route_scatter_chunk(a.topk_expert, a.topk_weight, (long long)a.T * a.k, G_BM * a.k, a.T, false, a.E, a.k, a.C, a.slot,
                                 a.slot_token, a.slot_weight, c, run);
+        }
         if (bid == nb - 1) {
             __syncthreads();
             build_ffn_units(a.expert_demand, a.C, a.E, a.C, a.ffn.lists, (int*)smem, L_THREADS);

@@ -15,6 +15,9 @@ __device__ __forceinline__ long long pair_index(long long q, int T, int k, bool 
     return choice_major ? (q % T) * k + q / T : q;
 }
 
+// the same for fewer than 2^31 pairs
+__device__ __forceinline__ int pair_index32(int q, int T, int k, bool choice_major) { return choice_major ? q % T * k + q / T : q; }
+
 // slot_token = -1, slot_weight = 0 for all E C entries: thread gid of `stride` threads
 __device__ __forceinline__ void route_clear_tables(int32_t* __restrict__ slot_token, float* __restrict__ slot_weight, long long EC,
                                                    long long gid, long long stride) {
@@ -51,19 +54,30 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// One wavefront: the slots of chunk c's pairs, 64 pairs at a time.  `run` is an LDS array of E ints that belongs
-// to this wavefront alone: slots handed out so far per expert, starting from the chunk's scanned bases.  A
-// lane's slot is base + (pairs of the same expert in earlier steps) + (lower lanes naming the same expert in this
-// step): lanes naming the same expert are found by intersecting ballots over the bits of the expert id.
+// Lanes that name the same expert, found by intersecting ballots over the bits of the expert id (lanes with
+// valid == false name none): the lane's rank among them and their number.
+__device__ __forceinline__ void route_match(int e, bool valid, int nbits, int& rank, int& group) {
+    unsigned long long same = __ballot(valid);
+    for (int b = 0; b < nbits; ++b) {
+        const bool bit = (e >> b) & 1;
+        const unsigned long long bal = __ballot(valid && bit);
+        same &= bit ? bal : ~bal;
+    }
+    const unsigned long long below = (1ull << (threadIdx.x % kWave)) - 1ull;
+    rank = __popcll(same & below);
+    group = __popcll(same);
+}
+__device__ __forceinline__ int route_expert_bits(int E) { return E > 1 ? 32 - __clz(E - 1) : 0; }
+
+// One wavefront: the slots of chunk c's pairs, 64 pairs at a time.  `run` is an LDS array of E ints that no other
+// wavefront uses meanwhile: slots handed out per expert before this chunk.  A lane's slot is run[e] + (lower lanes
+// naming the same expert in this step).
 __device__ __forceinline__ void route_scatter_chunk(const int32_t* __restrict__ topk_expert, const float* __restrict__ topk_weight,
                                                     long long P, int chunk_pairs, int T, bool choice_major, int E, int k, int C,
-                                                    const int32_t* __restrict__ base, int32_t* __restrict__ slot,
-                                                    int32_t* __restrict__ slot_token, float* __restrict__ slot_weight, int c,
-                                                    int32_t* run) {
+                                                    int32_t* __restrict__ slot, int32_t* __restrict__ slot_token,
+                                                    float* __restrict__ slot_weight, int c, int32_t* run) {
     const int lane = threadIdx.x % kWave;
-    for (int e = lane; e < E; e += kWave) run[e] = base[(size_t)c * E + e];
-    wave_lds_sync();
-    const int nbits = E > 1 ? 32 - __clz(E - 1) : 0;
+    const int nbits = route_expert_bits(E);
     const long long p_end = ((long long)c + 1) * chunk_pairs < P ? ((long long)c + 1) * chunk_pairs : P;
     for (long long p0 = (long long)c * chunk_pairs; p0 < p_end; p0 += kWave) {
         const long long p = p0 + lane;
@@ -71,15 +85,8 @@ __device__ __forceinline__ void route_scatter_chunk(const int32_t* __restrict__ 
         int e = p < p_end ? topk_expert[m] : -1;
         const bool valid = (e >= 0 && e < E);
         if (!valid) e = 0;
-        unsigned long long same = __ballot(valid);
-        for (int b = 0; b < nbits; ++b) {
-            const bool bit = (e >> b) & 1;
-            const unsigned long long bal = __ballot(valid && bit);
-            same &= bit ? bal : ~bal;
-        }
-        const unsigned long long below = (1ull << lane) - 1ull;
-        const int rank = __popcll(same & below);
-        const int group = __popcll(same);
+        int rank, group;
+        route_match(e, valid, nbits, rank, group);
         const int s = valid ? run[e] + rank : 0;
         wave_lds_sync();
         if (valid && rank == group - 1) run[e] = s + 1;
