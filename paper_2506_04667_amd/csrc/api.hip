@@ -333,7 +333,38 @@ struct BwdPlan {
     size_t off_wg_part;
     size_t off_counts, off_units, off_slot_token, off_slot_weight, off_slot, off_demand, off_dl, off_dL, off_wgt, off_xe,
         off_ge, off_a, off_h, off_dh, off_da, off_dxe, off_row_p, off_hT, off_xeT, off_xT, off_wrows, off_wunits1, off_wunits2, total;
+    bool w_stream;                                       // 16-bit storage: dW1 and dW2 on the weight-streaming kernel
+    int row_step;                                        // the experts' rows are zero from the last live one to the next multiple of this
+    int w_slices;                                        // 16-bit storage: slices of the weight gradients' sums over an expert's slots
 };
+constexpr long long kWgradWorkgroups = 512;              // two per CU
+
+// An expert's dW1 or dW2 as a GEMM of the weight-streaming kernel (its rows: `M` columns of h or xe, all C_pad slots as K)
+moe::GemmArgs stream_wgrad_args(const moe_config* c, const Plan& p, const void* rows, int M, const void* grad, int N, float* out,
+                                const int32_t* counts_dev, int32_t* units) {
+    moe::GemmArgs w{};
+    w.groups = c->E; w.dtype = c->dtype; w.act = MOE_ACT_IDENTITY; w.c_f32 = true; w.K = p.C_pad;
+    w.A = rows; w.a_is_km = true; w.lda = M; w.a_group_stride = (long long)p.C_pad * M; w.a_rows_total = p.C_pad;
+    w.rows_dev = counts_dev; w.units = units; w.rows_fixed = M; w.rows_cap = M; w.max_rows = M;
+    w.B = grad; w.b_group_stride = (long long)p.C_pad * N; w.ldb = N;
+    w.C = out; w.c_group_stride = (long long)c->H * c->I; w.ldc = N; w.N = N;
+    return w;
+}
+
+// dW1 and dW2 in 16-bit storage on the weight-streaming kernel, or all weight gradients in one launch of wgrad.hip, whose sums stop
+// at an expert's last live slot and which cuts tiles finer?  Both products, us, streaming / wgrad, H = I = 2048 (full slots): E = 128
+// of 256 slots 1200 / 1351; E = 64 of 512 799 / 876; E = 16 of 2048 569 / 588; E = 8 of 4096 (two rounds of 256 x 256 tiles) 520 /
+// 551.  E = 8 of 556, I = 768 (192 tiles): 69 / 49.  Slots a third empty, as at a capacity factor of 1.25: E = 128 of 384 1360 / 1290; E
+// = 16, H = 1024, I = 4096 209 / 136.
+bool wgrad_streams(const moe_config* c, const Plan& p) {
+    if (c->dtype == MOE_F32) return false;
+    int32_t some = 0;                                    // eligibility asks whether the lists are there, not what they hold
+    if (!moe::stream_gemm_eligible(stream_wgrad_args(c, p, nullptr, c->I, nullptr, c->H, nullptr, &some, &some)) ||
+        !moe::stream_gemm_eligible(stream_wgrad_args(c, p, nullptr, c->H, nullptr, c->I, nullptr, &some, &some)))
+        return false;
+    const long long tiles = (long long)c->E * ((c->H + 255) / 256) * ((c->I + 255) / 256);
+    return tiles >= 512 && (long long)c->E * p.C_pad * 10 <= (long long)c->T * c->k * 12;
+}
 
 moe_status make_bwd_plan(const moe_config* c, BwdPlan* b) {
     moe_status st = make_plan(c, &b->p);
@@ -376,11 +407,23 @@ moe_status make_bwd_plan(const moe_config* c, BwdPlan* b) {
     }
     b->off_xeT = b->off_dxe + x_bytes;
     b->off_hT = b->off_xeT + x_bytes;
-    b->off_xT = take(H * (size_t)b->T_pad * el);
-    // the weight-gradient GEMMs as streaming-kernel launches: their "experts" have H (dW1) or I (dW2) rows each
-    b->off_wrows = take(2 * E * 4);
-    b->off_wunits1 = take(moe::ffn_units_ints(c->E, c->H) * 4);
-    b->off_wunits2 = take(moe::ffn_units_ints(c->E, c->I) * 4);
+    b->w_slices = 1;
+    b->w_stream = wgrad_streams(c, p);
+    b->row_step = b->w_stream ? p.C_pad : 32;
+    if (c->dtype == MOE_F32) {
+        b->off_xT = take(H * (size_t)b->T_pad * el);
+    } else {
+        // dW1 and dW2 have few output tiles where there are few experts or narrow layers: then an expert's slots are cut into
+        // slices of at least 256, as many as give two workgroups per CU and as the partial sums have room for behind dxe
+        const long long tiles = moe::wgrad_tiles(c->E, c->I, c->H) + moe::wgrad_tiles(c->E, c->H, c->I);
+        const long long room = (long long)((off - b->off_xeT) / (2 * E * H * I * 4));
+        if (!b->w_stream) b->w_slices = (int)std::max(1ll, std::min({kWgradWorkgroups / tiles, (long long)p.C_pad / 256, room}));
+        if (b->w_stream) {
+            b->off_wrows = take(2 * E * 4);
+            b->off_wunits1 = take(moe::ffn_units_ints(c->E, c->H) * 4);
+            b->off_wunits2 = take(moe::ffn_units_ints(c->E, c->I) * 4);
+        }
+    }
     b->total = off;
     return MOE_OK;
 }
@@ -401,13 +444,12 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     void *dL = ws_at(ws, b.off_dL), *wgt = ws_at(ws, b.off_wgt), *xe = ws_at(ws, b.off_xe), *ge = ws_at(ws, b.off_ge);
     void *a = ws_at(ws, b.off_a), *h = ws_at(ws, b.off_h), *da = ws_at(ws, b.off_da), *dxe = ws_at(ws, b.off_dxe);
     float *dh = (float*)ws_at(ws, b.off_dh), *row_p = (float*)ws_at(ws, b.off_row_p);
-    void *hT = ws_at(ws, b.off_hT), *xeT = ws_at(ws, b.off_xeT), *xT = ws_at(ws, b.off_xT);
 #define MOE_TRY(call) do { if ((call) != hipSuccess) return MOE_ERR_HIP; } while (0)
     // the routing tables again, from the selection the forward pass made (slots are a function of it)
     MOE_TRY(moe::launch_route(topk_expert, topk_weight, T, E, k, C, c->drop_policy == MOE_DROP_CHOICE_MAJOR, counts, false, slot,
                               demand, slot_token, slot_weight, units, false, s));
     MOE_TRY(moe::launch_transpose_pad(Wg, wgt, H, E, p.E_pad, dt, s));
-    MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, slot_weight, H, E, C, C_pad, dt, xe, ge, s));
+    MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, slot_weight, demand, H, E, C, C_pad, b.row_step, dt, xe, ge, s));
     // grouped GEMMs over the experts' live rows
     moe::GemmArgs g{};
     g.rows_dev = demand; g.rows_fixed = 0; g.rows_cap = C; g.groups = E; g.max_rows = C;
@@ -423,61 +465,67 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     d1.A = ge; d1.a_group_stride = rH; d1.lda = H; d1.B = W2; d1.b_group_stride = HI; d1.ldb = H; d1.b_is_nk = true;
     d1.units = units; d1.C = dh; d1.c_group_stride = rI; d1.ldc = I; d1.N = I; d1.K = H; d1.c_f32 = true;
     MOE_TRY(moe::launch_grouped_gemm(d1, s));
-    MOE_TRY(moe::launch_bwd_act(a, dh, ge, b2, demand, slot_weight, E, C, C_pad, H, I, c->act, dt, h, da, row_p, s));
+    MOE_TRY(moe::launch_bwd_act(a, dh, ge, b2, demand, slot_weight, E, C, C_pad, b.row_step, H, I, c->act, dt, h, da, row_p, s));
     // gate: w dL/dw of every kept pair is in row_p; the softmax Jacobian
     MOE_TRY(moe::launch_bwd_gate(row_p, topk_expert, topk_weight, slot, T, b.T_pad, k, E, C, C_pad, b.ldL, dt, dl, dL, s));
     moe::GemmArgs d2 = g;
     d2.A = da; d2.a_group_stride = rI; d2.lda = I; d2.B = W1; d2.b_group_stride = HI; d2.ldb = I; d2.b_is_nk = true;
     d2.units = units; d2.C = dxe; d2.c_group_stride = rH; d2.ldc = H; d2.N = H; d2.K = I;
     MOE_TRY(moe::launch_grouped_gemm(d2, s));
-    // weight gradients over all C_pad rows (rows beyond the live ones are zero): dW2[e] = h[e]^T ge[e], dW1[e] = xe[e]^T da[e].
-    // 16-bit storage: row counts and lists of row tiles, so that the persistent weight-streaming kernel takes them (each
-    // GEMM writes E H I floats from a contraction over only C_pad rows: its stores must overlap the next tile's loads), with
-    // h and xe read as they are stored, [slot][column]; where it does not take the shape they are transposed first.
-    int32_t* wrows = (int32_t*)ws_at(ws, b.off_wrows);
-    int32_t *wunits1 = nullptr, *wunits2 = nullptr;
+    // weight gradients: dW2[e] = h[e]^T ge[e], dW1[e] = xe[e]^T da[e] over the expert's slots, dWg = x^T dL over the tokens
+    float* const wg_out = b.wg_slices > 1 ? (float*)ws_at(ws, b.off_wg_part) : dWg;
     if (dt != MOE_F32) {
-        wunits1 = (int32_t*)ws_at(ws, b.off_wunits1);
-        wunits2 = (int32_t*)ws_at(ws, b.off_wunits2);
-        MOE_TRY(moe::launch_bwd_fill_rows(wrows, E, H, I, s));
-        MOE_TRY(moe::launch_ffn_units(wrows, H, E, H, wunits1, s));
-        MOE_TRY(moe::launch_ffn_units(wrows + E, I, E, I, wunits2, s));
-    }
-    auto weight_grad = [&](const void* rows, int M, const int32_t* counts_dev, int32_t* list, void* rowsT, const void* grad, int N, float* out) {
-        moe::GemmArgs w{};
-        w.groups = E; w.dtype = dt; w.act = MOE_ACT_IDENTITY; w.c_f32 = true; w.K = C_pad;
-        w.A = rows; w.a_is_km = true; w.lda = M; w.a_group_stride = (long long)C_pad * M; w.a_rows_total = C_pad;
-        w.rows_dev = counts_dev; w.units = list; w.rows_fixed = M; w.rows_cap = M; w.max_rows = M;
-        w.B = grad; w.b_group_stride = (long long)C_pad * N; w.ldb = N;
-        w.C = out; w.c_group_stride = HI; w.ldc = N; w.N = N; w.k_span = c->act == MOE_ACT_RELU ? kReluGradSpan : 0;
-        if (!moe::stream_gemm_eligible(w)) {
-            if (hipError_t e = moe::launch_bwd_transpose(rows, rowsT, E, C_pad, M, C_pad, dt, s); e != hipSuccess) return e;
-            w.A = rowsT; w.a_is_km = false; w.lda = C_pad; w.a_rows_total = M;
-            if (!list) w.rows_dev = nullptr;
+        float *dW1_out = dW1, *dW2_out = dW2;
+        if (b.w_slices > 1) {
+            dW1_out = (float*)ws_at(ws, b.off_xeT);
+            dW2_out = dW1_out + (size_t)b.w_slices * E * HI;
         }
-        return moe::launch_grouped_gemm(w, s);
-    };
-    MOE_TRY(weight_grad(h, I, wrows + E, wunits2, hT, ge, H, dW2));
-    MOE_TRY(weight_grad(xe, H, wrows, wunits1, xeT, da, I, dW1));
+        if (b.w_stream) {
+            int32_t* wrows = (int32_t*)ws_at(ws, b.off_wrows);
+            int32_t *wunits1 = (int32_t*)ws_at(ws, b.off_wunits1), *wunits2 = (int32_t*)ws_at(ws, b.off_wunits2);
+            MOE_TRY(moe::launch_bwd_fill_rows(wrows, E, H, I, s));
+            MOE_TRY(moe::launch_ffn_units(wrows, H, E, H, wunits1, s));
+            MOE_TRY(moe::launch_ffn_units(wrows + E, I, E, I, wunits2, s));
+            MOE_TRY(moe::launch_grouped_gemm(stream_wgrad_args(c, p, h, I, ge, H, dW2, wrows + E, wunits2), s));
+            MOE_TRY(moe::launch_grouped_gemm(stream_wgrad_args(c, p, xe, H, da, I, dW1, wrows, wunits1), s));
+        }
+        const int experts = b.w_stream ? 0 : E;
+        const moe::WgradProblem w[moe::kWgradProblems] = {
+            {h, rI, I, C_pad, ge, rH, H, dW2_out, HI, H, demand, C, I, H, experts, b.w_slices},
+            {xe, rH, H, C_pad, da, rI, I, dW1_out, HI, I, demand, C, H, I, experts, b.w_slices},
+            {x, 0, H, T, dL, 0, b.ldL, wg_out, (long long)H * E, E, nullptr, T, H, E, 1, b.wg_slices}};
+        MOE_TRY(moe::launch_wgrad(w, dt, s));
+        if (b.w_slices > 1) {
+            MOE_TRY(moe::launch_bwd_sum_slices(dW1_out, b.w_slices, E * HI, dW1, s));
+            MOE_TRY(moe::launch_bwd_sum_slices(dW2_out, b.w_slices, E * HI, dW2, s));
+        }
+    } else {
+        auto weight_grad = [&](const void* rows, int M, void* rowsT, const void* grad, int N, float* out) {
+            if (hipError_t e = moe::launch_bwd_transpose(rows, rowsT, E, C_pad, M, C_pad, dt, s); e != hipSuccess) return e;
+            moe::GemmArgs w{};
+            w.groups = E; w.dtype = dt; w.act = MOE_ACT_IDENTITY; w.c_f32 = true; w.K = C_pad; w.k_dev = demand; w.k_cap = C;
+            w.A = rowsT; w.lda = C_pad; w.a_group_stride = (long long)C_pad * M; w.a_rows_total = M;
+            w.rows_fixed = M; w.rows_cap = M; w.max_rows = M;
+            w.B = grad; w.b_group_stride = (long long)C_pad * N; w.ldb = N;
+            w.C = out; w.c_group_stride = HI; w.ldc = N; w.N = N; w.k_span = c->act == MOE_ACT_RELU ? kReluGradSpan : 0;
+            return moe::launch_grouped_gemm(w, s);
+        };
+        void *hT = ws_at(ws, b.off_hT), *xeT = ws_at(ws, b.off_xeT), *xT = ws_at(ws, b.off_xT);
+        MOE_TRY(weight_grad(h, I, hT, ge, H, dW2));
+        MOE_TRY(weight_grad(xe, H, xeT, da, I, dW1));
+        MOE_TRY(moe::launch_bwd_transpose(x, xT, 1, T, H, b.T_pad, dt, s));
+        moe::GemmArgs wg{};
+        wg.groups = b.wg_slices; wg.dtype = dt; wg.act = MOE_ACT_IDENTITY; wg.c_f32 = true;
+        wg.A = xT; wg.lda = b.T_pad; wg.a_rows_total = H; wg.rows_fixed = H; wg.rows_cap = H; wg.max_rows = H;
+        wg.a_group_stride = b.wg_slice_k;                // slice g of every row of x^T
+        wg.B = dL; wg.ldb = b.ldL; wg.b_group_stride = (long long)b.wg_slice_k * b.ldL;
+        wg.C = wg_out; wg.ldc = E; wg.c_group_stride = (long long)H * E; wg.N = E; wg.K = b.wg_slice_k;   // rows of both beyond T are zero
+        MOE_TRY(moe::launch_grouped_gemm(wg, s));
+    }
+    if (b.wg_slices > 1) MOE_TRY(moe::launch_bwd_sum_slices(wg_out, b.wg_slices, (long long)H * E, dWg, s));
     MOE_TRY(moe::launch_bwd_colsum(ge, slot_weight, demand, E, C, C_pad, H, dt, db2, s));
     MOE_TRY(moe::launch_bwd_colsum(da, nullptr, demand, E, C, C_pad, I, dt, db1, s));
-    // gate weights: dWg = x^T dL, dgate_bias = column sums of dl
-    MOE_TRY(moe::launch_bwd_transpose(x, xT, 1, T, H, b.T_pad, dt, s));
-    moe::GemmArgs wg{};
-    wg.rows_dev = nullptr; wg.groups = 1; wg.dtype = dt; wg.act = MOE_ACT_IDENTITY; wg.c_f32 = true;
-    wg.A = xT; wg.lda = b.T_pad; wg.a_rows_total = H; wg.rows_fixed = H; wg.rows_cap = H; wg.max_rows = H;
-    wg.B = dL; wg.ldb = b.ldL; wg.C = dWg; wg.ldc = E; wg.N = E; wg.K = b.wg_slice_k;   // rows of both beyond T are zero
-    if (b.wg_slices > 1) {
-        float* part = (float*)ws_at(ws, b.off_wg_part);
-        wg.groups = b.wg_slices;
-        wg.a_group_stride = b.wg_slice_k;                // slice g of every row of x^T
-        wg.b_group_stride = (long long)b.wg_slice_k * b.ldL;
-        wg.C = part; wg.c_group_stride = (long long)H * E;
-        MOE_TRY(moe::launch_grouped_gemm(wg, s));
-        MOE_TRY(moe::launch_bwd_sum_slices(part, b.wg_slices, (long long)H * E, dWg, s));
-    } else {
-        MOE_TRY(moe::launch_grouped_gemm(wg, s));
-    }
+    // dgate_bias = column sums of dl
     MOE_TRY(moe::launch_bwd_gate_bias(topk_expert, dl, T, k, E, dgate_bias, s));
     // dx: the kept choices' rows of dxe plus the gate path
     MOE_TRY(moe::launch_bwd_dx(dxe, wgt, topk_expert, slot, dl, T, H, k, E, C, C_pad, dt, dx, s));
@@ -511,6 +559,7 @@ moe_status moe_init(void) {
     if (e == hipSuccess) e = moe::prepare_grouped_gemm_stream();
     if (e == hipSuccess) e = moe::prepare_layer_fused();
     if (e == hipSuccess) e = moe::prepare_gemm_f32();
+    if (e == hipSuccess) e = moe::prepare_wgrad();
     void* scratch_here = nullptr;
     if (e == hipSuccess) e = static_scratch(&scratch_here);
     if (e != hipSuccess) return MOE_ERR_HIP;

@@ -59,9 +59,12 @@ __device__ __forceinline__ u32x4 floats_to_chunk(const float (&f)[S::kVec]) {
     return v;
 }
 
+// Rows of an expert's buffers with `live` live ones that are written: those, and zeros up to the end of the K-tile in which the
+// weight gradients' sums over the rows end (their products read no further; row_step is its depth).
+__device__ __forceinline__ int written_rows(int live, int row_step) { return (max(live, 1) + row_step - 1) / row_step * row_step; }
+
 // One workgroup per slot row (e, s), s < C_pad: xe[e, s, :] = x[token, :] and ge[e, s, :] = dout[token, :]
-// for a live slot, zeros for an empty one (so that the rows beyond an expert's live rows contribute nothing to
-// the weight-gradient products, which run over all C_pad rows).  16 bytes per lane.
+// for a live slot, zeros for an empty one that the weight gradients read.  16 bytes per lane.
 // ge and the slot's combine weight change their sign together for about half of the tokens.  Everything made of them is a
 // product of the two and comes out as without, except the rounding of dh = ge W2^T: the matrix instructions line up their terms
 // by cutting them off towards minus infinity, every dh is low by a little, and db1, a sum over an expert's rows, would add that
@@ -74,10 +77,12 @@ __device__ __forceinline__ bool negated(int token) { return ((uint32_t)token * 0
 
 template <class S>
 __global__ __launch_bounds__(256) void bwd_gather_kernel(const void* __restrict__ x, const void* __restrict__ dout,
-                                                         const int32_t* __restrict__ slot_token, float* __restrict__ slot_weight, int H,
-                                                         int C, int C_pad, void* __restrict__ xe, void* __restrict__ ge) {
+                                                         const int32_t* __restrict__ slot_token, float* __restrict__ slot_weight,
+                                                         const int32_t* __restrict__ expert_demand, int H, int C, int C_pad, int row_step,
+                                                         void* __restrict__ xe, void* __restrict__ ge) {
     const size_t row = blockIdx.x;
     const int e = (int)(row / C_pad), s = (int)(row % C_pad);
+    if (s >= written_rows(min(expert_demand[e], C), row_step)) return;
     const int tok = s < C ? slot_token[(size_t)e * C + s] : -1;
     const int row_chunks = H / S::kVec;
     const bool neg = tok >= 0 && negated(tok);
@@ -150,18 +155,20 @@ __device__ __forceinline__ float wave_sum(float v) {
 // y = phi(a) W2 + b2 nor another pass over dout (a sixth of the backward pass's matrix work: at T = 16384, H = I = 2048,
 // E = 128, bf16 that product, the dot products with its rows and a separate pass for h were 0.36 of 3.2 ms; at T = 2048,
 // H = 1024, I = 4096, E = 16, fp32 0.43 of 2.02 ms).  The weight goes to h and da in fp32, so dout itself is the other operand
-// of dW2 and is not rounded again.  Rows at or beyond the expert's live rows give h = da = 0 (p is not written).  The row's sum is
+// of dW2 and is not rounded again.  Empty rows that the weight gradients read give h = da = 0 (p is not written).  The row's sum is
 // added in a fixed order.
 template <class S>
 __global__ __launch_bounds__(256) void bwd_act_kernel(const void* a, const float* dh, const void* __restrict__ ge,
                                                       const void* __restrict__ b2, const int32_t* __restrict__ expert_demand,
-                                                      const float* __restrict__ slot_weight, int C, int C_pad, int H, int I, int act,
+                                                      const float* __restrict__ slot_weight, int C, int C_pad, int row_step, int H, int I, int act,
                                                       void* h, void* da, float* __restrict__ p) {
     constexpr int VEC = S::kVec;
     __shared__ float part[4];
     const size_t row = blockIdx.x;
     const int e = (int)(row / C_pad), s = (int)(row % C_pad);
-    const bool live = s < min(expert_demand[e], C);
+    const int n = min(expert_demand[e], C);
+    if (s >= written_rows(n, row_step)) return;
+    const bool live = s < n;
     const float w = live ? slot_weight[(size_t)e * C + s] : 0.0f;
     const int row_chunks = I / VEC;
     float sum = 0.0f;
@@ -414,20 +421,20 @@ hipError_t launch_bwd_fill_rows(int32_t* rows, int E, int first, int second, hip
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, float* slot_weight, int H, int E, int C, int C_pad,
-                             int dtype, void* xe, void* ge, hipStream_t s) {
+hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, float* slot_weight, const int32_t* expert_demand,
+                             int H, int E, int C, int C_pad, int row_step, int dtype, void* xe, void* ge, hipStream_t s) {
     const dim3 g((unsigned)((size_t)E * C_pad)), b(256);
-    if (dtype == 0) hipLaunchKernelGGL(bwd_gather_kernel<F32>, g, b, 0, s, x, dout, slot_token, slot_weight, H, C, C_pad, xe, ge);
-    else if (dtype == 1) hipLaunchKernelGGL(bwd_gather_kernel<BF16>, g, b, 0, s, x, dout, slot_token, slot_weight, H, C, C_pad, xe, ge);
-    else hipLaunchKernelGGL(bwd_gather_kernel<F16>, g, b, 0, s, x, dout, slot_token, slot_weight, H, C, C_pad, xe, ge);
+    if (dtype == 0) hipLaunchKernelGGL(bwd_gather_kernel<F32>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge);
+    else if (dtype == 1) hipLaunchKernelGGL(bwd_gather_kernel<BF16>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge);
+    else hipLaunchKernelGGL(bwd_gather_kernel<F16>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_act(const void* a, const float* dh, const void* ge, const void* b2, const int32_t* expert_demand,
-                          const float* slot_weight, int E, int C, int C_pad, int H, int I, int act, int dtype, void* h, void* da, float* p,
+                          const float* slot_weight, int E, int C, int C_pad, int row_step, int H, int I, int act, int dtype, void* h, void* da, float* p,
                           hipStream_t s) {
     const dim3 g((unsigned)((size_t)E * C_pad)), b(256);
-#define MOE_BWD_ACT(S_) hipLaunchKernelGGL(bwd_act_kernel<S_>, g, b, 0, s, a, dh, ge, b2, expert_demand, slot_weight, C, C_pad, H, I, act, h, da, p)
+#define MOE_BWD_ACT(S_) hipLaunchKernelGGL(bwd_act_kernel<S_>, g, b, 0, s, a, dh, ge, b2, expert_demand, slot_weight, C, C_pad, row_step, H, I, act, h, da, p)
     if (dtype == 0) MOE_BWD_ACT(F32);
     else if (dtype == 1) MOE_BWD_ACT(BF16);
     else MOE_BWD_ACT(F16);

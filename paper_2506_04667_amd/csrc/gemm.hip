@@ -71,7 +71,8 @@ __global__ __launch_bounds__(WM * WN * 64) void grouped_gemm_kernel(GemmArgs a) 
     const int rows = a.rows_dev ? min(a.rows_dev[grp], a.rows_cap) : a.rows_fixed;
     if (row0 >= rows) return;
 
-    gemm_tile<S, NT, WM, WN, TM, TN>(a, smem, grp, row0, n0, rows, 0, (a.K + C::BK - 1) / C::BK, nullptr);
+    const int K = a.k_dev ? max(min(a.k_dev[grp], a.k_cap), 1) : a.K;
+    gemm_tile<S, NT, WM, WN, TM, TN>(a, smem, grp, row0, n0, rows, 0, (K + C::BK - 1) / C::BK, nullptr);
 }
 
 // the kernel's LDS limit on the current device (once per device)

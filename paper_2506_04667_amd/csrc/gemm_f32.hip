@@ -170,7 +170,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void f32_gemm_kernel(GemmArgs a) {
     const int row0 = id / ncol * C::BM, n0 = id % ncol * C::BN;
     const int rows = a.rows_dev ? min(a.rows_dev[grp], a.rows_cap) : a.rows_fixed;
     if (row0 >= rows) return;
-    const int nk = (a.K + C::BK - 1) / C::BK;
+    const int nk = ((a.k_dev ? max(min(a.k_dev[grp], a.k_cap), 1) : a.K) + C::BK - 1) / C::BK;
     if constexpr (SPANS) {
         const int span = a.k_span / C::BK;
         f32_tile<NT, WM, WN, TM, TN>(a, smem, grp, row0, n0, rows, 0, min(span, nk), nullptr);
@@ -189,7 +189,8 @@ __global__ __launch_bounds__(F32Low::THREADS, 2) void f32_gemm_low_kernel(GemmAr
     const int grp = blockIdx.x / ncol, n0 = blockIdx.x % ncol * F32Low::BN;
     const int rows = a.rows_dev ? min(a.rows_dev[grp], a.rows_cap) : a.rows_fixed;
     if (rows <= 0) return;
-    f32_tile_low<NT>(a, smem, grp, 0, n0, rows, 0, (a.K + F32Low::BK - 1) / F32Low::BK, nullptr);
+    const int K = a.k_dev ? max(min(a.k_dev[grp], a.k_cap), 1) : a.K;
+    f32_tile_low<NT>(a, smem, grp, 0, n0, rows, 0, (K + F32Low::BK - 1) / F32Low::BK, nullptr);
 }
 
 template <bool NT>

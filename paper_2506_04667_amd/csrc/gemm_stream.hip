@@ -69,7 +69,6 @@ hipError_t launch_stream_act(const GemmArgs& g1, const GemmArgs* g2, bool never_
         if (g1.b_is_nk)
             return g1.c_f32 ? launch_stream_t<S, kActF32Out, 1, kLayoutNK>(g1, nullptr, never_met, stream)
                             : launch_stream_t<S, 3, 1, kLayoutNK>(g1, nullptr, never_met, stream);
-        if (g1.c_f32) return launch_stream_t<S, kActF32Out, 1>(g1, nullptr, never_met, stream);
     }
     switch (g1.act) {
         case 0: return launch_stream_t<S, 0, NPH>(g1, g2, never_met, stream);
@@ -86,7 +85,6 @@ hipError_t prepare_stream_s() {
     if (e == hipSuccess) e = prepare_stream_t<S, 1, 1>();
     if (e == hipSuccess) e = prepare_stream_t<S, 2, 1>();
     if (e == hipSuccess) e = prepare_stream_t<S, 3, 1>();
-    if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1>();
     if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1, kLayoutKM>();
     if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1, kLayoutNK>();
     if (e == hipSuccess) e = prepare_stream_t<S, 3, 1, kLayoutNK>();
@@ -140,6 +138,7 @@ bool stream_gemm_eligible(const GemmArgs& a) {
     // the epilogues that the backward pass's forms need: fp32 output (weight gradients, <phi(a), dh>) and [n][k] weights take the
     // identity, [k][m] activations fp32 output from packed rows whose count is a multiple of 8
     if ((a.c_f32 || a.b_is_nk) && a.act != 3) return false;
+    if (a.c_f32 && !a.a_is_km && !a.b_is_nk) return false;
     if (a.b_is_nk && a.bias) return false;
     if (a.a_is_km && (!a.c_f32 || a.b_is_nk || a.a_row_index || a.rows_cap % 8 != 0)) return false;
     return a.rows_dev != nullptr && a.units != nullptr &&

@@ -38,6 +38,8 @@ struct GemmArgs {
     bool c_f32;                                             // C and bias are fp32 (gate logits)
     int k_span;                                             // fp32 storage, [k][n] B, no bias, identity: sums of more than this many
                                                             // products (> 0, a multiple of 32) are made span by span and added up in C
+    const int32_t* k_dev; int k_cap;                        // fp32 storage, optional: group g sums over its first min(k_dev[g], k_cap) products, at
+                                                            // least one K-tile (both operands are zero up to the end of the last one)
     bool fp32_mfma;                                         // fp32 storage: multiply on the fp32 instruction (gate logits, as in the fused gate)
 };
 hipError_t launch_grouped_gemm(const GemmArgs& a, hipStream_t stream);
@@ -143,17 +145,34 @@ hipError_t reset_layer_sync(hipStream_t stream);
 // Workgroup 0's stage times (ms) of the last single-launch layer on the current device; synchronises the stream.
 hipError_t layer_stage_ms(double* ms, int n, hipStream_t stream);
 
+// Weight gradients in 16-bit storage (wgrad.hip), all of them in one launch: C[part][m][n] = sum over k of A[g][k][m] B[g][k][n]
+// in fp32, part = slice * groups + g; the k of group g, 0 .. min(rows_dev[g], rows_cap) - 1 (rows_dev == nullptr: rows_cap), are
+// cut into `slices` about equal runs of K-tiles of 32.  B is zero from its last k to the next multiple of 32, and A finite or
+// zero there, its rows at or beyond a_rows taken as row a_rows - 1.  lda >= M and ldb >= N are multiples of 8.
+constexpr int kWgradProblems = 3;
+struct WgradProblem {
+    const void* A; long long a_group_stride; int lda; int a_rows;
+    const void* B; long long b_group_stride; int ldb;
+    float* C; long long c_group_stride; int ldc;
+    const int32_t* rows_dev; int rows_cap;
+    int M, N, groups, slices;
+};
+long long wgrad_tiles(int groups, int M, int N);         // workgroups of one slice
+hipError_t launch_wgrad(const WgradProblem (&p)[kWgradProblems], int dtype, hipStream_t stream);
+hipError_t prepare_wgrad();
+
 // ---- backward pass helpers (backward.hip); buffers per expert have C_pad rows ----------------------------
 // rows[0 .. E) = first, rows[E .. 2 E) = second
 hipError_t launch_bwd_fill_rows(int32_t* rows, int E, int first, int second, hipStream_t s);
-// xe[e, s, :] = x[token] and ge[e, s, :] = dout[token] for live slots, zeros for empty ones (s < C_pad); ge and
-// slot_weight[e, s] change their sign together for about half of the tokens
-hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, float* slot_weight, int H, int E, int C, int C_pad,
-                             int dtype, void* xe, void* ge, hipStream_t s);
+// xe[e, s, :] = x[token] and ge[e, s, :] = dout[token] for live slots, zeros for the empty ones up to the next multiple of
+// row_step (an expert without rows: for the first row_step); ge and slot_weight[e, s] change their sign together for about
+// half of the tokens
+hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, float* slot_weight, const int32_t* expert_demand,
+                             int H, int E, int C, int C_pad, int row_step, int dtype, void* xe, void* ge, hipStream_t s);
 // over [E, C_pad, I], w = slot_weight[e, s]: h = w phi(a), da = w dh phi'(a), p[e, s] = w (<phi(a), dh> + <ge, b2>) (b2
-// optional; h may be a; da may be dh in fp32 storage); rows beyond an expert's live rows give h = da = 0
+// optional; h may be a; da may be dh in fp32 storage); h = da = 0 in the rows where bwd_gather writes zeros
 hipError_t launch_bwd_act(const void* a, const float* dh, const void* ge, const void* b2, const int32_t* expert_demand,
-                          const float* slot_weight, int E, int C, int C_pad, int H, int I, int act, int dtype, void* h, void* da, float* p,
+                          const float* slot_weight, int E, int C, int C_pad, int row_step, int H, int I, int act, int dtype, void* h, void* da, float* p,
                           hipStream_t s);
 // dl[T, k] (fp32) and dL[T_pad, ld] (storage type, dense; rows at and beyond T zero): gradient with respect to the
 // selected gate logits (k <= 64) from p
