@@ -448,8 +448,7 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     // the routing tables again, from the selection the forward pass made (slots are a function of it)
     MOE_TRY(moe::launch_route(topk_expert, topk_weight, T, E, k, C, c->drop_policy == MOE_DROP_CHOICE_MAJOR, counts, false, slot,
                               demand, slot_token, slot_weight, units, false, s));
-    MOE_TRY(moe::launch_transpose_pad(Wg, wgt, H, E, p.E_pad, dt, s));
-    MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, slot_weight, demand, H, E, C, C_pad, b.row_step, dt, xe, ge, s));
+    MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, slot_weight, demand, H, E, C, C_pad, b.row_step, dt, xe, ge, Wg, wgt, s));
     // grouped GEMMs over the experts' live rows
     moe::GemmArgs g{};
     g.rows_dev = demand; g.rows_fixed = 0; g.rows_cap = C; g.groups = E; g.max_rows = C;
@@ -474,11 +473,14 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     MOE_TRY(moe::launch_grouped_gemm(d2, s));
     // weight gradients: dW2[e] = h[e]^T ge[e], dW1[e] = xe[e]^T da[e] over the expert's slots, dWg = x^T dL over the tokens
     float* const wg_out = b.wg_slices > 1 ? (float*)ws_at(ws, b.off_wg_part) : dWg;
+    moe::BwdFinish finish{};
     if (dt != MOE_F32) {
         float *dW1_out = dW1, *dW2_out = dW2;
         if (b.w_slices > 1) {
             dW1_out = (float*)ws_at(ws, b.off_xeT);
             dW2_out = dW1_out + (size_t)b.w_slices * E * HI;
+            finish.sum[0] = {dW1_out, b.w_slices, E * HI, dW1};
+            finish.sum[1] = {dW2_out, b.w_slices, E * HI, dW2};
         }
         if (b.w_stream) {
             int32_t* wrows = (int32_t*)ws_at(ws, b.off_wrows);
@@ -495,10 +497,6 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
             {xe, rH, H, C_pad, da, rI, I, dW1_out, HI, I, demand, C, H, I, experts, b.w_slices},
             {x, 0, H, T, dL, 0, b.ldL, wg_out, (long long)H * E, E, nullptr, T, H, E, 1, b.wg_slices}};
         MOE_TRY(moe::launch_wgrad(w, dt, s));
-        if (b.w_slices > 1) {
-            MOE_TRY(moe::launch_bwd_sum_slices(dW1_out, b.w_slices, E * HI, dW1, s));
-            MOE_TRY(moe::launch_bwd_sum_slices(dW2_out, b.w_slices, E * HI, dW2, s));
-        }
     } else {
         auto weight_grad = [&](const void* rows, int M, void* rowsT, const void* grad, int N, float* out) {
             if (hipError_t e = moe::launch_bwd_transpose(rows, rowsT, E, C_pad, M, C_pad, dt, s); e != hipSuccess) return e;
@@ -522,13 +520,13 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
         wg.C = wg_out; wg.ldc = E; wg.c_group_stride = (long long)H * E; wg.N = E; wg.K = b.wg_slice_k;   // rows of both beyond T are zero
         MOE_TRY(moe::launch_grouped_gemm(wg, s));
     }
-    if (b.wg_slices > 1) MOE_TRY(moe::launch_bwd_sum_slices(wg_out, b.wg_slices, (long long)H * E, dWg, s));
-    MOE_TRY(moe::launch_bwd_colsum(ge, slot_weight, demand, E, C, C_pad, H, dt, db2, s));
-    MOE_TRY(moe::launch_bwd_colsum(da, nullptr, demand, E, C, C_pad, I, dt, db1, s));
-    // dgate_bias = column sums of dl
-    MOE_TRY(moe::launch_bwd_gate_bias(topk_expert, dl, T, k, E, dgate_bias, s));
-    // dx: the kept choices' rows of dxe plus the gate path
-    MOE_TRY(moe::launch_bwd_dx(dxe, wgt, topk_expert, slot, dl, T, H, k, E, C, C_pad, dt, dx, s));
+    // dWg from its slices, the bias gradients, and dx: the kept choices' rows of dxe plus the gate path
+    finish.sum[2] = {wg_out, b.wg_slices, (long long)H * E, dWg};
+    finish.topk_expert = topk_expert; finish.slot = slot; finish.expert_demand = demand; finish.dl = dl; finish.slot_weight = slot_weight;
+    finish.dxe = dxe; finish.WgT = wgt; finish.ge = ge; finish.da = da;
+    finish.dx = dx; finish.dgate_bias = dgate_bias; finish.db1 = db1; finish.db2 = db2;
+    finish.T = T; finish.H = H; finish.I = I; finish.k = k; finish.E = E; finish.C = C; finish.C_pad = C_pad;
+    MOE_TRY(moe::launch_bwd_finish(finish, dt, s));
 #undef MOE_TRY
     return MOE_OK;
 }

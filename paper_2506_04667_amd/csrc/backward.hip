@@ -75,11 +75,29 @@ __device__ __forceinline__ int written_rows(int live, int row_step) { return (ma
 // row of dout puts both at the same distance from that end; it leaves weight and row alone where the row is the smaller one.
 __device__ __forceinline__ bool negated(int token) { return ((uint32_t)token * 0x9e3779b1u >> 31) != 0; }
 
+// The workgroups after the rows' transpose Wg for bwd_finish_kernel, a 32 x 32 tile each: WgT[e][h] = Wg[h][e].
+template <class elem>
+__device__ __forceinline__ void transpose_gate_weights(const elem* __restrict__ Wg, elem* __restrict__ WgT, int H, int E, int tile_id) {
+    __shared__ elem tile[32][33];
+    const int nh = (H + 31) / 32, h0 = tile_id % nh * 32, e0 = tile_id / nh * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;             // 32 x 8
+    for (int r = ty; r < 32; r += 8)
+        if (h0 + r < H && e0 + tx < E) tile[r][tx] = Wg[(size_t)(h0 + r) * E + e0 + tx];
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8)
+        if (e0 + r < E && h0 + tx < H) WgT[(size_t)(e0 + r) * H + h0 + tx] = tile[tx][r];
+}
+
 template <class S>
 __global__ __launch_bounds__(256) void bwd_gather_kernel(const void* __restrict__ x, const void* __restrict__ dout,
                                                          const int32_t* __restrict__ slot_token, float* __restrict__ slot_weight,
                                                          const int32_t* __restrict__ expert_demand, int H, int C, int C_pad, int row_step,
-                                                         void* __restrict__ xe, void* __restrict__ ge) {
+                                                         void* __restrict__ xe, void* __restrict__ ge, int rows,
+                                                         const void* __restrict__ Wg, void* __restrict__ WgT, int E) {
+    if ((int)blockIdx.x >= rows) {
+        typedef typename S::store_t elem;
+        return transpose_gate_weights((const elem*)Wg, (elem*)WgT, H, E, (int)blockIdx.x - rows);
+    }
     const size_t row = blockIdx.x;
     const int e = (int)(row / C_pad), s = (int)(row % C_pad);
     if (s >= written_rows(min(expert_demand[e], C), row_step)) return;
@@ -281,13 +299,13 @@ __global__ __launch_bounds__(256) void bwd_transpose_kernel(const elem* __restri
 // bytes of the columns of one expert; wavefront w adds the rows w, w + 4, ... in ascending order, four loads in flight
 // per lane, and the four partial sums are added in wavefront order: a fixed order, the same from run to run.
 template <class S, bool WEIGHTED>
-__global__ __launch_bounds__(256) void bwd_colsum_kernel(const void* __restrict__ in, const float* __restrict__ weight,
-                                                         const int32_t* __restrict__ expert_demand, int C, int C_pad, int cols,
-                                                         float* __restrict__ out) {
+__device__ __forceinline__ void bwd_colsum(const void* __restrict__ in, const float* __restrict__ weight,
+                                           const int32_t* __restrict__ expert_demand, int C, int C_pad, int cols, float* __restrict__ out,
+                                           int e, int block, float* __restrict__ lds) {
     constexpr int VEC = S::kVec;
-    __shared__ float part[3][64][VEC];
-    const int e = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row_chunks = cols / VEC, c = blockIdx.x * 64 + lane;
+    float (*part)[64][VEC] = (float (*)[64][VEC])lds;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row_chunks = cols / VEC, c = block * 64 + lane;
     const int n = min(expert_demand[e], C);
     float acc[VEC];
 #pragma unroll
@@ -328,18 +346,25 @@ __global__ __launch_bounds__(256) void bwd_colsum_kernel(const void* __restrict_
 }
 
 // dgate_bias[e] = sum of dl over the pairs that selected e: one workgroup per expert, fixed reduction tree.
-__global__ __launch_bounds__(256) void bwd_gate_bias_kernel(const int32_t* __restrict__ topk_expert, const float* __restrict__ dl,
-                                                            long long P, float* __restrict__ dgate_bias) {
-    __shared__ float part[256];
-    const int e = blockIdx.x;
+__device__ __forceinline__ void bwd_gate_bias(const int32_t* __restrict__ topk_expert, const float* __restrict__ dl, long long P,
+                                              float* __restrict__ dgate_bias, int e, float* __restrict__ part) {
     float acc = 0.0f;
-    const long long P4 = P / 4;                         // four pairs per thread and step (both tables are 16-byte aligned)
-    for (long long p = threadIdx.x; p < P4; p += 256) {
-        const u32x4 ev = ((const u32x4*)topk_expert)[p];
-        const f32x4 dv = ((const f32x4*)dl)[p];
+    const long long P4 = P / 4;                         // four pairs per thread and load (both tables are 16-byte aligned)
+    constexpr int kTrip = 4;                            // loads of either table in flight
+    for (long long p0 = threadIdx.x; p0 < P4; p0 += 256 * kTrip) {
+        u32x4 ev[kTrip];
+        f32x4 dv[kTrip];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if ((int)ev[q] == e) acc += dv[q];
+        for (int i = 0; i < kTrip; ++i) {
+            const long long p = min(p0 + i * 256, P4 - 1);
+            ev[i] = ((const u32x4*)topk_expert)[p];
+            dv[i] = ((const f32x4*)dl)[p];
+        }
+#pragma unroll
+        for (int i = 0; i < kTrip; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (p0 + i * 256 < P4 && (int)ev[i][q] == e) acc += dv[i][q];
     }
     for (long long p = P4 * 4 + threadIdx.x; p < P; p += 256)
         if (topk_expert[p] == e) acc += dl[p];
@@ -352,16 +377,26 @@ __global__ __launch_bounds__(256) void bwd_gate_bias_kernel(const int32_t* __res
     if (threadIdx.x == 0) dgate_bias[e] = part[0];
 }
 
+// out[i] = part[0][i] + part[1][i] + ... in that order, i < n4
+__device__ __forceinline__ void bwd_sum_slices(const f32x4* __restrict__ part, int slices, long long n4, f32x4* __restrict__ out, long long i) {
+    if (i >= n4) return;
+    f32x4 acc = part[i];
+    for (int g = 1; g < slices; ++g) {
+        const f32x4 v = part[(size_t)g * n4 + i];
+        acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
+    }
+    out[i] = acc;
+}
+
 // One wavefront per token: dx_i = sum over kept choices of dxe[e_ij, slot_ij, :] (ascending j), then
 // + sum over all k choices of dl_ij * Wg[:, e_ij] (rows of WgT), in fp32.  Lane j holds the routing entries of choice j
 // (k <= 64); a lane owns 16-byte chunks lane, lane + 64, ... of the row.
 template <class S>
-__global__ __launch_bounds__(256) void bwd_dx_kernel(const void* __restrict__ dxe, const void* __restrict__ WgT,
-                                                     const int32_t* __restrict__ topk_expert, const int32_t* __restrict__ slot,
-                                                     const float* __restrict__ dl, int T, int H, int k, int E, int C, int C_pad,
-                                                     float* __restrict__ dx) {
+__device__ __forceinline__ void bwd_dx(const void* __restrict__ dxe, const void* __restrict__ WgT, const int32_t* __restrict__ topk_expert,
+                                       const int32_t* __restrict__ slot, const float* __restrict__ dl, int T, int H, int k, int E, int C,
+                                       int C_pad, float* __restrict__ dx, int block) {
     constexpr int VEC = S::kVec;
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int t = block * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (t >= T) return;
     long long row_lane = -1;
     int e_lane = -1;
@@ -409,6 +444,34 @@ __global__ __launch_bounds__(256) void bwd_dx_kernel(const void* __restrict__ dx
     }
 }
 
+// What is left once the weight gradients' products are made, in one launch: each of these is a few microseconds in a small layer,
+// where a launch costs as much.  Workgroups in the order of the fields' ends; dx, the longest, comes last.
+template <class S>
+__global__ __launch_bounds__(256) void bwd_finish_kernel(BwdFinish a) {
+    __shared__ __attribute__((aligned(16))) float lds[3 * 64 * S::kVec];
+    static_assert(3 * 64 * S::kVec >= 256, "the gate bias's reduction");
+    const int b = blockIdx.x;
+    if (b < a.E) return bwd_gate_bias(a.topk_expert, a.dl, (long long)a.T * a.k, a.dgate_bias, b, lds);
+    if (b < a.end_db2) {
+        const int i = b - a.E, per = (a.end_db2 - a.E) / a.E;
+        return bwd_colsum<S, true>(a.ge, a.slot_weight, a.expert_demand, a.C, a.C_pad, a.H, a.db2, i / per, i % per, lds);
+    }
+    if (b < a.end_db1) {
+        const int i = b - a.end_db2, per = (a.end_db1 - a.end_db2) / a.E;
+        return bwd_colsum<S, false>(a.da, nullptr, a.expert_demand, a.C, a.C_pad, a.I, a.db1, i / per, i % per, lds);
+    }
+    int start = a.end_db1;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        if (b < a.end_sum[q]) {
+            const BwdSlices& m = a.sum[q];
+            return bwd_sum_slices((const f32x4*)m.part, m.slices, m.n / 4, (f32x4*)m.out, (long long)(b - start) * 256 + threadIdx.x);
+        }
+        start = a.end_sum[q];
+    }
+    bwd_dx<S>(a.dxe, a.WgT, a.topk_expert, a.slot, a.dl, a.T, a.H, a.k, a.E, a.C, a.C_pad, a.dx, b - start);
+}
+
 }  // namespace
 
 __global__ __launch_bounds__(256) void bwd_fill_rows_kernel(int32_t* __restrict__ rows, int E, int first, int second) {
@@ -422,11 +485,13 @@ hipError_t launch_bwd_fill_rows(int32_t* rows, int E, int first, int second, hip
 }
 
 hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, float* slot_weight, const int32_t* expert_demand,
-                             int H, int E, int C, int C_pad, int row_step, int dtype, void* xe, void* ge, hipStream_t s) {
-    const dim3 g((unsigned)((size_t)E * C_pad)), b(256);
-    if (dtype == 0) hipLaunchKernelGGL(bwd_gather_kernel<F32>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge);
-    else if (dtype == 1) hipLaunchKernelGGL(bwd_gather_kernel<BF16>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge);
-    else hipLaunchKernelGGL(bwd_gather_kernel<F16>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge);
+                             int H, int E, int C, int C_pad, int row_step, int dtype, void* xe, void* ge, const void* Wg, void* WgT, hipStream_t s) {
+    const long long rows = (long long)E * C_pad, tiles = (long long)((H + 31) / 32) * ((E + 31) / 32);
+    if (rows + tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 g((unsigned)(rows + tiles)), b(256);
+    if (dtype == 0) hipLaunchKernelGGL(bwd_gather_kernel<F32>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge, (int)rows, Wg, WgT, E);
+    else if (dtype == 1) hipLaunchKernelGGL(bwd_gather_kernel<BF16>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge, (int)rows, Wg, WgT, E);
+    else hipLaunchKernelGGL(bwd_gather_kernel<F16>, g, b, 0, s, x, dout, slot_token, slot_weight, expert_demand, H, C, C_pad, row_step, xe, ge, (int)rows, Wg, WgT, E);
     return hipGetLastError();
 }
 
@@ -451,24 +516,6 @@ hipError_t launch_bwd_gate(const float* p, const int32_t* topk_expert, const flo
     return hipGetLastError();
 }
 
-// out[i] = part[0][i] + part[1][i] + ... in that order, i < n (n a multiple of 4)
-__global__ __launch_bounds__(256) void bwd_sum_slices_kernel(const f32x4* __restrict__ part, int slices, long long n4, f32x4* __restrict__ out) {
-    const long long i = blockIdx.x * 256ll + threadIdx.x;
-    if (i >= n4) return;
-    f32x4 acc = part[i];
-    for (int g = 1; g < slices; ++g) {
-        const f32x4 v = part[(size_t)g * n4 + i];
-        acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
-    }
-    out[i] = acc;
-}
-
-hipError_t launch_bwd_sum_slices(const float* part, int slices, long long n, float* out, hipStream_t s) {
-    const long long n4 = n / 4;
-    hipLaunchKernelGGL(bwd_sum_slices_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, (const f32x4*)part, slices, n4, (f32x4*)out);
-    return hipGetLastError();
-}
-
 hipError_t launch_bwd_transpose(const void* in, void* out, int groups, int R, int Cc, int ld_out, int dtype, hipStream_t s) {
     if (groups <= 0 || R <= 0 || Cc <= 0) return hipSuccess;
     if (groups > 65535 || (Cc + 63) / 64 > 65535 || (Cc & 1) || (ld_out & 1)) return hipErrorInvalidValue;
@@ -478,30 +525,22 @@ hipError_t launch_bwd_transpose(const void* in, void* out, int groups, int R, in
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_colsum(const void* in, const float* weight, const int32_t* expert_demand, int E, int C, int C_pad, int cols,
-                             int dtype, float* out, hipStream_t s) {
-    if (E > 65535) return hipErrorInvalidValue;
-    const int chunks = cols / (dtype == 0 ? 4 : 8);      // 16-byte chunks per row (cols is a multiple of 8)
-    const dim3 g((unsigned)((chunks + 63) / 64), (unsigned)E), b(256);
-#define MOE_BWD_COLSUM(S_, W_) hipLaunchKernelGGL((bwd_colsum_kernel<S_, W_>), g, b, 0, s, in, weight, expert_demand, C, C_pad, cols, out)
-    if (dtype == 0) { if (weight) MOE_BWD_COLSUM(F32, true); else MOE_BWD_COLSUM(F32, false); }
-    else if (dtype == 1) { if (weight) MOE_BWD_COLSUM(BF16, true); else MOE_BWD_COLSUM(BF16, false); }
-    else { if (weight) MOE_BWD_COLSUM(F16, true); else MOE_BWD_COLSUM(F16, false); }
-#undef MOE_BWD_COLSUM
-    return hipGetLastError();
-}
-
-hipError_t launch_bwd_gate_bias(const int32_t* topk_expert, const float* dl, int T, int k, int E, float* dgate_bias, hipStream_t s) {
-    hipLaunchKernelGGL(bwd_gate_bias_kernel, dim3((unsigned)E), dim3(256), 0, s, topk_expert, dl, (long long)T * k, dgate_bias);
-    return hipGetLastError();
-}
-
-hipError_t launch_bwd_dx(const void* dxe, const void* WgT, const int32_t* topk_expert, const int32_t* slot, const float* dl, int T, int H,
-                         int k, int E, int C, int C_pad, int dtype, float* dx, hipStream_t s) {
-    const dim3 g((unsigned)((T + 3) / 4)), b(256);
-    if (dtype == 0) hipLaunchKernelGGL(bwd_dx_kernel<F32>, g, b, 0, s, dxe, WgT, topk_expert, slot, dl, T, H, k, E, C, C_pad, dx);
-    else if (dtype == 1) hipLaunchKernelGGL(bwd_dx_kernel<BF16>, g, b, 0, s, dxe, WgT, topk_expert, slot, dl, T, H, k, E, C, C_pad, dx);
-    else hipLaunchKernelGGL(bwd_dx_kernel<F16>, g, b, 0, s, dxe, WgT, topk_expert, slot, dl, T, H, k, E, C, C_pad, dx);
+hipError_t launch_bwd_finish(BwdFinish a, int dtype, hipStream_t s) {
+    const int vec = dtype == 0 ? 4 : 8;                  // elements of a 16-byte chunk; a workgroup of the column sums owns 64 chunks
+    long long end = a.E;
+    auto add = [&](long long n) {
+        end += n;
+        return end > 0x7fffffffLL ? 0x7fffffff : (int)end;
+    };
+    a.end_db2 = add((long long)a.E * ((a.H / vec + 63) / 64));
+    a.end_db1 = add((long long)a.E * ((a.I / vec + 63) / 64));
+    for (int q = 0; q < 3; ++q) a.end_sum[q] = add(a.sum[q].slices > 1 ? (a.sum[q].n / 4 + 255) / 256 : 0);
+    add((a.T + 3ll) / 4);
+    if (end > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 g((unsigned)end), b(256);
+    if (dtype == 0) hipLaunchKernelGGL(bwd_finish_kernel<F32>, g, b, 0, s, a);
+    else if (dtype == 1) hipLaunchKernelGGL(bwd_finish_kernel<BF16>, g, b, 0, s, a);
+    else hipLaunchKernelGGL(bwd_finish_kernel<F16>, g, b, 0, s, a);
     return hipGetLastError();
 }
 

@@ -166,9 +166,9 @@ hipError_t prepare_wgrad();
 hipError_t launch_bwd_fill_rows(int32_t* rows, int E, int first, int second, hipStream_t s);
 // xe[e, s, :] = x[token] and ge[e, s, :] = dout[token] for live slots, zeros for the empty ones up to the next multiple of
 // row_step (an expert without rows: for the first row_step); ge and slot_weight[e, s] change their sign together for about
-// half of the tokens
+// half of the tokens.  WgT[e, h] = Wg[h, e]
 hipError_t launch_bwd_gather(const void* x, const void* dout, const int32_t* slot_token, float* slot_weight, const int32_t* expert_demand,
-                             int H, int E, int C, int C_pad, int row_step, int dtype, void* xe, void* ge, hipStream_t s);
+                             int H, int E, int C, int C_pad, int row_step, int dtype, void* xe, void* ge, const void* Wg, void* WgT, hipStream_t s);
 // over [E, C_pad, I], w = slot_weight[e, s]: h = w phi(a), da = w dh phi'(a), p[e, s] = w (<phi(a), dh> + <ge, b2>) (b2
 // optional; h may be a; da may be dh in fp32 storage); h = da = 0 in the rows where bwd_gather writes zeros
 hipError_t launch_bwd_act(const void* a, const float* dh, const void* ge, const void* b2, const int32_t* expert_demand,
@@ -178,16 +178,22 @@ hipError_t launch_bwd_act(const void* a, const float* dh, const void* ge, const 
 // selected gate logits (k <= 64) from p
 hipError_t launch_bwd_gate(const float* p, const int32_t* topk_expert, const float* topk_weight, const int32_t* slot, int T, int T_pad,
                            int k, int E, int C, int C_pad, int ld, int dtype, float* dl, void* dL, hipStream_t s);
-// out[i] = sum over g < slices of part[g * n + i], in ascending g (n a multiple of 4, 16-byte aligned buffers)
-hipError_t launch_bwd_sum_slices(const float* part, int slices, long long n, float* out, hipStream_t s);
 // out[g][c][r] = in[g][r][c], r < R, c < Cc; rows of out have ld_out entries, zero at and beyond R
 hipError_t launch_bwd_transpose(const void* in, void* out, int groups, int R, int Cc, int ld_out, int dtype, hipStream_t s);
-// out[e][c] = sum over live rows of weight[e][r] in[e][r][c] (fp32); weight == nullptr: of in[e][r][c]
-hipError_t launch_bwd_colsum(const void* in, const float* weight, const int32_t* expert_demand, int E, int C, int C_pad, int cols,
-                             int dtype, float* out, hipStream_t s);
-hipError_t launch_bwd_gate_bias(const int32_t* topk_expert, const float* dl, int T, int k, int E, float* dgate_bias, hipStream_t s);
-// dx[t, :] = sum of the kept choices' rows of dxe + sum over choices of dl * WgT[expert, :]
-hipError_t launch_bwd_dx(const void* dxe, const void* WgT, const int32_t* topk_expert, const int32_t* slot, const float* dl, int T, int H,
-                         int k, int E, int C, int C_pad, int dtype, float* dx, hipStream_t s);
+// The rest of the backward pass once the products are made.  db2[e, c] = sum over live rows of slot_weight[e, r] ge[e, r, c] and db1
+// likewise of da alone; dgate_bias[e] = sum of dl over the pairs that selected e; dx[t, :] = sum of the kept choices' rows of dxe + sum
+// over choices of dl WgT[expert, :]; and for sums made in slices (slices > 1) out[i] = sum over g of part[g * n + i], g ascending
+// (n a multiple of 4).  All fp32.  The ends of the workgroups' ranges are filled in by the launch.
+struct BwdSlices { const float* part; int slices; long long n; float* out; };
+struct BwdFinish {
+    const int32_t *topk_expert, *slot, *expert_demand;
+    const float *dl, *slot_weight;
+    const void *dxe, *WgT, *ge, *da;
+    float *dx, *dgate_bias, *db1, *db2;
+    BwdSlices sum[3];
+    int T, H, I, k, E, C, C_pad;
+    int end_db2, end_db1, end_sum[3];
+};
+hipError_t launch_bwd_finish(BwdFinish a, int dtype, hipStream_t s);
 
 }  // namespace moe
