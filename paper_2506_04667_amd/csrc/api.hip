@@ -134,6 +134,11 @@ char* ws_at(void* ws, size_t off) { return (char*)ws + off; }
 
 // ---- stage launchers (arguments already validated) ---------------------------------
 
+// the gate's slices; their sums lie where h and y go later
+int gate_slices(const moe_config* c, const Plan& p) {
+    return moe::gate_slices(c->T, c->H, c->dtype, moe::device_cu_count(), p.total - p.off_h, c->E);
+}
+
 moe_status run_gate(const moe_config* c, const Plan& p, void* ws, const void* x, const void* Wg,
                     const float* gate_bias, float* logits, int32_t* topk_expert, float* topk_weight,
                     bool* route_counts_written, hipStream_t s) {
@@ -143,8 +148,8 @@ moe_status run_gate(const moe_config* c, const Plan& p, void* ws, const void* x,
     if (moe::gate_fused_eligible(c->T, c->H, c->E, c->k, c->dtype)) {
         int32_t* counts = route_counts_written ? (int32_t*)ws_at(ws, p.off_counts) : nullptr;
         if (route_counts_written) *route_counts_written = true;
-        return hip_status(moe::launch_gate_fused(x, Wg, gate_bias, c->T, c->H, c->E, c->k, c->dtype, logits,
-                                                 topk_expert, topk_weight, counts, s));
+        return hip_status(moe::launch_gate_fused(x, Wg, gate_bias, c->T, c->H, c->E, c->k, c->dtype, logits, topk_expert, topk_weight,
+                                                 counts, gate_slices(c, p), (float*)ws_at(ws, p.off_h), s));
     }
     void* wgt = ws_at(ws, p.off_wgt);
     hipError_t e = moe::launch_transpose_pad(Wg, wgt, c->H, c->E, p.E_pad, c->dtype, s);
@@ -291,7 +296,7 @@ moe_status forward_impl(const moe_config* cfg, void* workspace, size_t workspace
         // Alg. 1 as one persistent kernel: the same stages from one launch, device-wide barriers in between
         moe::GemmArgs g1, g2;
         ffn_gemms(cfg, p, workspace, x, slot_token, expert_demand, W1, b1, W2, b2, y, &g1, &g2);
-        if (moe::launch_layer_fused(x, Wg, gate_bias, cfg->T, cfg->H, cfg->E, cfg->k, p.C, p.C_pad, cfg->dtype, logits, topk_expert,
+        if (moe::launch_layer_fused(x, Wg, gate_bias, cfg->T, cfg->H, cfg->E, cfg->k, p.C, p.C_pad, cfg->dtype, gate_slices(cfg, p), logits, topk_expert,
                                     topk_weight, (int32_t*)ws_at(workspace, p.off_counts), slot, expert_demand, slot_token,
                                     slot_weight, g1, g2, out, s) != hipSuccess)
             return MOE_ERR_HIP;

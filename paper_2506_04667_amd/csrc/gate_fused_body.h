@@ -77,17 +77,27 @@ __device__ __forceinline__ void merge_best(float& bv, int& bi) {
     if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
 }
 
-// The gate for the 64 tokens of tile number `tile` (tokens 64 tile .. 64 tile + 63), by all G_THREADS threads of a
-// workgroup that has GateCfg<S, BN_>::LDS_BYTES of dynamic LDS.  route_counts (optional) receives row `tile`.
-template <class S, int BN_>
-__device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict__ x, const unsigned char* __restrict__ Wg,
-                                                const float* __restrict__ gate_bias, int T, int H, int E, int k,
-                                                float* __restrict__ logits, int32_t* __restrict__ topk_expert,
-                                                float* __restrict__ topk_weight, int32_t* __restrict__ route_counts, int tile) {
+// zeros for the copies' lanes beyond the last k
+static __device__ const u32x4 gate_zeros = {0u, 0u, 0u, 0u};
+
+// K-tiles of a gate of H k, and of its slice `slice` (of `slices`): [first, end)
+__host__ __device__ inline int gate_k_tiles(int H, int el) { return (H * el + 127) / 128; }
+__host__ __device__ inline int gate_slice_begin(int nk, int slice, int slices) { return (int)((long long)nk * slice / slices); }
+
+// The logits of the 64 tokens of tile number `tile` (tokens 64 tile .. 64 tile + 63), by all G_THREADS threads of a workgroup that
+// has GateCfg<S, BN_>::LDS_BYTES of dynamic LDS, into its [64][LP] floats: the sum of slices [slice0, slice1) of the K-tiles, each
+// summed by itself and added in that order, plus the bias (optional).
+// LIN: E is a multiple of 4 but not of 8 in 16-bit storage, so that rows of Wg do not start on 16-byte chunks: a K-tile of it, which is
+// contiguous, is copied as it lies, without a swizzle (transpose reads take 8 bytes of a row from anywhere).
+template <class S, int BN_, bool LIN>
+__device__ __forceinline__ void gate_logits_tile(const unsigned char* __restrict__ x, const unsigned char* __restrict__ Wg,
+                                                 const float* __restrict__ gate_bias, int T, int H, int E, int tile, int slice0, int slice1,
+                                                 int slices) {
     using C = GateCfg<S, BN_>;
     constexpr int BN = C::BN, PITCH = C::PITCH, STAGE = C::STAGE, D = C::STAGES, TN = C::TN, LP = C::LP;
     constexpr int EL = C::EL, VEC = C::VEC, KT = C::KT;
     constexpr bool k16 = EL == 2;
+    static_assert(!LIN || k16, "chunks of four fp32 experts are aligned");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
     const int tid = threadIdx.x;
@@ -99,6 +109,15 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
     const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const int l32 = lane & 31, g2 = lane >> 5;
     const int row0 = tile * G_BM;
+    const int nk_all = gate_k_tiles(H, EL);
+    f32x16 total[TN];                                   // group 0: sum of the slices so far
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) total[j][q] = 0.0f;
+    float* lg = (float*)smem;
+    for (int slice = slice0; slice < slice1; ++slice) {
+    const int k_begin = gate_slice_begin(nk_all, slice, slices), nk = gate_slice_begin(nk_all, slice + 1, slices) - k_begin;
 
     // ---- this wavefront's 1 KB copies per K-tile: 1 of token rows (8 rows x 128 B), B_COPIES of Wg ----
     // Workgroup b starts its K loop at K-tile b % nk and wraps around: at any moment the workgroups read
@@ -106,13 +125,13 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
     // spread over all memory channels instead of marching down one 4 KB-strided column band together.  The
     // order in which a workgroup accumulates its K-tiles depends on its number only: results are the same
     // from run to run.
-    const int nk = H / KT;
-    const int k_first = kRotateK ? (int)((unsigned)tile % (unsigned)nk) : 0;
+    const int k_first = k_begin + (kRotateK ? (int)((unsigned)tile % (unsigned)nk) : 0);
     const size_t b_step = (size_t)KT * E * EL;
     const unsigned char* const a_row0 = uniform(x + (size_t)row0 * H * EL);
     const unsigned char* a_base = uniform(a_row0 + (size_t)k_first * 128);
     const unsigned char* b_base = uniform(Wg + (size_t)k_first * b_step);
     int k_issue = k_first;                              // K-tile the next request fetches
+    const int k_ragged = H % KT ? nk_all - 1 : -1;      // K-tile that ends beyond H
     uint32_t a_off, b_off[C::B_COPIES];
     {
         const int r = wave * 8 + (lane >> 3), p = lane & 7;
@@ -123,6 +142,10 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
     constexpr int CPR = PITCH / 16;                     // 16-byte chunks per k-row
 #pragma unroll
     for (int j = 0; j < C::B_COPIES; ++j) {
+        if (LIN) {                                      // chunk i of the K-tile's KT E elements; beyond its end the last one again
+            b_off[j] = (uint32_t)min(((wave * C::B_COPIES + j) * 64 + lane) * 16, KT * E * EL - 16);
+            continue;
+        }
         const int kk = (wave * C::B_COPIES + j) * (64 / CPR) + lane / CPR, p = lane % CPR;
         const int c = p ^ (k16 ? ((kk & 3) << 2) : (((kk >> 2) & 1) << 3));
         const int n = min(c * VEC, E - VEC);            // columns beyond E repeat the last experts (masked later)
@@ -132,16 +155,26 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
 
     auto issue = [&](int t) __attribute__((always_inline)) {
         const uint32_t d = lds_base + (t % D) * STAGE;
-        copy_to_lds(a_base, a_off, d + wave * 1024);
+        if (k_issue != k_ragged) {
+            copy_to_lds(a_base, a_off, d + wave * 1024);
 #pragma unroll
-        for (int j = 0; j < C::B_COPIES; ++j)
-            copy_to_lds(b_base, b_off[j], d + G_A_STAGE + (wave * C::B_COPIES + j) * 1024);
+            for (int j = 0; j < C::B_COPIES; ++j)
+                copy_to_lds(b_base, b_off[j], d + G_A_STAGE + (wave * C::B_COPIES + j) * 1024);
+        } else {                                        // H is a multiple of 8: a chunk of either operand is inside or beyond
+            const unsigned char* const zero = (const unsigned char*)&gate_zeros;
+            const int left = H - k_issue * KT;
+            const int c = (lane & 7) ^ (((wave * 8 + (lane >> 3)) >> 1) & 7);
+            copy_to_lds_lane(c * VEC < left ? a_base + a_off : zero, d + wave * 1024);
+#pragma unroll
+            for (int j = 0; j < C::B_COPIES; ++j)
+                copy_to_lds_lane(b_off[j] < (uint32_t)left * (uint32_t)(E * EL) ? b_base + b_off[j] : zero, d + G_A_STAGE + (wave * C::B_COPIES + j) * 1024);
+        }
         a_base += 128;
         b_base += b_step;
-        if (++k_issue == nk) {
-            k_issue = 0;
-            a_base = a_row0;
-            b_base = uniform(Wg);
+        if (++k_issue == k_begin + nk) {
+            k_issue = k_begin;
+            a_base = uniform(a_row0 + (size_t)k_begin * 128);
+            b_base = uniform(Wg + (size_t)k_begin * b_step);
         }
     };
 
@@ -155,7 +188,9 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
     for (int i = 0; i < 2; ++i) a_rd[i] = a_row * 128 + (((((2 * kg + i) << 1) | g2) ^ a_sw) << 4);
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
-        if (k16) {
+        if (LIN) {                                      // columns beyond E repeat the last four (masked later)
+            b_rd[tn] = G_A_STAGE + (2 * kg * 16 + bk) * E * EL + min((wn * TN + tn) * 8 + nb16 * 4 + (L & 3), E / 4 - 1) * 8;
+        } else if (k16) {
             const int chunk = (wn * TN + tn) * 4 + nb16 * 2 + ((L & 3) >> 1);
             b_rd[tn] = G_A_STAGE + (2 * kg * 16 + bk) * PITCH + ((chunk ^ ((bk & 3) << 2)) << 4) + (L & 1) * 8;
         } else {
@@ -167,6 +202,7 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
         }
     }
 
+    const int w_pitch = LIN ? E * EL : PITCH;           // bytes between k-rows of Wg in LDS
     f32x16 acc[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j)
@@ -191,9 +227,9 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
                 if constexpr (k16) {
-                    const unsigned char* pw = st + b_rd[tn] + ks * 16 * PITCH;
+                    const unsigned char* pw = st + b_rd[tn] + ks * 16 * w_pitch;
                     const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)pw));
-                    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(pw + 4 * PITCH)));
+                    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(pw + 4 * w_pitch)));
                     o.w[ks][tn] = u32x4{lo[0], lo[1], hi[0], hi[1]};
                 } else {
 #pragma unroll
@@ -245,10 +281,10 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
     if (u < nk) step(u, o0, o1);
     wait_copies_and_barrier<0>();                       // every wavefront is done with the ring: reuse it
 
-    // ---- logits tile [64 tokens][LP] fp32 in LDS: group 1 parks its partial sums, group 0 adds its own and
-    // the bias ----
+    // ---- group 1 parks its partial sums in LDS, group 0 adds its own; after the last slice it adds the bias, and the tile
+    // [64 tokens][LP] is complete ----
     // accumulator elements 4 qa .. 4 qa + 3 of tile tn: experts e .. e + 3 of token l32
-    float* lg = (float*)smem;
+    const bool last = slice + 1 == slice1;
 #pragma unroll
     for (int pass = 1; pass >= 0; --pass) {
         if (kg == pass) {
@@ -263,16 +299,32 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
                     for (int i = 0; i < 4; ++i) v[i] = acc[tn][qa * 4 + i];
                     if (pass == 0) {
                         f32x4 b = {0.0f, 0.0f, 0.0f, 0.0f};
-                        if (gate_bias && e < E) b = *(const f32x4*)(gate_bias + e);
+                        if (last && gate_bias && e < E) b = *(const f32x4*)(gate_bias + e);
                         const f32x4 other = *(const f32x4*)cell;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i] = (v[i] + other[i]) + b[i];
+                        for (int i = 0; i < 4; ++i) {
+                            const float sum = slice == slice0 ? v[i] + other[i] : total[tn][qa * 4 + i] + (v[i] + other[i]);
+                            total[tn][qa * 4 + i] = sum;
+                            v[i] = sum + b[i];
+                        }
                     }
                     *(f32x4*)cell = v;
                 }
         }
         __syncthreads();
     }
+    }
+}
+
+// Logits to memory, selection and combine weights of the tile's tokens from the [64][LP] logits at the start of the dynamic LDS (a
+// wavefront reads the rows of its own 8 tokens); route_counts (optional) receives row `tile`.
+template <int BN>
+__device__ __forceinline__ void gate_select_tile(int T, int E, int k, float* __restrict__ logits, int32_t* __restrict__ topk_expert,
+                                                 float* __restrict__ topk_weight, int32_t* __restrict__ route_counts, int tile) {
+    constexpr int LP = BN + 4;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), row0 = tile * G_BM;
+    float* lg = (float*)smem;
 
     // ---- logits to HBM: each wavefront stores its 8 tokens, full rows ----
     constexpr int TOK = G_BM / G_WAVES;                 // tokens per wavefront from here on
@@ -354,6 +406,16 @@ __device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict_
         __syncthreads();
         for (int e = tid; e < E; e += G_THREADS) route_counts[(size_t)tile * E + e] = hist[e];
     }
+}
+
+// The whole gate for one tile.
+template <class S, int BN_, bool LIN = false>
+__device__ __forceinline__ void gate_fused_tile(const unsigned char* __restrict__ x, const unsigned char* __restrict__ Wg,
+                                                const float* __restrict__ gate_bias, int T, int H, int E, int k, int slices,
+                                                float* __restrict__ logits, int32_t* __restrict__ topk_expert,
+                                                float* __restrict__ topk_weight, int32_t* __restrict__ route_counts, int tile) {
+    gate_logits_tile<S, BN_, LIN>(x, Wg, gate_bias, T, H, E, tile, 0, slices, slices);
+    gate_select_tile<BN_>(T, E, k, logits, topk_expert, topk_weight, route_counts, tile);
 }
 
 

@@ -104,7 +104,9 @@ bool gate_fused_eligible(int T, int H, int E, int k, int dtype);
 // of the slot assignment (launch_route with counts_ready).
 hipError_t launch_gate_fused(const void* x, const void* Wg, const float* gate_bias, int T, int H, int E, int k,
                              int dtype, float* logits, int32_t* topk_expert, float* topk_weight,
-                             int32_t* route_counts, hipStream_t stream);
+                             int32_t* route_counts, int slices, float* partial, hipStream_t stream);
+// How many slices its sums over H are best made in, given scratch of partial_bytes for slices * T * E floats; 1: none, no scratch.
+int gate_slices(int T, int H, int dtype, int cus, size_t partial_bytes, int E);
 
 // Top-k selection and combine weights from fp32 logits.
 hipError_t launch_topk(const float* logits, int T, int E, int k, int32_t* topk_expert,
@@ -136,7 +138,7 @@ hipError_t launch_combine(const void* y, const int32_t* topk_expert, const float
 // (g1.A = x gathered through slot_token, g2.C = y); counts = route_chunks(T) * E ints.
 bool layer_fused_eligible(int T, int H, int I, int ldh, int E, int k, int C_pad, int dtype);
 hipError_t launch_layer_fused(const void* x, const void* Wg, const float* gate_bias, int T, int H, int E, int k, int C, int C_pad,
-                              int dtype, float* logits, int32_t* topk_expert, float* topk_weight, int32_t* counts, int32_t* slot,
+                              int dtype, int gate_slices, float* logits, int32_t* topk_expert, float* topk_weight, int32_t* counts, int32_t* slot,
                               int32_t* expert_demand, int32_t* slot_token, float* slot_weight, const GemmArgs& g1, const GemmArgs& g2,
                               void* out, hipStream_t stream);
 hipError_t prepare_layer_fused();

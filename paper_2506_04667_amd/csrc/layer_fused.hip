@@ -47,7 +47,7 @@ __device__ __forceinline__ void stamp(int32_t* sync, int i) {
 
 struct LayerArgs {
     const unsigned char* x; const unsigned char* Wg; const float* gate_bias;
-    int T, H, E, k, C, C_pad;
+    int T, H, E, k, C, C_pad, gate_slices;             // the sums in as many slices as the default path's, for the same bits
     float* logits; int32_t* topk_expert; float* topk_weight;
     int32_t* counts;                                    // [chunks][E] scratch of the slot assignment
     int32_t* slot; int32_t* expert_demand; int32_t* slot_token; float* slot_weight;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(L_THREADS) void moe_layer_kernel(LayerArgs a) {
     stamp(a.sync, 0);
     // ---- gate: logits, top-k, combine weights, per-chunk expert counts
     for (int tile = bid; tile < n_chunks; tile += nb) {
-        gate_fused_tile<S, L_GATE_BN>(a.x, a.Wg, a.gate_bias, a.T, a.H, a.E, a.k, a.logits, a.topk_expert, a.topk_weight, a.counts, tile);
+        gate_fused_tile<S, L_GATE_BN>(a.x, a.Wg, a.gate_bias, a.T, a.H, a.E, a.k, a.gate_slices, a.logits, a.topk_expert, a.topk_weight, a.counts, tile);
         __syncthreads();                                // the tile's LDS is free again
     }
     stamp(a.sync, 1);
@@ -231,18 +231,18 @@ hipError_t layer_stage_ms(double* ms, int n, hipStream_t stream) {
 bool layer_fused_eligible(int T, int H, int I, int ldh, int E, int k, int C_pad, int dtype) {
     static_assert(G_THREADS == L_THREADS && THREADS == L_THREADS, "every stage of the layer runs with the same workgroup size");
     static_assert(GateCfg<BF16, L_GATE_BN>::LDS_BYTES <= LDS_BYTES, "the gate tile fits in the FFN kernel's LDS");
-    return dtype != 0 && E <= L_GATE_BN && gate_fused_eligible(T, H, E, k, dtype) &&
+    return dtype != 0 && E <= L_GATE_BN && E % 8 == 0 && gate_fused_eligible(T, H, E, k, dtype) &&
            stream_gemm_shape_ok(dtype, I, H, H, I, ldh, T) && stream_gemm_shape_ok(dtype, H, I, ldh, H, H, C_pad) &&
            (long long)L_WAVES * E * 4 + 64 * 4 <= LDS_BYTES;
 }
 
 hipError_t launch_layer_fused(const void* x, const void* Wg, const float* gate_bias, int T, int H, int E, int k, int C, int C_pad,
-                              int dtype, float* logits, int32_t* topk_expert, float* topk_weight, int32_t* counts, int32_t* slot,
+                              int dtype, int gate_slices, float* logits, int32_t* topk_expert, float* topk_weight, int32_t* counts, int32_t* slot,
                               int32_t* expert_demand, int32_t* slot_token, float* slot_weight, const GemmArgs& g1, const GemmArgs& g2,
                               void* out, hipStream_t stream) {
     LayerArgs a{};
     a.x = (const unsigned char*)x; a.Wg = (const unsigned char*)Wg; a.gate_bias = gate_bias;
-    a.T = T; a.H = H; a.E = E; a.k = k; a.C = C; a.C_pad = C_pad;
+    a.T = T; a.H = H; a.E = E; a.k = k; a.C = C; a.C_pad = C_pad; a.gate_slices = gate_slices;
     a.logits = logits; a.topk_expert = topk_expert; a.topk_weight = topk_weight; a.counts = counts;
     a.slot = slot; a.expert_demand = expert_demand; a.slot_token = slot_token; a.slot_weight = slot_weight;
     a.out = out;
