@@ -47,22 +47,36 @@ __global__ __launch_bounds__(G_THREADS) void gate_finish_kernel(GateArgs a) {
     const int tile = blockIdx.x, row0 = tile * G_BM, quads = a.E / 4;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t step = (size_t)a.T * a.E;
-    for (int i = lane; i < TOK * quads; i += 64) {      // the rows of this wavefront's tokens
-        const int r = wave * TOK + i / quads, e = i % quads * 4;
-        if (row0 + r >= a.T) continue;
-        const float* p = a.partial + (size_t)(row0 + r) * a.E + e;
-        f32x4 sum = *(const f32x4*)p;
-        constexpr int kTrip = 8;                        // slices in flight
-        for (int s0 = 1; s0 < a.slices; s0 += kTrip) {
-            f32x4 v[kTrip];
+    // the rows of this wavefront's tokens: two quads of experts and eight slices in flight per lane
+    for (int i0 = lane; i0 < TOK * quads; i0 += 128) {
+        f32x4 sum[2];
+        const float* p[2];
+        int cell[2];
 #pragma unroll
-            for (int q = 0; q < kTrip; ++q) v[q] = *(const f32x4*)(p + (size_t)min(s0 + q, a.slices - 1) * step);
-#pragma unroll
-            for (int q = 0; q < kTrip; ++q)
-                if (s0 + q < a.slices) sum += v[q];
+        for (int u = 0; u < 2; ++u) {
+            const int i = min(i0 + u * 64, TOK * quads - 1), r = wave * TOK + i / quads, e = i % quads * 4;
+            p[u] = a.partial + (size_t)min(row0 + r, a.T - 1) * a.E + e;       // (beyond the last token: not used)
+            cell[u] = r * LP + e;
+            sum[u] = *(const f32x4*)p[u];
         }
-        if (a.gate_bias) sum += *(const f32x4*)(a.gate_bias + e);
-        *(f32x4*)(lg + r * LP + e) = sum;
+        constexpr int kTrip = 8;
+        for (int s0 = 1; s0 < a.slices; s0 += kTrip) {
+            f32x4 v[2][kTrip];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int q = 0; q < kTrip; ++q) v[u][q] = *(const f32x4*)(p[u] + (size_t)min(s0 + q, a.slices - 1) * step);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int q = 0; q < kTrip; ++q)
+                    if (s0 + q < a.slices) sum[u] += v[u][q];
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (a.gate_bias) sum[u] += *(const f32x4*)(a.gate_bias + cell[u] % LP);
+            *(f32x4*)(lg + cell[u]) = sum[u];
+        }
     }
     __syncthreads();
     gate_select_tile<BN>(a.T, a.E, a.k, a.logits, a.topk_expert, a.topk_weight, a.route_counts, tile);

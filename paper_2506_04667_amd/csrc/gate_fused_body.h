@@ -373,6 +373,7 @@ __device__ __forceinline__ void gate_select_tile(int T, int E, int k, float* __r
             int bi = kNone;
 #pragma unroll
             for (int i = 0; i < VL; ++i) {
+                if ((i >> 2) * 64 >= E) break;          // (the same for all lanes)
                 const int e = (i >> 2) * 64 + s16 * 4 + (i & 3);   // ascending in i: equal values keep the earlier index
                 const float v = vals[c][i];
                 const bool avail = (j == 0) || (v < last_v[c]) || (v == last_v[c] && e > last_i[c]);

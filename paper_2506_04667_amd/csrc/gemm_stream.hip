@@ -70,6 +70,16 @@ hipError_t launch_stream_act(const GemmArgs& g1, const GemmArgs* g2, bool never_
             return g1.c_f32 ? launch_stream_t<S, kActF32Out, 1, kLayoutNK>(g1, nullptr, never_met, stream)
                             : launch_stream_t<S, 3, 1, kLayoutNK>(g1, nullptr, never_met, stream);
     }
+    if constexpr (NPH == 1) {
+        if (g1.K % (2 * BK) != 0) {
+            switch (g1.act) {
+                case 0: return launch_stream_t<S, 0, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
+                case 1: return launch_stream_t<S, 1, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
+                case 2: return launch_stream_t<S, 2, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
+                default: return launch_stream_t<S, 3, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
+            }
+        }
+    }
     switch (g1.act) {
         case 0: return launch_stream_t<S, 0, NPH>(g1, g2, never_met, stream);
         case 1: return launch_stream_t<S, 1, NPH>(g1, g2, never_met, stream);
@@ -88,6 +98,10 @@ hipError_t prepare_stream_s() {
     if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1, kLayoutKM>();
     if (e == hipSuccess) e = prepare_stream_t<S, kActF32Out, 1, kLayoutNK>();
     if (e == hipSuccess) e = prepare_stream_t<S, 3, 1, kLayoutNK>();
+    if (e == hipSuccess) e = prepare_stream_t<S, 0, 1, kLayoutRagged>();
+    if (e == hipSuccess) e = prepare_stream_t<S, 1, 1, kLayoutRagged>();
+    if (e == hipSuccess) e = prepare_stream_t<S, 2, 1, kLayoutRagged>();
+    if (e == hipSuccess) e = prepare_stream_t<S, 3, 1, kLayoutRagged>();
     if (e == hipSuccess) e = prepare_stream_t<S, 0, 2>();
     if (e == hipSuccess) e = prepare_stream_t<S, 1, 2>();
     if (e == hipSuccess) e = prepare_stream_t<S, 2, 2>();
@@ -141,8 +155,11 @@ bool stream_gemm_eligible(const GemmArgs& a) {
     if (a.c_f32 && !a.a_is_km && !a.b_is_nk) return false;
     if (a.b_is_nk && a.bias) return false;
     if (a.a_is_km && (!a.c_f32 || a.b_is_nk || a.a_row_index || a.rows_cap % 8 != 0)) return false;
-    return a.rows_dev != nullptr && a.units != nullptr &&
-           stream_gemm_shape_ok(a.dtype, a.N, a.K, a.lda, a.ldb, a.ldc, a.a_rows_total, a.a_is_km, a.b_is_nk);
+    if (a.rows_dev == nullptr || a.units == nullptr) return false;
+    // forward layouts whose K is no multiple of 64: as if K were filled up to the next one
+    const bool ragged = !a.b_is_nk && !a.a_is_km && a.K % 8 == 0 && a.K > 4 * BK;
+    return stream_gemm_shape_ok(a.dtype, a.N, ragged ? (a.K + 2 * BK - 1) / (2 * BK) * (2 * BK) : a.K, a.lda, a.ldb, a.ldc, a.a_rows_total,
+                                a.a_is_km, a.b_is_nk);
 }
 
 hipError_t launch_grouped_gemm_stream(const GemmArgs& a, hipStream_t stream) {
@@ -150,7 +167,7 @@ hipError_t launch_grouped_gemm_stream(const GemmArgs& a, hipStream_t stream) {
 }
 
 bool ffn_fused_eligible(const GemmArgs& g1, const GemmArgs& g2) {
-    return stream_gemm_eligible(g1) && stream_gemm_eligible(g2) && !g1.b_is_nk && !g2.b_is_nk && !g1.c_f32 && !g2.c_f32 && g2.act == 3 && g2.a_row_index == nullptr &&
+    return stream_gemm_eligible(g1) && stream_gemm_eligible(g2) && g1.K % (2 * BK) == 0 && g2.K % (2 * BK) == 0 && !g1.b_is_nk && !g2.b_is_nk && !g1.c_f32 && !g2.c_f32 && g2.act == 3 && g2.a_row_index == nullptr &&
            g1.units == g2.units && g1.rows_dev == g2.rows_dev && g1.rows_cap == g2.rows_cap &&
            g1.groups == g2.groups && g1.max_rows == g2.max_rows && g1.dtype == g2.dtype;
 }

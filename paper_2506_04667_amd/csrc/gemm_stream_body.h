@@ -55,7 +55,9 @@
 // transposes 32 rows at a time through a wave-private LDS area and stores full
 // 128-byte row segments.
 //
-// Requires K % 64 == 0, K >= 192 (kLayoutNK: 256) and N % 8 == 0; other shapes use the generic kernel.
+// Requires K % 64 == 0, K >= 192 (kLayoutNK: 256) and N % 8 == 0.  kLayoutRagged takes every K % 8 == 0 above 128: the last
+// pair of K-tiles is filled up with zeros, in both operands, so that an infinity beyond K cannot meet them.  Other shapes use the
+// generic kernel.
 #pragma once
 #include "common.h"
 #include "kernels.h"
@@ -157,8 +159,11 @@ struct StreamArgs {
     int spin_limit;                                     // NPH == 2: polls (about 100 ns apart) before a dependency wait gives up
 };
 
+// what the copies of a K-tile that ends beyond K read there
+static __device__ const u32x4 stream_zeros = {0u, 0u, 0u, 0u};
+
 constexpr int kSpinLimit = 1 << 21;
-constexpr int kLayoutNK = 1, kLayoutKM = 2;
+constexpr int kLayoutNK = 1, kLayoutKM = 2, kLayoutRagged = 4;
 constexpr int B_PAIR_STAGE = BN * 128, B_PAIR_STAGES = 3;               // kLayoutNK: 256 n x 64 k
 static_assert(B_REGION + B_PAIR_STAGES * B_PAIR_STAGE <= LDS_BYTES, "three pairs of [n][k] weights");
 constexpr int kActF32Out = 4;                           // template value of ACT: identity with C (and bias) in fp32
@@ -178,14 +183,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     const int32_t* const units = list + 1;              // [0] = live units, [1 + q] = group * nrow + row tile
     int32_t* const done = list + 2 + cap;               // [q] wavefronts that have stored a ph[0] tile of unit q; zero at launch
     constexpr int BM = 128 * G, TM = 4 * G;             // rows of a tile; 16-row MFMA tiles per wavefront
-    constexpr bool NK = (LAYOUT & kLayoutNK) != 0, KM = (LAYOUT & kLayoutKM) != 0;
+    constexpr bool NK = (LAYOUT & kLayoutNK) != 0, KM = (LAYOUT & kLayoutKM) != 0, RAGGED = (LAYOUT & kLayoutRagged) != 0;
+    static_assert(!RAGGED || (!NK && !KM), "only the forward layouts' last K-tiles are filled up with zeros");
     constexpr int B_COPIES = NK ? 4 : 2;                // 1 KB copies per wavefront and request of weights (NK: two K-tiles)
     constexpr int A_COPIES = 2 * G;                     // 1 KB copies per wavefront and activation stage
     static_assert(BM == (G == 2 ? kUnitRowsLarge : kUnitRowsSmall), "the unit list is cut in row tiles of this kernel");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
     const int ncol = (P.N + BN - 1) / BN;
-    const int nk = P.K / BK;                            // K-tiles per task (even, >= 6)
+    const int nk = RAGGED ? (P.K + 2 * BK - 1) / (2 * BK) * 2 : P.K / BK;      // K-tiles per task (even, >= 6)
     const int nrow = (a.max_rows + BM - 1) / BM;
 
     // Work is the compact list of live (expert, row tile) units, each one task per column tile.  Each XCD
@@ -327,11 +333,26 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     const uint32_t lds_a_wave = lds_base + wave * (A_COPIES * 1024);
     const uint32_t lds_b_wave = lds_base + B_REGION + wave * (B_COPIES * 1024);
 
+    // the lane number, opaque to the compiler: what is made of it is made there and not kept in registers across the main loop
+    auto lane_here = [&]() __attribute__((always_inline)) {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
     int a_issue_stage = 0, b_issue_stage = 0;
     auto issue_a = [&]() __attribute__((always_inline)) {                              // next pair of K-tiles of the activation rows
         const uint32_t d = lds_a_wave + a_issue_stage * A_STAGE;
+        if (RAGGED && a_left == 1) {                    // a chunk of 8 k is inside K or beyond it
+            const int l = lane_here(), left = P.K - (nk - 2) * BK;
 #pragma unroll
-        for (int j = 0; j < A_COPIES; ++j) copy_to_lds(a_base, a_off[j], d + j * 1024);
+            for (int j = 0; j < A_COPIES; ++j) {
+                const int c = (l & 7) ^ swz_a((wave * A_COPIES + j) * 8 + (l >> 3));
+                copy_to_lds_lane(c * 8 < left ? a_base + a_off[j] : (const unsigned char*)&stream_zeros, d + j * 1024);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < A_COPIES; ++j) copy_to_lds(a_base, a_off[j], d + j * 1024);
+        }
         if (--a_left == 0) {
             a_left = nk / 2;
             a_base = na_base;
@@ -344,8 +365,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     };
     auto issue_b = [&]() __attribute__((always_inline)) {                              // next K-tile (NK: pair) of the weights
         const uint32_t d = lds_b_wave + b_issue_stage * (NK ? B_PAIR_STAGE : B_STAGE);
+        if (RAGGED && b_left <= 2) {
+            const int l = lane_here(), left = P.K - (nk - b_left) * BK;        // may be none
 #pragma unroll
-        for (int j = 0; j < B_COPIES; ++j) copy_to_lds_stream(b_base, b_off[j], d + j * 1024);
+            for (int j = 0; j < B_COPIES; ++j)
+                copy_to_lds_lane((wave * 2 + j) * 2 + (l >> 5) < left ? b_base + b_off[j] : (const unsigned char*)&stream_zeros, d + j * 1024);
+        } else {
+#pragma unroll
+            for (int j = 0; j < B_COPIES; ++j) copy_to_lds_stream(b_base, b_off[j], d + j * 1024);
+        }
         if (--b_left == 0) {
             b_left = b_requests;
             b_base = nb_base;
@@ -423,10 +451,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     // ---- epilogue of task `cur`: bias, activation, conversion, transposed store; then advance to the next task ----
     unsigned char* epi = smem + EPI_REGION + wave * EPI_BYTES_PER_WAVE;   // [32 rows][64 columns], 128 B pitch
     auto store_tile = [&]() __attribute__((always_inline)) {
-        // the lane number as the epilogue sees it: opaque to the compiler, so that the address arithmetic below
-        // is done here and not kept in registers across the main loop
-        int lane_e = lane;
-        asm volatile("" : "+v"(lane_e));
+        const int lane_e = lane_here();
         const int r16 = lane_e & 15, kq = lane_e >> 4;
         const int N = P.N;
         const int col_w = cur.n0 + wn * (TN * 16);      // first column of this wavefront
