@@ -194,7 +194,7 @@ void ffn_gemms(const moe_config* c, const Plan& p, void* ws, const void* xe, con
     const long long H = c->H, I = c->I;
     moe::GemmArgs g{};
     g.rows_dev = expert_demand; g.rows_fixed = 0; g.rows_cap = p.C;
-    g.groups = c->E; g.max_rows = p.C;
+    g.groups = c->E; g.max_rows = p.C; g.rows_likely = (long long)c->T * c->k;
     g.dtype = c->dtype; g.b_is_nk = false; g.c_f32 = false;
     // both tasks walk the same live (expert, row tile) units
     g.units = (int32_t*)ws_at(ws, p.off_units);
@@ -456,7 +456,7 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, slot_weight, demand, H, E, C, C_pad, b.row_step, dt, xe, ge, Wg, wgt, s));
     // grouped GEMMs over the experts' live rows
     moe::GemmArgs g{};
-    g.rows_dev = demand; g.rows_fixed = 0; g.rows_cap = C; g.groups = E; g.max_rows = C;
+    g.rows_dev = demand; g.rows_fixed = 0; g.rows_cap = C; g.groups = E; g.max_rows = C; g.rows_likely = (long long)T * k;
     g.dtype = dt; g.act = MOE_ACT_IDENTITY; g.a_rows_total = C_pad;
     const long long rH = (long long)C_pad * H, rI = (long long)C_pad * I, HI = (long long)H * I;
     // the pre-activation again: a = xe W1 + b1
@@ -560,6 +560,7 @@ moe_status moe_init(void) {
     hipError_t e = moe::prepare_gate_fused();
     if (e == hipSuccess) e = moe::prepare_grouped_gemm();
     if (e == hipSuccess) e = moe::prepare_grouped_gemm_stream();
+    if (e == hipSuccess) e = moe::prepare_gemm_narrow();
     if (e == hipSuccess) e = moe::prepare_layer_fused();
     if (e == hipSuccess) e = moe::prepare_gemm_f32();
     if (e == hipSuccess) e = moe::prepare_wgrad();

@@ -1,6 +1,6 @@
 // Grouped tile GEMM on CDNA4 matrix cores: the two FFN tasks of every expert
 // (C1 <- phi1(A B1 + D1), C2 <- C1 B2 + D2, Sec. 3.1 task abstraction) in 16-bit storage at
-// shapes that the weight-streaming kernel does not take, the gate projection of shapes that
+// shapes that neither the weight-streaming kernel nor the 128 x 128 tiles of gemm_narrow.hip take, the gate projection of shapes that
 // the fused gate does not take (in fp32 on the fp32 instruction, as there), and fp32 products whose
 // weights gemm_f32_body.h cannot address.  One workgroup computes one (group, row tile, column tile) task; tasks whose row tile lies beyond the group's live rows exit at
 // once, so only ceil(rows/BM) row tiles per expert are ever computed (the in-place
@@ -138,7 +138,9 @@ hipError_t prepare_grouped_gemm() {
 
 hipError_t launch_grouped_gemm(const GemmArgs& a, hipStream_t stream) {
     if (a.groups <= 0 || a.max_rows <= 0 || a.N <= 0) return hipSuccess;
-    if (stream_gemm_eligible(a)) return launch_grouped_gemm_stream(a, stream);
+    const bool streams = stream_gemm_eligible(a);
+    if (narrow_gemm_eligible(a) && (!streams || narrow_gemm_worth(a))) return launch_gemm_narrow(a, stream);
+    if (streams) return launch_grouped_gemm_stream(a, stream);
     if (a.a_is_km) return hipErrorInvalidValue;
     if (f32_stream_eligible(a)) return launch_gemm_f32_stream(a, stream);
     if (f32_gemm_eligible(a)) return launch_gemm_f32(a, stream);

@@ -56,8 +56,8 @@
 // 128-byte row segments.
 //
 // Requires K % 64 == 0, K >= 192 (kLayoutNK: 256) and N % 8 == 0.  kLayoutRagged takes every K % 8 == 0 above 128: the last
-// pair of K-tiles is filled up with zeros, in both operands, so that an infinity beyond K cannot meet them.  Other shapes use the
-// generic kernel.
+// pair of K-tiles is filled up with zeros, in both operands, so that an infinity beyond K cannot meet them.  Other shapes, and launches
+// with few tasks, use the 128 x 128 tiles of gemm_narrow.hip.
 #pragma once
 #include "common.h"
 #include "kernels.h"

@@ -29,6 +29,8 @@ struct GemmArgs {
     // share (units is then the list written by launch_f32_units)
     float* partials;
     int groups; int max_rows;                               // grid extent in rows
+    long long rows_likely;                                  // live rows of all groups together, where the caller knows about how many there
+                                                            // can be (0: groups * max_rows); only the choice of a kernel looks at it
     int N; int K;
     int act;                                                // moe_act, applied after the bias
     int dtype;                                              // storage of A, B (and of C, bias unless c_f32)
@@ -67,6 +69,12 @@ hipError_t launch_grouped_gemm_stream(const GemmArgs& a, hipStream_t stream);
 size_t ffn_units_ints(int groups, int max_rows);
 hipError_t launch_ffn_units(const int32_t* rows_dev, int rows_cap, int groups, int max_rows, int32_t* units,
                             hipStream_t stream);
+// 16-bit products in 128 x 128 tiles, for launches with few tasks and for narrow layers; reads the same scratch block
+bool narrow_gemm_eligible(const GemmArgs& a);
+// are they the faster ones where the streaming kernel takes the product too?
+bool narrow_gemm_worth(const GemmArgs& a);
+hipError_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream);
+hipError_t prepare_gemm_narrow();
 // Both FFN GEMMs in one persistent launch: a unit's second-GEMM tasks start when all its first-GEMM tiles are
 // stored (g2.A is g1.C).  Eligible when both GEMMs are and they share rows, groups and units.
 // never_met: the dependency waits get a target no counter reaches and a poll limit of 16, so that every
