@@ -381,7 +381,8 @@ moe_status make_bwd_plan(const moe_config* c, BwdPlan* b) {
     const size_t rows = E * (size_t)p.C_pad;
     b->ldL = (int)align_up(E, 8);
     // dWg has only (H / 128) x (E / 128) output tiles for a contraction over all T tokens: the tokens are cut into up to
-    // 16 slices of at least 1024, each slice one "group" of the grouped GEMM, and the partial products added in slice order
+    // 16 slices, each slice one "group" of the grouped GEMM, and the partial products added in slice order.  Slices of at least 1024 have
+    // room of their own; those of fewer tokens see below
     b->wg_slices = (int)(T / 1024 < 1 ? 1 : (T / 1024 > 16 ? 16 : T / 1024));
     b->wg_slice_k = (int)align_up((T + b->wg_slices - 1) / b->wg_slices, 64);
     b->T_pad = b->wg_slices * b->wg_slice_k;             // >= T: x^T rows and dL are zero beyond T
@@ -428,6 +429,21 @@ moe_status make_bwd_plan(const moe_config* c, BwdPlan* b) {
             b->off_wunits1 = take(moe::ffn_units_ints(c->E, c->H) * 4);
             b->off_wunits2 = take(moe::ffn_units_ints(c->E, c->I) * 4);
         }
+    }
+    // Slices of at least 256 tokens, as many as make no more rows of x^T and dL and as the partial products have room for behind dxe
+    // and the partial sums of dW1 and dW2 there: those of 1024 were 16 tiles each for 256 CUs in fp32 (T = 2048, H = 1024, E = 16:
+    // 35.2 us, 13.8 in eight slices of 256), and in 16-bit storage the longest sums of the launch in small layers (whole call, T = 1024, H
+    // = I = 256, E = 4 73.6 -> 60.9 us; T = 2048, H = 512, I = 1024, E = 8 126 -> 114; T = 8192, H = I = 2048, E = 32 1010 -> 1002).
+    const size_t room_at = b->off_xeT + (b->w_slices > 1 ? 2 * (size_t)b->w_slices * E * H * I * 4 : 0);
+    const size_t room_end = b->off_dxe + (c->dtype == MOE_F32 ? 2 * x_bytes + h_bytes : std::max(rows * I * 4, 2 * x_bytes + h_bytes));
+    for (int n = (int)std::min<size_t>(16, T / 256); n > b->wg_slices; --n) {
+        const size_t slice = align_up((T + n - 1) / n, 64);
+        if (n * slice > (size_t)b->T_pad || (n - 1) * slice >= T || room_at + (size_t)n * H * E * 4 > room_end) continue;
+        b->wg_slices = n;
+        b->wg_slice_k = (int)slice;
+        b->T_pad = (int)(n * slice);
+        b->off_wg_part = room_at;
+        break;
     }
     b->total = off;
     return MOE_OK;
