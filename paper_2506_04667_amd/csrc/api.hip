@@ -520,7 +520,7 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
         MOE_TRY(moe::launch_wgrad(w, dt, s));
     } else {
         auto weight_grad = [&](const void* rows, int M, void* rowsT, const void* grad, int N, float* out) {
-            if (hipError_t e = moe::launch_bwd_transpose(rows, rowsT, E, C_pad, M, C_pad, dt, s); e != hipSuccess) return e;
+            if (hipError_t e = moe::launch_bwd_transpose((const float*)rows, (float*)rowsT, E, C_pad, M, C_pad, demand, C, s); e != hipSuccess) return e;
             moe::GemmArgs w{};
             w.groups = E; w.dtype = dt; w.act = MOE_ACT_IDENTITY; w.c_f32 = true; w.K = C_pad; w.k_dev = demand; w.k_cap = C;
             w.A = rowsT; w.lda = C_pad; w.a_group_stride = (long long)C_pad * M; w.a_rows_total = M;
@@ -532,7 +532,7 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
         void *hT = ws_at(ws, b.off_hT), *xeT = ws_at(ws, b.off_xeT), *xT = ws_at(ws, b.off_xT);
         MOE_TRY(weight_grad(h, I, hT, ge, H, dW2));
         MOE_TRY(weight_grad(xe, H, xeT, da, I, dW1));
-        MOE_TRY(moe::launch_bwd_transpose(x, xT, 1, T, H, b.T_pad, dt, s));
+        MOE_TRY(moe::launch_bwd_transpose((const float*)x, (float*)xT, 1, T, H, b.T_pad, nullptr, 0, s));
         moe::GemmArgs wg{};
         wg.groups = b.wg_slices; wg.dtype = dt; wg.act = MOE_ACT_IDENTITY; wg.c_f32 = true;
         wg.A = xT; wg.lda = b.T_pad; wg.a_rows_total = H; wg.rows_fixed = H; wg.rows_cap = H; wg.max_rows = H;

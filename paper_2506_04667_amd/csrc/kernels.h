@@ -188,8 +188,10 @@ hipError_t launch_bwd_act(const void* a, const float* dh, const void* ge, const 
 // selected gate logits (k <= 64) from p
 hipError_t launch_bwd_gate(const float* p, const int32_t* topk_expert, const float* topk_weight, const int32_t* slot, int T, int T_pad,
                            int k, int E, int C, int C_pad, int ld, int dtype, float* dl, void* dL, hipStream_t s);
-// out[g][c][r] = in[g][r][c], r < R, c < Cc; rows of out have ld_out entries, zero at and beyond R
-hipError_t launch_bwd_transpose(const void* in, void* out, int groups, int R, int Cc, int ld_out, int dtype, hipStream_t s);
+// fp32: out[g][c][r] = in[g][r][c], r < R, c < Cc; rows of out have ld_out entries, zero at and beyond R.  With expert_demand only r up
+// to the end of the 32-row step that holds group g's last live row
+hipError_t launch_bwd_transpose(const float* in, float* out, int groups, int R, int Cc, int ld_out, const int32_t* expert_demand, int C,
+                                hipStream_t s);
 // The rest of the backward pass once the products are made.  db2[e, c] = sum over live rows of slot_weight[e, r] ge[e, r, c] and db1
 // likewise of da alone; dgate_bias[e] = sum of dl over the pairs that selected e; dx[t, :] = sum of the kept choices' rows of dxe + sum
 // over choices of dl WgT[expert, :]; and for sums made in slices (slices > 1) out[i] = sum over g of part[g * n + i], g ascending
