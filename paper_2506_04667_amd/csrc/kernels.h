@@ -157,8 +157,8 @@ hipError_t layer_stage_ms(double* ms, int n, hipStream_t stream);
 
 // Weight gradients in 16-bit storage (wgrad.hip), all of them in one launch: C[part][m][n] = sum over k of A[g][k][m] B[g][k][n]
 // in fp32, part = slice * groups + g; the k of group g, 0 .. min(rows_dev[g], rows_cap) - 1 (rows_dev == nullptr: rows_cap), are
-// cut into `slices` about equal runs of K-tiles of 32.  B is zero from its last k to the next multiple of 32, and A finite or
-// zero there, its rows at or beyond a_rows taken as row a_rows - 1.  lda >= M and ldb >= N are multiples of 8.
+// cut into `slices` about equal runs of K-tiles of 32.  B is zero from its last k to the next multiple of 32, and so is A, whose
+// rows at or beyond a_rows are taken as zeros.  lda >= M and ldb >= N are multiples of 8.
 constexpr int kWgradProblems = 3;
 struct WgradProblem {
     const void* A; long long a_group_stride; int lda; int a_rows;

@@ -72,8 +72,8 @@ __global__ __launch_bounds__(W_THREADS, 2) void wgrad_kernel(WgradArgs a) {
         const unsigned char* const a_base = uniform((const unsigned char*)P.A + (size_t)grp * P.a_group_stride * 2);
         const unsigned char* const b_base = uniform((const unsigned char*)P.B + (size_t)grp * P.b_group_stride * 2);
         const uint32_t lds_base = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
-        // a copy of A is 4 k-rows of 16 chunks, one of B 2 k-rows of 32; columns beyond the last repeat it, and rows of A beyond
-        // a_rows (their B is zero) do too
+        // a copy of A is 4 k-rows of 16 chunks, one of B 2 k-rows of 32; columns beyond the last repeat it; rows of A beyond a_rows are
+        // zeros, as their B is (a row of A in their place could hold an infinity)
         const int ra = lane >> 4, rb = lane >> 5;
         uint32_t a_col[2], b_col[4];
 #pragma unroll
@@ -88,9 +88,10 @@ __global__ __launch_bounds__(W_THREADS, 2) void wgrad_kernel(WgradArgs a) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int k = k0 + (wave * 2 + j) * 4;
-                const int kb = min(k, a_rows - 1);
-                const uint32_t off = k + 4 <= a_rows ? a_lane : (uint32_t)(min(k + ra, a_rows - 1) - kb) * (uint32_t)lda2;
-                copy_to_lds(a_base + (size_t)kb * lda2, off + a_col[j], d + (wave * 2 + j) * 1024);
+                const unsigned char* const row = a_base + (size_t)k * lda2;
+                const uint32_t off = a_lane + a_col[j], to = d + (wave * 2 + j) * 1024;
+                if (k + 4 <= a_rows) copy_to_lds(row, off, to);
+                else copy_to_lds_lane(k + ra < a_rows ? row + off : (const unsigned char*)&stream_zeros, to);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)

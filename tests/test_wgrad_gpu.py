@@ -65,3 +65,30 @@ def test_weight_gradients(T, H, I, E, k, C, dtype):
     for e in range(E):
         if used[e] == 0:
             assert float(grads["dW1"][e].abs().max()) == 0.0 and float(grads["dW2"][e].abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_infinity_in_the_last_token_enters_the_gate_gradient_once(dtype):
+    # 33 tokens: the sum over the tokens ends one k into a K-tile of 32, and the last token's x is infinite.  Its activations are all
+    # below zero or -inf, so that after ReLU its logit gradients come from b2 alone and are finite: dWg is infinite where it chose
+    # an expert, NaN (infinity times no gradient) elsewhere, and untouched in the other rows
+    T, H, I, E, k = 33, 8, 8, 4, 2
+    td = moe.TORCH_DTYPE[dtype]
+    g = torch.Generator().manual_seed(3)
+    n = lambda *s: torch.randn(*s, generator=g).to(td)
+    x, Wg, W1, W2, dout, b2 = n(T, H), n(H, E), -n(E, H, I).abs(), n(E, I, H), n(T, H), n(E, H)
+    x[T - 1] = 1.0
+    x[T - 1, 0] = float("inf")
+    order = torch.stack([torch.arange(T) % E, (torch.arange(T) + 1) % E], 1).int()
+    w = torch.full((T, k), 0.5)
+    out = [torch.full(s, 7.0, device="cuda") for s in ((T, H), (H, E), (E,), (E, H, I), (E, I), (E, I, H), (E, H))]
+    cfg = moe.make_config(T, H, I, E, k, 4.0, "relu", dtype)
+    ws = torch.full((moe.moe_backward_workspace_bytes(cfg),), 0xff, dtype=torch.uint8, device="cuda")
+    c = lambda t: t.cuda()
+    moe.moe_backward(cfg, ws, c(x), c(Wg), c(W1), None, c(W2), c(b2), c(order), c(w), c(dout), *out)
+    dWg = out[1].cpu()
+    assert order[T - 1].tolist() == [0, 1]
+    p = [float(dout[T - 1].double() @ b2[e].double()) for e in (0, 1)]
+    sign = 1.0 if p[0] > p[1] else -1.0                # of dl of the first choice; the second's is the opposite
+    assert float(dWg[0, 0]) == sign * float("inf") and float(dWg[0, 1]) == -sign * float("inf"), dWg[0]
+    assert bool(torch.isnan(dWg[0, 2:]).all()) and bool(torch.isfinite(dWg[1:]).all())
