@@ -113,10 +113,12 @@ __device__ __forceinline__ float gelu_erf_poly(float v) {
     const float hv = 0.5f * v;
     return fmaf(hv, vc * p, hv);
 }
-// phi_1 where the result goes to bf16/fp16 storage
+// phi_1 where the result goes to bf16/fp16 storage; kActGeluErf: the erf form by 7.1.26, as in fp32
+constexpr int kActGeluErf = 5;
 template <int ACT>
 __device__ __forceinline__ float apply_act16_t(float v) {
     if constexpr (ACT == 2) return gelu_erf_poly(v);
+    else if constexpr (ACT == kActGeluErf) return apply_act_t<2>(v);
     else return apply_act_t<ACT>(v);
 }
 __device__ __forceinline__ float apply_act(float v, int act) {

@@ -75,7 +75,7 @@ hipError_t launch_stream_act(const GemmArgs& g1, const GemmArgs* g2, bool never_
             switch (g1.act) {
                 case 0: return launch_stream_t<S, 0, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
                 case 1: return launch_stream_t<S, 1, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
-                case 2: return launch_stream_t<S, 2, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
+                case 2: return launch_stream_t<S, kActGeluErf, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
                 default: return launch_stream_t<S, 3, 1, kLayoutRagged>(g1, nullptr, never_met, stream);
             }
         }
@@ -100,7 +100,7 @@ hipError_t prepare_stream_s() {
     if (e == hipSuccess) e = prepare_stream_t<S, 3, 1, kLayoutNK>();
     if (e == hipSuccess) e = prepare_stream_t<S, 0, 1, kLayoutRagged>();
     if (e == hipSuccess) e = prepare_stream_t<S, 1, 1, kLayoutRagged>();
-    if (e == hipSuccess) e = prepare_stream_t<S, 2, 1, kLayoutRagged>();
+    if (e == hipSuccess) e = prepare_stream_t<S, kActGeluErf, 1, kLayoutRagged>();
     if (e == hipSuccess) e = prepare_stream_t<S, 3, 1, kLayoutRagged>();
     if (e == hipSuccess) e = prepare_stream_t<S, 0, 2>();
     if (e == hipSuccess) e = prepare_stream_t<S, 1, 2>();
