@@ -150,10 +150,9 @@ bool stream_gemm_shape_ok(int dtype, int N, int K, int lda, int ldb, int ldc, lo
 
 bool stream_gemm_eligible(const GemmArgs& a) {
     // the epilogues that the backward pass's forms need: fp32 output (weight gradients, <phi(a), dh>) and [n][k] weights take the
-    // identity, [k][m] activations fp32 output from packed rows whose count is a multiple of 8
-    if ((a.c_f32 || a.b_is_nk) && a.act != 3) return false;
+    // identity without a bias, [k][m] activations fp32 output from packed rows whose count is a multiple of 8
+    if ((a.c_f32 || a.b_is_nk) && (a.act != 3 || a.bias)) return false;
     if (a.c_f32 && !a.a_is_km && !a.b_is_nk) return false;
-    if (a.b_is_nk && a.bias) return false;
     if (a.a_is_km && (!a.c_f32 || a.b_is_nk || a.a_row_index || a.rows_cap % 8 != 0)) return false;
     if (a.rows_dev == nullptr || a.units == nullptr) return false;
     // forward layouts whose K is no multiple of 64: as if K were filled up to the next one

@@ -166,7 +166,7 @@ constexpr int kSpinLimit = 1 << 21;
 constexpr int kLayoutNK = 1, kLayoutKM = 2, kLayoutRagged = 4;
 constexpr int B_PAIR_STAGE = BN * 128, B_PAIR_STAGES = 3;               // kLayoutNK: 256 n x 64 k
 static_assert(B_REGION + B_PAIR_STAGES * B_PAIR_STAGE <= LDS_BYTES, "three pairs of [n][k] weights");
-constexpr int kActF32Out = 4;                           // template value of ACT: identity with C (and bias) in fp32
+constexpr int kActF32Out = 4;                           // template value of ACT: identity, no bias, C in fp32
 
 // The work of one workgroup on one list for one GEMM (phase PH of the arguments, activation ACT): `list` =
 // { fault word, number of live units, ids[cap], completion counters[cap] }; the workgroup is number wg_local of
@@ -457,7 +457,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         const int col_w = cur.n0 + wn * (TN * 16);      // first column of this wavefront
         const size_t c_base = (size_t)cur.grp * P.c_group_stride;
         if constexpr (ACT == kActF32Out) {
-            // fp32 output (and fp32 bias), no activation: a lane's four sums of a tile are four consecutive columns of one
+            // fp32 output, no bias, no activation: a lane's four sums of a tile are four consecutive columns of one
             // row, a tile's row half a line.  Lanes 8 rows apart swap halves of two neighbouring tiles, so that a store
             // writes whole lines of 8 rows, and the non-temporal hint keeps them from pushing the operands out of L2.
             // The weight gradients write 4 GiB at T = 16384, H = I = 2048, E = 128; whole backward pass there: 2.59 ms with
@@ -469,14 +469,6 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 #pragma unroll
                 for (int tn = 0; tn < TN; tn += 2) {
                     f32x4 v[2] = {acc[tm][tn], acc[tm][tn + 1]};
-                    if (P.bias) {
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            const int c = min(col_w + (tn + j) * 16 + kq * 4, N - 4);
-                            const f32x4 bv = *(const f32x4*)((const float*)P.bias + (size_t)cur.grp * P.bias_group_stride + c);
-                            v[j][0] += bv[0]; v[j][1] += bv[1]; v[j][2] += bv[2]; v[j][3] += bv[3];
-                        }
-                    }
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
                         const float got = swap_8_lanes(low ? v[1][b] : v[0][b]);
