@@ -337,7 +337,7 @@ struct BwdPlan {
     int wg_slices, wg_slice_k;                           // dWg = x^T dL as wg_slices partial products over wg_slice_k tokens each
     size_t off_wg_part;
     size_t off_counts, off_units, off_slot_token, off_slot_weight, off_slot, off_demand, off_dl, off_dL, off_wgt, off_xe,
-        off_ge, off_a, off_h, off_dh, off_da, off_dxe, off_row_p, off_hT, off_xeT, off_xT, off_wrows, off_wunits1, off_wunits2, total;
+        off_ge, off_a, off_h, off_dh, off_da, off_dxe, off_row_p, off_sums, off_xT, off_wrows, off_wunits1, off_wunits2, total;
     bool w_stream;                                       // 16-bit storage: dW1 and dW2 on the weight-streaming kernel
     int row_step;                                        // the experts' rows are zero from the last live one to the next multiple of this
     int w_slices;                                        // 16-bit storage: slices of the weight gradients' sums over an expert's slots
@@ -403,47 +403,50 @@ moe_status make_bwd_plan(const moe_config* c, BwdPlan* b) {
     b->off_a = b->off_h = take(rows * I * el);           // the activation kernel writes h where it reads a
     b->off_row_p = take(rows * 4);
     const size_t h_bytes = align_up(rows * I * el, kAlign), x_bytes = align_up(rows * H * el, kAlign);
+    // dxe, and behind it h^T and xe^T (fp32) or partial sums.  In 16-bit storage dh lies there before, which is read for the last time
+    // when dxe begins, and the partial sums may take what makes this four buffers of H and four of I values per slot row with xe,
+    // ge, h and da (more where dh needs more)
+    const size_t most = c->dtype == MOE_F32 ? 2 * x_bytes + h_bytes : std::max(rows * I * 4, 2 * x_bytes + h_bytes);
     if (c->dtype == MOE_F32) {
         b->off_dh = b->off_da = take(rows * I * 4);      // and da in the place of dh, in fp32
-        b->off_dxe = take(2 * x_bytes + h_bytes);
+        b->off_xT = take(H * (size_t)b->T_pad * el);
     } else {
         b->off_da = take(rows * I * el);
-        // dh is read for the last time when dxe and the transposed copies begin
-        b->off_dh = b->off_dxe = take(std::max(rows * I * 4, 2 * x_bytes + h_bytes));
     }
-    b->off_xeT = b->off_dxe + x_bytes;
-    b->off_hT = b->off_xeT + x_bytes;
+    b->off_dxe = off;
+    if (c->dtype != MOE_F32) b->off_dh = b->off_dxe;
+    b->off_sums = b->off_dxe + x_bytes;
     b->w_slices = 1;
     b->w_stream = wgrad_streams(c, p);
     b->row_step = b->w_stream ? p.C_pad : 32;
-    if (c->dtype == MOE_F32) {
-        b->off_xT = take(H * (size_t)b->T_pad * el);
-    } else {
+    if (c->dtype != MOE_F32 && !b->w_stream) {
         // dW1 and dW2 have few output tiles where there are few experts or narrow layers: then an expert's slots are cut into
         // slices of at least 256, as many as give two workgroups per CU and as the partial sums have room for behind dxe
         const long long tiles = moe::wgrad_tiles(c->E, c->I, c->H) + moe::wgrad_tiles(c->E, c->H, c->I);
-        const long long room = (long long)((off - b->off_xeT) / (2 * E * H * I * 4));
-        if (!b->w_stream) b->w_slices = (int)std::max(1ll, std::min({kWgradWorkgroups / tiles, (long long)p.C_pad / 256, room}));
-        if (b->w_stream) {
-            b->off_wrows = take(2 * E * 4);
-            b->off_wunits1 = take(moe::ffn_units_ints(c->E, c->H) * 4);
-            b->off_wunits2 = take(moe::ffn_units_ints(c->E, c->I) * 4);
-        }
+        const long long room = (long long)((align_up(most, kAlign) - x_bytes) / (2 * E * H * I * 4));
+        b->w_slices = (int)std::max(1ll, std::min({kWgradWorkgroups / tiles, (long long)p.C_pad / 256, room}));
     }
     // Slices of at least 256 tokens, as many as make no more rows of x^T and dL and as the partial products have room for behind dxe
     // and the partial sums of dW1 and dW2 there: those of 1024 were 16 tiles each for 256 CUs in fp32 (T = 2048, H = 1024, E = 16:
     // 35.2 us, 13.8 in eight slices of 256), and in 16-bit storage the longest sums of the launch in small layers (whole call, T = 1024, H
     // = I = 256, E = 4 73.6 -> 60.9 us; T = 2048, H = 512, I = 1024, E = 8 126 -> 114; T = 8192, H = I = 2048, E = 32 1010 -> 1002).
-    const size_t room_at = b->off_xeT + (b->w_slices > 1 ? 2 * (size_t)b->w_slices * E * H * I * 4 : 0);
-    const size_t room_end = b->off_dxe + (c->dtype == MOE_F32 ? 2 * x_bytes + h_bytes : std::max(rows * I * 4, 2 * x_bytes + h_bytes));
+    const size_t w_sums = b->w_slices > 1 ? 2 * (size_t)b->w_slices * E * H * I * 4 : 0;
+    size_t live = c->dtype == MOE_F32 ? most : std::max(rows * I * 4, x_bytes + w_sums);      // bytes from dxe on
     for (int n = (int)std::min<size_t>(16, T / 256); n > b->wg_slices; --n) {
-        const size_t slice = align_up((T + n - 1) / n, 64);
-        if (n * slice > (size_t)b->T_pad || (n - 1) * slice >= T || room_at + (size_t)n * H * E * 4 > room_end) continue;
+        const size_t slice = align_up((T + n - 1) / n, 64), end = x_bytes + w_sums + (size_t)n * H * E * 4;
+        if (n * slice > (size_t)b->T_pad || (n - 1) * slice >= T || end > most) continue;
         b->wg_slices = n;
         b->wg_slice_k = (int)slice;
         b->T_pad = (int)(n * slice);
-        b->off_wg_part = room_at;
+        b->off_wg_part = b->off_sums + w_sums;
+        live = std::max(live, end);
         break;
+    }
+    take(live);
+    if (b->w_stream) {
+        b->off_wrows = take(2 * E * 4);
+        b->off_wunits1 = take(moe::ffn_units_ints(c->E, c->H) * 4);
+        b->off_wunits2 = take(moe::ffn_units_ints(c->E, c->I) * 4);
     }
     b->total = off;
     return MOE_OK;
@@ -498,7 +501,7 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
     if (dt != MOE_F32) {
         float *dW1_out = dW1, *dW2_out = dW2;
         if (b.w_slices > 1) {
-            dW1_out = (float*)ws_at(ws, b.off_xeT);
+            dW1_out = (float*)ws_at(ws, b.off_sums);
             dW2_out = dW1_out + (size_t)b.w_slices * E * HI;
             finish.sum[0] = {dW1_out, b.w_slices, E * HI, dW1};
             finish.sum[1] = {dW2_out, b.w_slices, E * HI, dW2};
@@ -529,7 +532,8 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
             w.C = out; w.c_group_stride = HI; w.ldc = N; w.N = N; w.k_span = c->act == MOE_ACT_RELU ? kReluGradSpan : 0;
             return moe::launch_grouped_gemm(w, s);
         };
-        void *hT = ws_at(ws, b.off_hT), *xeT = ws_at(ws, b.off_xeT), *xT = ws_at(ws, b.off_xT);
+        void *xeT = ws_at(ws, b.off_sums), *xT = ws_at(ws, b.off_xT);
+        void* hT = (char*)xeT + align_up((size_t)E * rH * 4, kAlign);
         MOE_TRY(weight_grad(h, I, hT, ge, H, dW2));
         MOE_TRY(weight_grad(xe, H, xeT, da, I, dW1));
         MOE_TRY(moe::launch_bwd_transpose((const float*)x, (float*)xT, 1, T, H, b.T_pad, nullptr, 0, s));
