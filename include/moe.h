@@ -218,7 +218,8 @@ moe_status moe_probe_lds_fill(int32_t mode, const void* src, size_t region_bytes
 
 /* Gate ("FusedGate", Alg. 1): gate_logits = x Wg (+ gate_bias) with fp32
  * accumulation, then top-k and combine weights as in moe_route.  gate_logits is
- * required here. */
+ * required here.  Overwrites parts of the workspace, also those where other calls
+ * keep h and y: a call that overlaps one of those needs a workspace of its own. */
 moe_status moe_gate(const moe_config* cfg, void* workspace, size_t workspace_bytes,
                     const void* x, const void* Wg, const float* gate_bias,
                     float* gate_logits, int32_t* topk_expert, float* topk_weight, void* stream);

@@ -309,7 +309,7 @@ moe_status forward_impl(const moe_config* cfg, void* workspace, size_t workspace
     if (!mark(1)) return MOE_ERR_HIP;
     // Dispatch builds the routing table only; the first FFN GEMM gathers its rows from x through
     // slot_token, so the packed copy xe is never materialised on this path.
-    // the scatter launch also lists the live FFN units
+    // the routing launch also lists the live FFN units
     st = run_dispatch(cfg, p, (int32_t*)ws_at(workspace, p.off_counts), (int32_t*)ws_at(workspace, p.off_units), x, topk_expert,
                       topk_weight, slot, expert_demand, slot_token, slot_weight, nullptr, counts_ready, s);
     if (st != MOE_OK) return st;

@@ -1,6 +1,6 @@
 // Device-side construction of the lists of live (group, row tile) units that the weight-streaming FFN
-// kernels walk, shared by the stand-alone launcher and by the routing scatter launch (which appends it as
-// one more workgroup so that the whole layer needs no separate launch for it).
+// kernels walk, shared by the stand-alone launcher and by the routing launch (where one of the workgroups
+// that add up all counts makes them, so that the whole layer needs no separate launch for it).
 #pragma once
 #include "common.h"
 
@@ -9,7 +9,7 @@ namespace moe {
 // Row tiles of the streaming FFN kernels.  A group's live rows are cut into large tiles; what remains beyond
 // its full large tiles becomes one more large tile if it exceeds the small tile, else one small tile (half the
 // matrix-core work and half the activation copies for the same weight bytes).  Each tile size has its own
-// list and its own launch.
+// list.
 constexpr int kUnitRowsLarge = 256, kUnitRowsSmall = 128;
 
 // Scratch block: two lists of the same format, the large tiles' first, then kXcds placement words.

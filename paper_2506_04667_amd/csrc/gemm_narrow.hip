@@ -281,9 +281,11 @@ bool narrow_gemm_eligible(const GemmArgs& a) {
 // I = 840 48 / 28; E = 4 of 64, H = I = 512 44 / 23; E = 16 of 64 and 128, H = I = 2048 70 / 62 and 76 / 72; E = 32 of 8 and 128, H = I =
 // 1024 44 / 40 and 48 / 44.  With somewhat more a few CUs have two and the rest wait for them, with many the operands' way from L2
 // decides: E = 24 of 128, H = I = 1536 (288 tiles) 71 / 103; E = 64 of 128, H = I = 1024 (512) 73 / 81; E = 16 of 512, H = I = 2048 127 /
-// 232.  Few rows have next to no activations to bring in, and finer tasks even out the last round of the weights' stream: E = 128, one
-// row in 80 of them, H = I = 2048 240 / 208, in all of them 335 / 318; E = 96 of 8, H = I = 1024 90 / 74; 16 rows, E = 128 344 /
-// 352.  [n][k] weights in half lines do not gain from that.
+// 232.  Few rows have next to no activations to bring in, and finer tasks even out the last round of the weights' stream.  Whole forward
+// calls timed in turn, capacities of 1 to 8 rows, top-2: H = I = 1024, E = 96, T = 384 101 / 94, T = 48 69.8 / 67.3; H = I = 1536, E = 64, T =
+// 256 136 / 127; H = I = 2880, E = 48, T = 100 312 / 298; H = 4096, I = 1536, E = 64, T = 64 274 / 264; H = I = 2048, E = 128, T = 64
+// 253 / 248 on one card and 259 / 259 on another, T = 512 355 / 355, T = 16 106.4 / 107.2; top-8, H = 7168, I = 2048, E = 32, T = 32
+// 341 / 343.  16 rows, E = 128 (both GEMMs) 344 / 352.  [n][k] weights in half lines do not gain from that.
 bool narrow_gemm_worth(const GemmArgs& a) {
     const long long all = (long long)a.groups * ((a.max_rows + R_BM - 1) / R_BM), ncol = (a.N + R_BN - 1) / R_BN, cus = device_cu_count();
     const long long likely = a.rows_likely > 0 ? std::min(all, a.groups + a.rows_likely / R_BM) : all;

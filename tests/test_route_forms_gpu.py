@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
     (129, 40, 40, 17),                               # 40 steps of 64 pairs per chunk, 16 wavefronts at a time
     (65, 1024, 8, 3), (65, 1025, 8, 3),              # most experts of one launch; scan launch
     (65536, 8, 1, 0), (65537, 8, 1, 9000),           # most chunks of one launch; scan launch
-    (3000, 6, 3, 1200), (200, 2500, 5, 1),           # experts not a multiple of 4; two wavefronts' counts
+    (3000, 6, 3, 1200), (200, 2500, 5, 1),           # experts not a multiple of 4; room for three wavefronts' counts
 ])
 def test_slots_where_the_form_changes(oracle, T, E, k, C, policy):
     cfg = moe.make_config(T, 8, 8, E, k, 1.0, "relu", "f32", capacity_override=C, drop_policy=policy)
