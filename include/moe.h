@@ -351,6 +351,17 @@ enum { MOE_F32_BODY_SPANS = 0,        /* the equal-share kernel: 256 x 256 tiles
        MOE_F32_BODY_64X256 = 1, MOE_F32_BODY_64 = 64, MOE_F32_BODY_128 = 128, MOE_F32_BODY_256 = 256 };
 int32_t moe_f32_gemm_body(int32_t groups, int32_t max_rows, int32_t N, int32_t K, int32_t listed, int32_t cus);
 
+/* Host arithmetic only: which kernel makes a product of a 16-bit layer of this configuration on a GPU with `cus` CUs (the
+ * functions that the launches use): the two FFN tasks of the forward calls (the first one also of moe_backward), the two
+ * data gradients dh = dout W2^T and dxe = da W1^T, and the weight gradients dW1 and dW2 together.  One of the numbers
+ * below, or -1 for fp32 storage, invalid configurations and other values of `product`.  For tests. */
+enum { MOE_PRODUCT_FFN1 = 0, MOE_PRODUCT_FFN2 = 1, MOE_PRODUCT_DH = 2, MOE_PRODUCT_DXE = 3, MOE_PRODUCT_DW = 4 };
+enum { MOE_KERNEL16_GENERIC = 0,      /* tiles of any shape */
+       MOE_KERNEL16_128 = 1,          /* 128 x 128 tiles, a workgroup each */
+       MOE_KERNEL16_STREAM = 2,       /* the persistent weight-streaming kernel */
+       MOE_KERNEL16_WGRAD = 3 };      /* all weight gradients in one launch */
+int32_t moe_gemm16_kernel(const moe_config* cfg, int32_t product, int32_t cus);
+
 /* Outcome of the single-launch FFN of the last moe_forward / moe_expert_ffn enqueued on `stream` with this
  * configuration and workspace (Alg. 2's dependency between t1 and t2 tiles, resolved by bounded waits).
  * Unlike every other call this one SYNCHRONISES: it copies the two fault words of the workspace to the host

@@ -19,7 +19,8 @@ TORCH_DTYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float1
 EXPORTS = ["moe_status_string", "moe_init", "moe_row_tile", "moe_capacity", "moe_workspace_bytes", "moe_forward",
            "moe_gate", "moe_route", "moe_dispatch", "moe_expert_ffn", "moe_combine", "moe_ffn_status", "moe_ffn_schedule",
            "moe_forward_timed", "moe_probe_stream", "moe_probe_mfma", "moe_dispatch_noalloc",
-           "moe_backward_workspace_bytes", "moe_backward", "moe_layer_stage_ms", "moe_f32_ffn_schedule", "moe_probe_lds_fill", "moe_f32_gemm_body"]
+           "moe_backward_workspace_bytes", "moe_backward", "moe_layer_stage_ms", "moe_f32_ffn_schedule", "moe_probe_lds_fill", "moe_f32_gemm_body",
+           "moe_gemm16_kernel"]
 LAYER_STAGES = ("gate", "barrier1", "clear_scan", "barrier2", "scatter_units", "barrier3", "ffn_gemm1", "ffn_gemm2", "barrier4",
                 "combine")
 STATIC_SCRATCH_BYTES = 4 << 20
@@ -68,6 +69,8 @@ def load(path=None):
     i64p = ctypes.POINTER(ctypes.c_int64)
     lib.moe_f32_gemm_body.restype = ctypes.c_int32
     lib.moe_f32_gemm_body.argtypes = [ctypes.c_int32] * 6
+    lib.moe_gemm16_kernel.restype = ctypes.c_int32
+    lib.moe_gemm16_kernel.argtypes = [cfgp, ctypes.c_int32, ctypes.c_int32]
     lib.moe_f32_ffn_schedule.restype = ctypes.c_int32
     lib.moe_f32_ffn_schedule.argtypes = [i32p] + [ctypes.c_int32] * 5 + [i64p, i64p, i32p, i32p, ctypes.c_int32]
     lib.moe_layer_stage_ms.restype = ctypes.c_int
@@ -195,6 +198,18 @@ def moe_f32_gemm_body(groups, max_rows, N, K, listed=False, cus=256):
     if body < 0:
         raise MoeError(-1, "moe_f32_gemm_body")
     return body
+
+
+PRODUCTS = ("ffn1", "ffn2", "dh", "dxe", "dw")
+KERNELS16 = ("generic", "128", "stream", "wgrad")
+
+
+def moe_gemm16_kernel(cfg, product, cus=256):
+    """The kernel (one of KERNELS16) that makes this product (one of PRODUCTS) of a 16-bit layer."""
+    kernel = load().moe_gemm16_kernel(ctypes.byref(cfg), PRODUCTS.index(product), cus)
+    if kernel < 0:
+        raise MoeError(-1, "moe_gemm16_kernel")
+    return KERNELS16[kernel]
 
 
 def moe_layer_stage_ms(stream=None):

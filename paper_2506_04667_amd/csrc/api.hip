@@ -18,6 +18,8 @@
 constexpr size_t kStaticScratchBytes = 4u << 20;
 static_assert(MOE_F32_BODY_64X256 == moe::kF32Body64x256 && MOE_F32_BODY_64 == moe::kF32Body64 && MOE_F32_BODY_128 == moe::kF32Body128 &&
                   MOE_F32_BODY_256 == moe::kF32Body256, "the header's numbers");
+static_assert(MOE_KERNEL16_GENERIC == moe::kGemm16Generic && MOE_KERNEL16_128 == moe::kGemm16Narrow && MOE_KERNEL16_STREAM == moe::kGemm16Stream &&
+                  MOE_KERNEL16_WGRAD == moe::kGemm16Wgrad, "the header's numbers");
 static_assert(kStaticScratchBytes == MOE_STATIC_SCRATCH_BYTES, "the limit stated in the header");
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
@@ -344,6 +346,25 @@ struct BwdPlan {
 };
 constexpr long long kWgradWorkgroups = 512;              // two per CU
 
+// The products over the experts' live rows
+moe::GemmArgs bwd_gemm_args(const moe_config* c, const Plan& p, const int32_t* demand, int32_t* units) {
+    moe::GemmArgs g{};
+    g.rows_dev = demand; g.rows_fixed = 0; g.rows_cap = p.C; g.groups = c->E; g.max_rows = p.C; g.rows_likely = (long long)c->T * c->k;
+    g.dtype = c->dtype; g.act = MOE_ACT_IDENTITY; g.a_rows_total = p.C_pad; g.units = units;
+    return g;
+}
+
+// dh = ge W2^T in fp32 (of_h; W2[e] read as [N = I][K = H]) or dxe = da W1^T (W1[e] as [N = H][K = I])
+moe::GemmArgs data_gradient_args(const moe_config* c, const Plan& p, const int32_t* demand, int32_t* units, const void* grad, const void* W,
+                                 void* out, bool of_h) {
+    const int K = of_h ? c->H : c->I, N = of_h ? c->I : c->H;
+    moe::GemmArgs g = bwd_gemm_args(c, p, demand, units);
+    g.A = grad; g.a_group_stride = (long long)p.C_pad * K; g.lda = K;
+    g.B = W; g.b_group_stride = (long long)c->H * c->I; g.ldb = K; g.b_is_nk = true;
+    g.C = out; g.c_group_stride = (long long)p.C_pad * N; g.ldc = N; g.N = N; g.K = K; g.c_f32 = of_h;
+    return g;
+}
+
 // An expert's dW1 or dW2 as a GEMM of the weight-streaming kernel (its rows: `M` columns of h or xe, all C_pad slots as K)
 moe::GemmArgs stream_wgrad_args(const moe_config* c, const Plan& p, const void* rows, int M, const void* grad, int N, float* out,
                                 const int32_t* counts_dev, int32_t* units) {
@@ -474,27 +495,18 @@ moe_status run_backward(const moe_config* c, const BwdPlan& b, void* ws, const v
                               demand, slot_token, slot_weight, units, false, s));
     MOE_TRY(moe::launch_bwd_gather(x, dout, slot_token, slot_weight, demand, H, E, C, C_pad, b.row_step, dt, xe, ge, Wg, wgt, s));
     // grouped GEMMs over the experts' live rows
-    moe::GemmArgs g{};
-    g.rows_dev = demand; g.rows_fixed = 0; g.rows_cap = C; g.groups = E; g.max_rows = C; g.rows_likely = (long long)T * k;
-    g.dtype = dt; g.act = MOE_ACT_IDENTITY; g.a_rows_total = C_pad;
     const long long rH = (long long)C_pad * H, rI = (long long)C_pad * I, HI = (long long)H * I;
     // the pre-activation again: a = xe W1 + b1
-    moe::GemmArgs f1 = g;
+    moe::GemmArgs f1 = bwd_gemm_args(c, p, demand, units);
     f1.A = xe; f1.a_group_stride = rH; f1.lda = H; f1.B = W1; f1.b_group_stride = HI; f1.ldb = I;
-    f1.C = a; f1.c_group_stride = rI; f1.ldc = I; f1.bias = b1; f1.bias_group_stride = I; f1.N = I; f1.K = H; f1.units = units;
+    f1.C = a; f1.c_group_stride = rI; f1.ldc = I; f1.bias = b1; f1.bias_group_stride = I; f1.N = I; f1.K = H;
     MOE_TRY(moe::launch_grouped_gemm(f1, s));
     // dh = dout W2^T in fp32 (W2[e] read as [N = I][K = H]); h = w phi(a), da = w dh phi'(a); dxe = da W1^T (W1[e] as [N = H][K = I])
-    moe::GemmArgs d1 = g;
-    d1.A = ge; d1.a_group_stride = rH; d1.lda = H; d1.B = W2; d1.b_group_stride = HI; d1.ldb = H; d1.b_is_nk = true;
-    d1.units = units; d1.C = dh; d1.c_group_stride = rI; d1.ldc = I; d1.N = I; d1.K = H; d1.c_f32 = true;
-    MOE_TRY(moe::launch_grouped_gemm(d1, s));
+    MOE_TRY(moe::launch_grouped_gemm(data_gradient_args(c, p, demand, units, ge, W2, dh, true), s));
     MOE_TRY(moe::launch_bwd_act(a, dh, ge, b2, demand, slot_weight, E, C, C_pad, b.row_step, H, I, c->act, dt, h, da, row_p, s));
     // gate: w dL/dw of every kept pair is in row_p; the softmax Jacobian
     MOE_TRY(moe::launch_bwd_gate(row_p, topk_expert, topk_weight, slot, T, b.T_pad, k, E, C, C_pad, b.ldL, dt, dl, dL, s));
-    moe::GemmArgs d2 = g;
-    d2.A = da; d2.a_group_stride = rI; d2.lda = I; d2.B = W1; d2.b_group_stride = HI; d2.ldb = I; d2.b_is_nk = true;
-    d2.units = units; d2.C = dxe; d2.c_group_stride = rH; d2.ldc = H; d2.N = H; d2.K = I;
-    MOE_TRY(moe::launch_grouped_gemm(d2, s));
+    MOE_TRY(moe::launch_grouped_gemm(data_gradient_args(c, p, demand, units, da, W1, dxe, false), s));
     // weight gradients: dW2[e] = h[e]^T ge[e], dW1[e] = xe[e]^T da[e] over the expert's slots, dWg = x^T dL over the tokens
     float* const wg_out = b.wg_slices > 1 ? (float*)ws_at(ws, b.off_wg_part) : dWg;
     moe::BwdFinish finish{};
@@ -631,6 +643,25 @@ int32_t moe_f32_gemm_body(int32_t groups, int32_t max_rows, int32_t N, int32_t K
     if (groups <= 0 || max_rows <= 0 || N <= 0 || K <= 0 || cus <= 0) return -1;
     if (listed && moe::f32_spans_worth(groups, max_rows, N, K, cus)) return MOE_F32_BODY_SPANS;
     return moe::f32_tile_body(groups, max_rows, N, cus);
+}
+
+int32_t moe_gemm16_kernel(const moe_config* cfg, int32_t product, int32_t cus) {
+    Plan p;
+    if (make_plan(cfg, &p) != MOE_OK || cfg->dtype == MOE_F32 || cus <= 0) return -1;
+    int32_t some = 0;                                    // the choice asks whether buffers are there, not what they hold
+    switch (product) {
+        case MOE_PRODUCT_FFN1:
+        case MOE_PRODUCT_FFN2: {
+            moe::GemmArgs g[2];
+            ffn_gemms(cfg, p, &some, &some, nullptr, &some, &some, nullptr, &some, nullptr, &some, &g[0], &g[1]);
+            return moe::gemm16_kernel(g[product], cus);
+        }
+        case MOE_PRODUCT_DH:
+        case MOE_PRODUCT_DXE:
+            return moe::gemm16_kernel(data_gradient_args(cfg, p, &some, &some, &some, &some, &some, product == MOE_PRODUCT_DH), cus);
+        case MOE_PRODUCT_DW: return wgrad_streams(cfg, p) ? MOE_KERNEL16_STREAM : MOE_KERNEL16_WGRAD;
+    }
+    return -1;
 }
 
 moe_status moe_ffn_status(const moe_config* cfg, const void* workspace, size_t workspace_bytes, void* stream) {

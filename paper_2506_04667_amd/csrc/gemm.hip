@@ -136,11 +136,19 @@ hipError_t prepare_grouped_gemm() {
     return e;
 }
 
+int gemm16_kernel(const GemmArgs& a, int cus) {
+    const bool streams = stream_gemm_eligible(a);
+    if (narrow_gemm_eligible(a) && (!streams || narrow_gemm_worth(a, cus))) return kGemm16Narrow;
+    return streams ? kGemm16Stream : kGemm16Generic;
+}
+
 hipError_t launch_grouped_gemm(const GemmArgs& a, hipStream_t stream) {
     if (a.groups <= 0 || a.max_rows <= 0 || a.N <= 0) return hipSuccess;
-    const bool streams = stream_gemm_eligible(a);
-    if (narrow_gemm_eligible(a) && (!streams || narrow_gemm_worth(a))) return launch_gemm_narrow(a, stream);
-    if (streams) return launch_grouped_gemm_stream(a, stream);
+    if (a.dtype != 0) {
+        const int kernel = gemm16_kernel(a, device_cu_count());
+        if (kernel == kGemm16Narrow) return launch_gemm_narrow(a, stream);
+        if (kernel == kGemm16Stream) return launch_grouped_gemm_stream(a, stream);
+    }
     if (a.a_is_km) return hipErrorInvalidValue;
     if (f32_stream_eligible(a)) return launch_gemm_f32_stream(a, stream);
     if (f32_gemm_eligible(a)) return launch_gemm_f32(a, stream);

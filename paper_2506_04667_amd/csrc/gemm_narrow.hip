@@ -286,8 +286,8 @@ bool narrow_gemm_eligible(const GemmArgs& a) {
 // 256 136 / 127; H = I = 2880, E = 48, T = 100 312 / 298; H = 4096, I = 1536, E = 64, T = 64 274 / 264; H = I = 2048, E = 128, T = 64
 // 253 / 248 on one card and 259 / 259 on another, T = 512 355 / 355, T = 16 106.4 / 107.2; top-8, H = 7168, I = 2048, E = 32, T = 32
 // 341 / 343.  16 rows, E = 128 (both GEMMs) 344 / 352.  [n][k] weights in half lines do not gain from that.
-bool narrow_gemm_worth(const GemmArgs& a) {
-    const long long all = (long long)a.groups * ((a.max_rows + R_BM - 1) / R_BM), ncol = (a.N + R_BN - 1) / R_BN, cus = device_cu_count();
+bool narrow_gemm_worth(const GemmArgs& a, int cus) {
+    const long long all = (long long)a.groups * ((a.max_rows + R_BM - 1) / R_BM), ncol = (a.N + R_BN - 1) / R_BN;
     const long long likely = a.rows_likely > 0 ? std::min(all, a.groups + a.rows_likely / R_BM) : all;
     return likely * ncol <= cus || (!a.b_is_nk && a.max_rows <= 8 && likely * ncol * 2 >= 3 * cus);
 }

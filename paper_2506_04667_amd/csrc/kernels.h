@@ -45,6 +45,10 @@ struct GemmArgs {
     bool fp32_mfma;                                         // fp32 storage: multiply on the fp32 instruction (gate logits, as in the fused gate)
 };
 hipError_t launch_grouped_gemm(const GemmArgs& a, hipStream_t stream);
+// which kernel that is for 16-bit storage on a GPU with `cus` CUs: the generic tiles (gemm.hip), the 128 x 128 tiles (gemm_narrow.hip) or
+// the weight-streaming kernel.  (The weight gradients have kernels of their own: wgrad.hip, and a form of the streaming kernel.)
+enum { kGemm16Generic = 0, kGemm16Narrow = 1, kGemm16Stream = 2, kGemm16Wgrad = 3 };
+int gemm16_kernel(const GemmArgs& a, int cus);
 
 // Kernels that use more than 64 KB of LDS have that limit raised per device before their first launch there;
 // the launchers do it on first use, these do it for every instantiation at once (moe_init).
@@ -72,7 +76,7 @@ hipError_t launch_ffn_units(const int32_t* rows_dev, int rows_cap, int groups, i
 // 16-bit products in 128 x 128 tiles, for launches with few tasks and for narrow layers; reads the same scratch block
 bool narrow_gemm_eligible(const GemmArgs& a);
 // are they the faster ones where the streaming kernel takes the product too?
-bool narrow_gemm_worth(const GemmArgs& a);
+bool narrow_gemm_worth(const GemmArgs& a, int cus);
 hipError_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream);
 hipError_t prepare_gemm_narrow();
 // Both FFN GEMMs in one persistent launch: a unit's second-GEMM tasks start when all its first-GEMM tiles are
