@@ -44,7 +44,7 @@ def _backward(w, dev, host, dout):
     dict(T=300, H=64, I=72, E=6, k=2, capacity_factor=0.8, dtype="f32", with_bias=True, act="gelu_tanh", gate_bias=True),
     dict(T=257, H=40, I=136, E=3, k=3, capacity_factor=1.0, dtype="f32", with_bias=False, act="gelu_erf"),
     dict(T=130, H=72, I=64, E=5, k=1, capacity_factor=0.5, dtype="f32", with_bias=True, act="relu"),
-    # 16-bit on the generic kernels (K not a multiple of 64) and on the weight-streaming ones
+    # 16-bit in tiles of 128 x 128, with K no multiple of 64 and with whole K-tiles
     dict(T=757, H=328, I=840, E=8, k=2, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_tanh"),
     dict(T=1500, H=256, I=512, E=8, k=2, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_erf", gate_bias=True),
     dict(T=900, H=256, I=256, E=12, k=3, capacity_factor=0.7, dtype="f16", with_bias=False, act="identity",
@@ -56,7 +56,7 @@ def _backward(w, dev, host, dout):
     dict(T=2100, H=64, I=72, E=8, k=2, capacity_factor=1.0, dtype="f32", with_bias=False, act="relu", gate_bias=True),
     dict(T=3333, H=128, I=64, E=12, k=3, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_tanh"),
     # the paper's layer shape per expert (H = I = 2048, 256 slots, top-2, erf-GELU, bf16) with 16 experts: the tile
-    # shapes, K = 256 weight-gradient GEMMs and streaming kernels of the full-size backward pass
+    # shapes, K = 256 weight-gradient GEMMs and weight-streaming kernels of the full-size backward pass
     dict(T=2048, H=2048, I=2048, E=16, k=2, capacity_factor=1.0, dtype="bf16", with_bias=False, act="gelu_erf"),
 ])
 def test_backward_matches_the_oracle(oracle, case):

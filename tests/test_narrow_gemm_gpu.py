@@ -22,9 +22,15 @@ def _layer(E, rows, H, I, act, dtype, bias, seed):
     return t, C
 
 
-def _ffn(t, rows, C, H, I, act, dtype):
+def kernels(cfg):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return moe.moe_gemm16_kernel(cfg, "ffn1", cus), moe.moe_gemm16_kernel(cfg, "ffn2", cus)
+
+
+def _ffn(t, rows, C, H, I, act, dtype, on):
     E = len(rows)
     cfg = moe.make_config(max(1, sum(rows)), H, I, E, 1, 1.0, act, dtype, capacity_override=C)
+    assert kernels(cfg) == on
     b = moe.Buffers(cfg).alloc_staged()
     b.xe.zero_()
     b.xe[:, :C] = t["xe"].cuda()
@@ -46,10 +52,14 @@ def _ffn(t, rows, C, H, I, act, dtype):
     ([3] * 48, 1032, 264, "gelu_tanh", False),                   # few rows: a weight stream
 ])
 def test_against_float64(rows, H, I, act, bias, dtype):
+    check_against_float64(rows, H, I, act, bias, dtype, ("128", "128"))
+
+
+def check_against_float64(rows, H, I, act, bias, dtype, on):
     print("case", rows, H, I, act, bias, dtype, flush=True)
     t, C = _layer(len(rows), rows, H, I, act, dtype, bias, H + I)
-    y = _ffn(t, rows, C, H, I, act, dtype).double()
-    f = {k: None if v is None else v.double() for k, v in t.items()}
+    y = _ffn(t, rows, C, H, I, act, dtype, on).double().cuda()
+    f = {k: None if v is None else v.double().cuda() for k, v in t.items()}
     # h and y are each rounded once to storage: relative to each value 2^-8 (bf16) or 2^-11 (f16) at most
     tol = 2 * 2.0 ** (-8 if dtype == "bf16" else -11)
     for e, r in enumerate(rows):
@@ -67,8 +77,8 @@ def test_same_sums_as_the_streaming_kernel(H, I, dtype):
     few = [200, 130, 1, 97]
     many = few + [140] * 72
     t, C = _layer(len(many), many, H, I, "gelu_erf", dtype, True, 5)
-    wide = _ffn(t, many, C, H, I, "gelu_erf", dtype)
-    narrow = _ffn({k: v[:4] for k, v in t.items()}, few, C, H, I, "gelu_erf", dtype)
+    wide = _ffn(t, many, C, H, I, "gelu_erf", dtype, ("stream", "stream"))
+    narrow = _ffn({k: v[:4] for k, v in t.items()}, few, C, H, I, "gelu_erf", dtype, ("128", "128"))
     assert torch.equal(narrow, wide[:4])
 
 
@@ -85,6 +95,8 @@ def test_same_data_gradients_as_the_streaming_kernel(dtype):
     out = []
     for E in (4, 76):
         cfg = moe.make_config(T, H, I, E, k, 1.0, "relu", dtype, capacity_override=C)
+        cus = torch.cuda.get_device_properties(0).multi_processor_count
+        assert {moe.moe_gemm16_kernel(cfg, p, cus) for p in ("ffn1", "dh", "dxe")} == {"128" if E == 4 else "stream"}
         dx, dWg, dgb, dW1, db1, dW2, db2 = (torch.empty(s, device="cuda") for s in
                                             ((T, H), (H, E), (E,), (E, H, I), (E, I), (E, I, H), (E, H)))
         ws = torch.empty(moe.moe_backward_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")

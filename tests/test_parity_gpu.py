@@ -80,32 +80,46 @@ def test_activations_bf16(oracle, act):
     _run(oracle, w)
 
 
-# ------------------------------------------------------------ shapes that take the weight-streaming FFN kernel
+# ------------------------------------------------------------ 16-bit FFNs: 128 x 128 tiles and the weight-streaming kernel
 
-@pytest.mark.parametrize("case", [
-    # several ragged row tiles per expert, fewer experts than XCDs, shortest K the kernel takes, ragged last column tile
-    dict(T=900, H=192, I=448, E=3, k=2, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_erf"),
-    # experts nobody picks between live ones; second column tile only 8 wide (I = 264); second GEMM on the generic kernel
-    dict(T=2000, H=320, I=264, E=11, k=2, capacity_factor=1.25, dtype="f16", with_bias=True, act="relu", empty=(0, 4, 5, 10)),
-    # more experts than XCDs, three row tiles each, both GEMMs streaming
-    dict(T=3000, H=256, I=256, E=16, k=2, capacity_factor=1.5, dtype="f16", with_bias=False, act="gelu_tanh"),
-    # one live expert out of nine: a single unit feeds one XCD only
-    dict(T=300, H=256, I=512, E=9, k=1, capacity_factor=9.0, dtype="bf16", with_bias=True, act="identity",
-         empty=(0, 1, 2, 3, 4, 5, 7, 8)),
-    # capacities of at most 128 rows take the 128-row tile: ragged rows (C = 108), ragged last column tile
-    dict(T=700, H=256, I=320, E=13, k=2, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_erf"),
+@pytest.mark.parametrize("on,case", [
+    # few tasks.  Several ragged row tiles per expert, fewer experts than XCDs, ragged last column tile
+    (("128", "128"), dict(T=900, H=192, I=448, E=3, k=2, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_erf")),
+    # experts nobody picks between live ones; last column tile only 8 wide (I = 264)
+    (("128", "128"), dict(T=2000, H=320, I=264, E=11, k=2, capacity_factor=1.25, dtype="f16", with_bias=True, act="relu", empty=(0, 4, 5, 10))),
+    # more experts than XCDs, three row tiles each
+    (("128", "128"), dict(T=3000, H=256, I=256, E=16, k=2, capacity_factor=1.5, dtype="f16", with_bias=False, act="gelu_tanh")),
+    # one live expert out of nine
+    (("128", "128"), dict(T=300, H=256, I=512, E=9, k=1, capacity_factor=9.0, dtype="bf16", with_bias=True, act="identity",
+                          empty=(0, 1, 2, 3, 4, 5, 7, 8))),
+    # capacities of at most 128 rows: ragged rows (C = 108), ragged last column tile
+    (("128", "128"), dict(T=700, H=256, I=320, E=13, k=2, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_erf")),
     # ... with drops (C = 47), more units than XCDs, experts nobody picks
-    dict(T=520, H=192, I=256, E=20, k=3, capacity_factor=0.6, dtype="f16", with_bias=False, act="relu", empty=(3, 19)),
+    (("128", "128"), dict(T=520, H=192, I=256, E=20, k=3, capacity_factor=0.6, dtype="f16", with_bias=False, act="relu", empty=(3, 19))),
     # ... exactly one full 128-row tile per expert
-    dict(T=1024, H=512, I=512, E=16, k=2, capacity_factor=1.0, dtype="f16", with_bias=True, act="gelu_tanh"),
+    (("128", "128"), dict(T=1024, H=512, I=512, E=16, k=2, capacity_factor=1.0, dtype="f16", with_bias=True, act="gelu_tanh")),
     # a handful of rows per expert (decode-like): C = 4 with drops; C = 2 with five tokens
-    dict(T=64, H=256, I=512, E=16, k=2, capacity_factor=0.5, dtype="bf16", with_bias=True, act="gelu_erf"),
-    dict(T=5, H=192, I=256, E=8, k=2, capacity_factor=1.0, dtype="f16", with_bias=False, act="relu"),
+    (("128", "128"), dict(T=64, H=256, I=512, E=16, k=2, capacity_factor=0.5, dtype="bf16", with_bias=True, act="gelu_erf")),
+    (("128", "128"), dict(T=5, H=192, I=256, E=8, k=2, capacity_factor=1.0, dtype="f16", with_bias=False, act="relu")),
+    # more tasks than CUs: 256-row tiles and, in most experts, a 128-row one (C = 296); ragged last column tile
+    (("stream", "stream"), dict(T=9000, H=256, I=448, E=64, k=2, capacity_factor=1.05, dtype="bf16", with_bias=True, act="gelu_erf")),
+    # the shortest K the streaming kernel takes, three row tiles; the second GEMM is too narrow for it
+    (("stream", "128"), dict(T=9000, H=192, I=448, E=33, k=2, capacity_factor=1.25, dtype="f16", with_bias=False, act="gelu_tanh")),
+    # 128-row tiles only (C = 93), not a multiple of 8 experts, second column tile 8 wide, drops, experts nobody picks
+    (("stream", "stream"), dict(T=6000, H=256, I=264, E=130, k=2, capacity_factor=1.0, dtype="f16", with_bias=True, act="relu", empty=(0, 4, 129))),
+    # a handful of rows per expert, more experts than half the CUs
+    (("stream", "stream"), dict(T=200, H=256, I=256, E=130, k=2, capacity_factor=1.0, dtype="bf16", with_bias=True, act="gelu_erf")),
+    # one live expert out of 64: its units feed one XCD or two
+    (("stream", "128"), dict(T=300, H=256, I=512, E=64, k=1, capacity_factor=64.0, dtype="bf16", with_bias=True, act="identity",
+                             empty=tuple(e for e in range(64) if e != 37))),
 ])
-def test_streaming_ffn_shapes(oracle, case):
+def test_streaming_ffn_shapes(oracle, on, case):
     case = dict(case)
     empty = case.pop("empty", ())
     w = scaled(WORKLOADS["paper_bf16_e128"], name="stream", seed=21, **case)
+    cfg = moe.config_of(w)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert (moe.moe_gemm16_kernel(cfg, "ffn1", cus), moe.moe_gemm16_kernel(cfg, "ffn2", cus)) == on
     gb = None
     if empty:
         gb = torch.zeros(w.E)
@@ -283,11 +297,12 @@ def test_single_launch_ffn_give_up_is_reported():
     assert torch.equal(b.out, b_ref.out)
 
 
+@pytest.mark.parametrize("copies,on", [(1, "128"), (33, "stream")])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("act", ["relu", "gelu_tanh", "gelu_erf", "identity"])
-def test_activation_over_its_whole_range(oracle, dtype, act):
-    # phi_1 of the first FFN task (Eq. ffn) on a grid of pre-activations over [-10, 10], through the streaming
-    # kernel's epilogue: row r of expert e is the unit vector of h = r, so x W1 reproduces row r of W1 exactly (one
+def test_activation_over_its_whole_range(oracle, dtype, act, copies, on):
+    # phi_1 of the first FFN task (Eq. ffn) on a grid of pre-activations over [-10, 10], through the epilogues of the 128 x 128
+    # tiles and, with copies of the two experts, of the streaming kernel: row r of expert e is the unit vector of h = r, so x W1 reproduces row r of W1 exactly (one
     # non-zero product per sum); W2 is the identity, so y = phi(W1) rounded to storage.  The 16-bit erf-GELU is a
     # clamped polynomial: the grid covers the clamp at +-3 sqrt 2 and the tail below -5 that Gaussian
     # pre-activations never reach.
@@ -301,14 +316,17 @@ def test_activation_over_its_whole_range(oracle, dtype, act):
     W1 = grid.to(td).reshape(E, H, H).contiguous()
     v = W1.double().numpy()                                   # the pre-activations, exactly
     W2 = torch.eye(H, dtype=td).repeat(E, 1, 1).contiguous()
-    xe = torch.eye(H, dtype=td).repeat(E, 1, 1).contiguous()  # [E, C_pad = 256, H]
-    cfg = moe.make_config(H, H, H, E, 2, 1.0, act, dtype)     # C = k T / E = 256 rows per expert
+    xe = torch.eye(H, dtype=td).repeat(E * copies, 1, 1)      # [experts, C_pad = 256, H]
+    cfg = moe.make_config(E * copies * H, H, H, E * copies, 1, 1.0, act, dtype)       # C = k T / E = 256 rows per expert
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert moe.moe_gemm16_kernel(cfg, "ffn1", cus) == on
     b = moe.Buffers(cfg).alloc_staged()
     assert b.C == H and b.C_pad == H
-    demand = torch.full((E,), H, dtype=torch.int32, device="cuda")
-    moe.moe_expert_ffn(cfg, b.workspace, xe.cuda(), demand, W1.cuda(), None, W2.cuda(), None, b.y)
+    demand = torch.full((E * copies,), H, dtype=torch.int32, device="cuda")
+    moe.moe_expert_ffn(cfg, b.workspace, xe.cuda(), demand, W1.repeat(copies, 1, 1).cuda(), None, W2.repeat(copies, 1, 1).cuda(), None, b.y)
     torch.cuda.synchronize()
-    got = b.y.double().cpu().numpy()
+    got = b.y[:E].double().cpu().numpy()
+    assert torch.equal(b.y, b.y[:E].repeat(copies, 1, 1))
     ref = np.vectorize(lambda t: oracle.activation(t, act))(v)
     # the layer's bar on the tensor as a whole ...
     parity.assert_close(got, ref, parity.TOL[dtype], "phi(v) over [-10, 10]")
