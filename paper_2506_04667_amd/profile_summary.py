@@ -22,6 +22,7 @@ import sys
 def _short(name, n=96):
     name = re.sub(r"\(anonymous namespace\)::", "", name)
     name = re.sub(r"^void ", "", name)
+    name = re.sub(r"\((?:\w+::)*\w+\)(-?\d+)", r"\1", name)      # template values of an enum: (moe::RouteBase)1
     name = re.sub(r"\(.*\)$", "", name)
     return name if len(name) <= n else name[: n - 3] + "..."
 
