@@ -137,7 +137,8 @@ def test_streaming_ffn_shapes(oracle, on, case):
 
 # (the kernel takes a GEMM with fewer than 4 x 256 tiles of 256 x 256 at full capacity and at least 8 x 256 K-tiles of 32)
 @pytest.mark.parametrize("case", [
-    # one live expert of nine, long K: one or two live tiles for all the workgroups, so every tile is cut into many pieces
+    # one live expert of nine, long K: one or two live tiles for all the workgroups, so every tile is cut into many pieces (128 each in
+    # the first GEMM: twice the boundaries that the fix-up's lanes hold at a time)
     dict(T=150, H=4096, I=512, E=9, k=1, capacity_factor=9.0, with_bias=True, act="gelu_erf", empty=(0, 1, 2, 3, 4, 5, 7, 8)),
     # short K (four K-tiles per tile): ranges of whole tiles with few cuts; 128 units
     dict(T=6000, H=128, I=1024, E=64, k=2, capacity_factor=1.5, with_bias=True, act="relu"),
