@@ -333,3 +333,21 @@ def test_backward_workspace_bytes(args, most):
     row = 4 * (H + I) * 4 if args[-1] == "f32" else 2 * (H + I) * 2 + max(4 * I, 2 * H)
     assert most > row * E * C_pad
     assert moe.moe_backward_workspace_bytes(cfg) <= most
+
+
+def test_gemm16_kernel_query(lib):
+    def kernels(*args, cus=256, **kw):
+        cfg = moe.make_config(*args, **kw)
+        return [moe.moe_gemm16_kernel(cfg, p, cus) for p in moe.PRODUCTS]
+    assert kernels(16384, 2048, 2048, 128, 2, 1.0, "gelu_erf", "bf16") == ["stream"] * 5
+    assert kernels(757, 328, 840, 8, 2, 1.0, "gelu_tanh", "f16") == ["128"] * 4 + ["wgrad"]
+    # one tile of 128 x 128 per CU is the line: 16 experts of 128 rows and 16 column tiles are 256 of them
+    assert kernels(1024, 2048, 2048, 16, 2, 1.0, "relu", "bf16", capacity_override=128)[0] == "128"
+    assert kernels(1024, 2048, 2048, 16, 2, 1.0, "relu", "bf16", capacity_override=128, cus=255)[0] == "stream"
+    assert kernels(1024, 2048, 2048, 16, 2, 1.0, "relu", "bf16", capacity_override=129)[0] == "stream"
+    # operands that 32-bit offsets cannot reach
+    assert kernels(64, 8, 1 << 27, 2, 1, 1.0, "relu", "bf16")[0] == "generic"
+    cfg = moe.make_config(64, 64, 64, 4, 1, 1.0, "relu", "bf16")
+    f32 = moe.make_config(64, 64, 64, 4, 1, 1.0, "relu", "f32")
+    for c, product, cus in ((cfg, -1, 256), (cfg, 5, 256), (cfg, 0, 0), (f32, 0, 256), (moe.make_config(64, 60, 64, 4, 1, 1.0, "relu", "bf16"), 0, 256)):
+        assert lib.moe_gemm16_kernel(ctypes.byref(c), product, cus) == -1
