@@ -395,7 +395,14 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 
     // ---- per-lane LDS read offsets ----
     const int r16 = lane & 15, kq = lane >> 4;          // row/column inside a 16-wide MFMA tile; k-octet of the lane
-    const int a_row = wm * TM * 16 + r16;
+    // Small tiles seldom have all their rows live.  Their 16-row MFMA tiles are dealt to the two wavefront rows in turn, and products of those
+    // without a live row are left out: the matrix cores' power comes off the clocks (layers, us, sustained: fp16, E = 128, 16384 tokens Zipf 1.2,
+    // mostly 24 live rows 279 -> 264; E = 64, H = 1024, Zipf 1.2 143 -> 133; bf16, E = 128, 8 to 16 rows 366 -> 360, 64 rows 405 -> 401; all
+    // rows live 146 either way).  Large tiles: every condition costs the full ones more (7 % for all products, 2 to 3 % for the last three
+    // eighths of them) than a tile of 145 rows gains (4 %).
+    constexpr bool DEAL = G == 1 && !KM;
+    constexpr int ROW_STEP = DEAL ? 32 : 16, WM_STEP = DEAL ? 16 : TM * 16;  // rows between a wavefront's MFMA tiles; between the wavefront rows
+    const int a_row = wm * WM_STEP + r16;
     const int a_sw = swz_a(a_row);                      // same for every 16-row tile of this lane
     const int bk = kq * 8 + (r16 >> 2);                 // k of the first transpose read; the second is k + 4
     const int b_sw = swz_b(bk);
@@ -427,7 +434,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
                 f.x[i][2 * half + 1] = t[1];
             }
         } else {
-            f.x[i] = *(const u32x4*)(smem + sa * A_STAGE + a_rd[h] + (g * 4 + i) * 16 * 128);
+            f.x[i] = *(const u32x4*)(smem + sa * A_STAGE + a_rd[h] + (g * 4 + i) * ROW_STEP * 128);
         }
     };
     // weights of the K-tile in weight stage sb (NK: in half h of it): read i of 8 (column tile i / 2, k 0-3 or 4-7 of the lane's octet)
@@ -465,7 +472,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
             const bool low = r16 < 8;
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
-                const int row = cur.row0 + wm * (TM * 16) + tm * 16 + (r16 & 7);
+                const int row = cur.row0 + wm * WM_STEP + tm * ROW_STEP + (r16 & 7);
 #pragma unroll
                 for (int tn = 0; tn < TN; tn += 2) {
                     f32x4 v[2] = {acc[tm][tn], acc[tm][tn + 1]};
@@ -489,7 +496,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
             // no bias, identity: lanes 16 apart swap halves of two neighbouring tiles and store 8 columns each
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
-                const int row = cur.row0 + wm * (TM * 16) + tm * 16 + r16;
+                const int row = cur.row0 + wm * WM_STEP + tm * ROW_STEP + r16;
 #pragma unroll
                 for (int tn = 0; tn < TN; tn += 2) {
                     u32x4 v;
@@ -544,7 +551,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
             for (int i = 0; i < 4; ++i) {
                 const int r_local = i * 8 + (lane_e >> 3), chunk = lane_e & 7;
                 const u32x4 v = *(const u32x4*)(epi + r_local * 128 + ((chunk ^ swz_e(r_local)) << 4));
-                const int row = cur.row0 + wm * (TM * 16) + pass * 32 + r_local, col = col_w + chunk * 8;
+                const int row = cur.row0 + wm * WM_STEP + (pass * 2 + (i >> 1)) * ROW_STEP + (r_local & 15), col = col_w + chunk * 8;
                 if (row < cur.rows && col < N) *(u32x4*)((elem*)P.C + c_base + (size_t)row * P.ldc + col) = v;
             }
         }
@@ -608,6 +615,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         issue_b();
         wait_copies_and_barrier<4>();                   // A0 and B0 (and more) have landed
     }
+    auto live_tiles = [&](const Task& t) __attribute__((always_inline)) { return DEAL ? uniform((t.rows - t.row0 - wm * 16 + 31) >> 5) : TM; };
+    int live = live_tiles(cur);                         // MFMA row tiles of this wavefront with live rows (may be more than it has)
     WFrags w0, w1;                                      // weights of the even / odd tile of a pair
     XFrags x0, x1;                                      // activations of row tiles 0-3 / 4-7 (G = 1: of the even / odd tile)
 #pragma unroll
@@ -645,10 +654,16 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     // the next tile's operands (-> wn_f, xn_f) between them.
     auto single_tail = [&](const WFrags& wf, const XFrags& xf, WFrags& wn_f, XFrags& xn_f, int sb_n, int sa_n, int h_n) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 4; i < 16; ++i) {
-            mma_one(i, 0, wf, xf);
-            if (i < 12) read_w(i - 4, sb_n, h_n, wn_f);
-            else read_x(i - 12, 0, sa_n, h_n, xn_f);
+        for (int t = 1; t < 4; ++t) {
+            if (!DEAL || t < live) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mma_one(t * 4 + i, 0, wf, xf);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (t < 3) read_w((t - 1) * 4 + i, sb_n, h_n, wn_f);
+                else read_x(i, 0, sa_n, h_n, xn_f);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -662,7 +677,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         if (G == 2) first_half(w0, sa, 0);
         const int sb1 = NK ? sb : (sb + 1) & (B_STAGES - 1);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) mma_one(i, LAST_G, w0, G == 2 ? x1 : x0);   // these cover the wait for tile u+1
+        for (int i = 0; i < 4; ++i)                     // these cover the wait for tile u+1
+            if (!DEAL || live > 0) mma_one(i, LAST_G, w0, G == 2 ? x1 : x0);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!NK) {                            // (the pair's weights arrive together)
             wait_copies_and_barrier<STEADY ? A_COPIES + 4 : 0>();
@@ -676,7 +692,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         sb = NK ? (sb == B_PAIR_STAGES - 1 ? 0 : sb + 1) : (sb1 + 1) & (B_STAGES - 1);
         if (!LAST) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) mma_one(i, LAST_G, w1, x1);
+            for (int i = 0; i < 4; ++i)
+                if (!DEAL || live > 0) mma_one(i, LAST_G, w1, x1);
             __builtin_amdgcn_sched_barrier(0);
             wait_copies_and_barrier<MODE <= kRowsOnly ? 4 : 0>();
             if (MODE <= kRowsOnly) issue_a();
@@ -686,12 +703,14 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
             else single_tail(w1, x1, w0, x0, sb, sa ^ 1, 0);
         } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mma_one(i, LAST_G, w1, x1);
+            for (int i = 0; i < 16; ++i)
+                if (!DEAL || (i >> 2) < live) mma_one(i, LAST_G, w1, x1);
             __builtin_amdgcn_sched_barrier(0);
         }
         k_done += 2;
         if (k_done == nk) {
             k_done = 0;
+            live = live_tiles(nxt);
             finish_task();
             __builtin_amdgcn_sched_barrier(0);
         }
