@@ -16,12 +16,17 @@
 //     128 x 256 variant of the same loop takes remainders of at most 128 rows;
 //   * K-tile 32.  Weights (from HBM) go through a ring of 4 LDS stages of 16 KB
 //     (32 x 256), requested 3 K-tiles ahead; activations (re-read from L2 by the 8
-//     column tiles of an expert) go through 2 stages of 32 KB that hold two K-tiles
-//     each (256 rows x 128 B), so every L2 request is a full 128-byte line;
+//     column tiles of an expert) go through 3 stages (128-row tiles: 2) of 32 KB that
+//     hold two K-tiles each (256 rows x 128 B), so every L2 request is a full 128-byte line;
 //   * global -> LDS copies are direct (global_load_lds_dwordx4: no VGPR staging),
 //     issued from inline asm and waited for with explicit s_waitcnt vmcnt(n) +
 //     s_barrier: a compiler-visible LDS-DMA makes every later LDS read wait for all
 //     outstanding copies;
+//   * a large tile's copies are issued one at a time between the MFMAs.  A copy takes the CU's address unit 16 cycles; issued together
+//     behind the barrier by eight wavefronts, up to 48 of them held their wavefronts up for 768 cycles of a 1024-cycle K-tile.  Layers,
+//     us: E = 16, 16384 tokens 547 -> 505, E = 32, H = 7168, top-8, 4096 tokens 1815 -> 1715, E = 128 600 -> 571; a deeper ring alone
+//     changes nothing.  128-row tiles have half as many copies and wait for bytes instead: later requests cost them 3 %, so theirs
+//     stay together;
 //   * MFMA operand fragments are double-buffered in registers at half-K-tile
 //     granularity: while 16 MFMAs run, the LDS reads of the next 16 are in flight,
 //     across K-tile and task boundaries too.
@@ -39,8 +44,8 @@
 // H = I = 2048, E = 128):
 //   kLayoutNK  weights stored [n][k] (the data gradients): copied in pairs of K-tiles like the activations, so that a
 //              request is a full line (with 64-byte rows every line crossed from HBM twice: 498 us per GEMM at that shape),
-//              through a ring of 3 stages of 32 KB (256 n x 128 B), requested 3 pairs ahead.  The third stage takes the
-//              place of the epilogue's LDS area: this epilogue pairs up lanes instead.  One wait and barrier per pair;
+//              through a ring of 3 stages of 32 KB (256 n x 128 B), requested 2 pairs ahead (128-row tiles: 3).  The third stage
+//              leaves the activations two, and none for the epilogue, which pairs up lanes instead.  One wait and barrier per pair;
 //   kLayoutKM  activations stored [k][m] (the weight gradients, whose k runs over an expert's slots): a stage holds
 //              64 k x 256 G B, swizzled and read with the transpose read like the weights' [k][n].
 // Rows at or beyond the live row count are fetched from the last live row (their
@@ -52,8 +57,8 @@
 // The MFMAs take the weight fragment as their first operand, so a lane's
 // accumulators hold, for ONE token row, runs of four consecutive output columns.
 // The epilogue applies bias and activation in registers, packs each run to 8 bytes,
-// transposes 32 rows at a time through a wave-private LDS area and stores full
-// 128-byte row segments.
+// transposes 32 rows at a time through a wave-private part of an activation stage
+// that is free then and stores full 128-byte row segments.
 //
 // Requires K % 64 == 0, K >= 192 (kLayoutNK: 256) and N % 8 == 0.  kLayoutRagged takes every K % 8 == 0 above 128: the last
 // pair of K-tiles is filled up with zeros, in both operands, so that an infinity beyond K cannot meet them.  Other shapes, and launches
@@ -97,14 +102,14 @@ constexpr int TN = 4, WN = 4;                           // 16-column MFMA tiles 
 // kernel), so experts with few rows (skewed routing, small capacities, few tokens) do not pay for a
 // half-empty large tile.
 constexpr int A_STAGE = kUnitRowsLarge * 128;           // up to 256 rows x 64 k (two K-tiles)
-constexpr int A_STAGES = 2;
+constexpr int A_STAGES = 3;
 constexpr int B_STAGE = BK * BN * 2;                    // 32 k x 256 columns
 constexpr int B_STAGES = 4;
 constexpr int B_ROW_BYTES = BN * 2;
 constexpr int B_REGION = A_STAGES * A_STAGE;            // weights ring starts after the activation stages
-constexpr int EPI_REGION = B_REGION + B_STAGES * B_STAGE;
 constexpr int EPI_BYTES_PER_WAVE = 32 * 128;            // 32 rows x 64 columns x 2 B
-constexpr int LDS_BYTES = EPI_REGION + 8 * EPI_BYTES_PER_WAVE;
+static_assert(8 * EPI_BYTES_PER_WAVE == A_STAGE, "a tile's epilogue goes through an activation stage");
+constexpr int LDS_BYTES = B_REGION + B_STAGES * B_STAGE;
 static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of a gfx950 CU");
 
 // v_mfma_f32_16x16x32: a lane holds, of each operand, 8 consecutive k (k = 8 (lane / 16) ..) of row/column
@@ -164,8 +169,8 @@ static __device__ const u32x4 stream_zeros = {0u, 0u, 0u, 0u};
 
 constexpr int kSpinLimit = 1 << 21;
 constexpr int kLayoutNK = 1, kLayoutKM = 2, kLayoutRagged = 4;
-constexpr int B_PAIR_STAGE = BN * 128, B_PAIR_STAGES = 3;               // kLayoutNK: 256 n x 64 k
-static_assert(B_REGION + B_PAIR_STAGES * B_PAIR_STAGE <= LDS_BYTES, "three pairs of [n][k] weights");
+constexpr int A_STAGES_NK = 2, B_PAIR_STAGE = BN * 128, B_PAIR_STAGES = 3;              // kLayoutNK: 256 n x 64 k
+static_assert(A_STAGES_NK * A_STAGE + B_PAIR_STAGES * B_PAIR_STAGE <= LDS_BYTES, "three pairs of [n][k] weights");
 constexpr int kActF32Out = 4;                           // template value of ACT: identity, no bias, C in fp32
 
 // The work of one workgroup on one list for one GEMM (phase PH of the arguments, activation ACT): `list` =
@@ -186,7 +191,10 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     constexpr bool NK = (LAYOUT & kLayoutNK) != 0, KM = (LAYOUT & kLayoutKM) != 0, RAGGED = (LAYOUT & kLayoutRagged) != 0;
     static_assert(!RAGGED || (!NK && !KM), "only the forward layouts' last K-tiles are filled up with zeros");
     constexpr int B_COPIES = NK ? 4 : 2;                // 1 KB copies per wavefront and request of weights (NK: two K-tiles)
-    constexpr int A_COPIES = 2 * G;                     // 1 KB copies per wavefront and activation stage
+    constexpr int A_COPIES = 2 * G, A_HALF = G;         // 1 KB copies per wavefront and activation stage; half of them
+    constexpr bool SPREAD = G == 2;                     // copies one by one between the MFMAs
+    constexpr int AS = SPREAD && !NK ? A_STAGES : 2;    // activation stages in the ring
+    constexpr int B_BASE = (NK ? A_STAGES_NK : A_STAGES) * A_STAGE;
     static_assert(BM == (G == 2 ? kUnitRowsLarge : kUnitRowsSmall), "the unit list is cut in row tiles of this kernel");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
@@ -331,7 +339,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     const size_t b_step = NK ? (size_t)128 : (size_t)BK * P.ldb * 2;       // bytes between K-tiles of the weights
     const uint32_t lds_base = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
     const uint32_t lds_a_wave = lds_base + wave * (A_COPIES * 1024);
-    const uint32_t lds_b_wave = lds_base + B_REGION + wave * (B_COPIES * 1024);
+    const uint32_t lds_b_wave = lds_base + B_BASE + wave * (B_COPIES * 1024);
 
     // the lane number, opaque to the compiler: what is made of it is made there and not kept in registers across the main loop
     auto lane_here = [&]() __attribute__((always_inline)) {
@@ -340,19 +348,21 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         return l;
     };
     int a_issue_stage = 0, b_issue_stage = 0;
-    auto issue_a = [&]() __attribute__((always_inline)) {                              // next pair of K-tiles of the activation rows
+    // copies [first, last) of the next pair of K-tiles of the activation rows
+    auto issue_a = [&](int first, int last) __attribute__((always_inline)) {
         const uint32_t d = lds_a_wave + a_issue_stage * A_STAGE;
         if (RAGGED && a_left == 1) {                    // a chunk of 8 k is inside K or beyond it
             const int l = lane_here(), left = P.K - (nk - 2) * BK;
 #pragma unroll
-            for (int j = 0; j < A_COPIES; ++j) {
+            for (int j = first; j < last; ++j) {
                 const int c = (l & 7) ^ swz_a((wave * A_COPIES + j) * 8 + (l >> 3));
                 copy_to_lds_lane(c * 8 < left ? a_base + a_off[j] : (const unsigned char*)&stream_zeros, d + j * 1024);
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < A_COPIES; ++j) copy_to_lds(a_base, a_off[j], d + j * 1024);
+            for (int j = first; j < last; ++j) copy_to_lds(a_base, a_off[j], d + j * 1024);
         }
+        if (last < A_COPIES) return;
         if (--a_left == 0) {
             a_left = nk / 2;
             a_base = na_base;
@@ -361,19 +371,21 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         } else {
             a_base += a_step;
         }
-        a_issue_stage ^= 1;
+        a_issue_stage = AS == 2 ? a_issue_stage ^ 1 : a_issue_stage + 1 == AS ? 0 : a_issue_stage + 1;
     };
-    auto issue_b = [&]() __attribute__((always_inline)) {                              // next K-tile (NK: pair) of the weights
+    // copies [first, last) of the next K-tile (NK: pair) of the weights
+    auto issue_b = [&](int first, int last) __attribute__((always_inline)) {
         const uint32_t d = lds_b_wave + b_issue_stage * (NK ? B_PAIR_STAGE : B_STAGE);
         if (RAGGED && b_left <= 2) {
             const int l = lane_here(), left = P.K - (nk - b_left) * BK;        // may be none
 #pragma unroll
-            for (int j = 0; j < B_COPIES; ++j)
+            for (int j = first; j < last; ++j)
                 copy_to_lds_lane((wave * 2 + j) * 2 + (l >> 5) < left ? b_base + b_off[j] : (const unsigned char*)&stream_zeros, d + j * 1024);
         } else {
 #pragma unroll
-            for (int j = 0; j < B_COPIES; ++j) copy_to_lds_stream(b_base, b_off[j], d + j * 1024);
+            for (int j = first; j < last; ++j) copy_to_lds_stream(b_base, b_off[j], d + j * 1024);
         }
+        if (last < B_COPIES) return;
         if (--b_left == 0) {
             b_left = b_requests;
             b_base = nb_base;
@@ -416,11 +428,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         if constexpr (NK) {                             // [half of the 64-wide stage]
-            b_rd[tn] = B_REGION + (wn * TN * 16 + r16) * 128 + (((((tn & 1) << 2) | kq) ^ swz_a(r16)) << 4);
+            b_rd[tn] = B_BASE + (wn * TN * 16 + r16) * 128 + (((((tn & 1) << 2) | kq) ^ swz_a(r16)) << 4);
             continue;
         }
         const int chunk = (wn * TN + tn) * 2 + ((r16 & 3) >> 1);
-        b_rd[tn] = B_REGION + bk * B_ROW_BYTES + ((chunk ^ b_sw) << 4) + (r16 & 1) * 8;
+        b_rd[tn] = B_BASE + bk * B_ROW_BYTES + ((chunk ^ b_sw) << 4) + (r16 & 1) * 8;
     }
 
     // activations of row tiles 4 g .. 4 g + 3, K-tile in activation stage sa, half h: read i of 4
@@ -456,9 +468,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     };
 
     // ---- epilogue of task `cur`: bias, activation, conversion, transposed store; then advance to the next task ----
-    unsigned char* epi = smem + EPI_REGION + wave * EPI_BYTES_PER_WAVE;   // [32 rows][64 columns], 128 B pitch
-    auto store_tile = [&]() __attribute__((always_inline)) {
+    auto store_tile = [&](int free_stage) __attribute__((always_inline)) {
         const int lane_e = lane_here();
+        // [32 rows][64 columns], 128 B pitch, in a stage that is free: the third one, or where that is part of the ring the one of the pair that
+        // was multiplied last, where a wavefront's own next copies go and only they
+        unsigned char* const epi = smem + free_stage * A_STAGE + wave * EPI_BYTES_PER_WAVE;
         const int r16 = lane_e & 15, kq = lane_e >> 4;
         const int N = P.N;
         const int col_w = cur.n0 + wn * (TN * 16);      // first column of this wavefront
@@ -556,9 +570,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
             }
         }
     };
-    auto finish_task = [&]() __attribute__((always_inline)) {
+    auto finish_task = [&](int free_stage) __attribute__((always_inline)) {
         // Both copy cursors have moved on to `nxt` by now (they run at most 4 K-tiles ahead and K >= 6
-        // K-tiles; NK: 6 ahead and K >= 8), so the addresses of its successor can replace `nxt`'s.  The loads they need (the gather
+        // K-tiles; NK: at most 6 ahead and K >= 8), so the addresses of its successor can replace `nxt`'s.  The loads they need (the gather
         // table) are requested first and used after the tile is stored.
         Task after = nxt;
         ++nxt_j;
@@ -570,7 +584,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
             task_bases(after, na_base, nb_base);
             task_offsets(after, na_off, nb_off);
         }
-        store_tile();
+        store_tile(free_stage);
         if (COUNT) {
             // this wavefront's part of the tile has reached the XCD's L2 before it is counted
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -581,38 +595,50 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     };
 
     // ---- main loop over the stream of K-tiles u = 0 .. U-1 ----
-    // K-tile u: weights in stage u % 4, activations in stage (u / 2) % 2, half u % 2; one 32-wide MFMA step
+    // K-tile u: weights in stage u % 4, activations in stage (u / 2) % AS, half u % 2; one 32-wide MFMA step
     // per 16 x 16 tile, done as two halves of 16 MFMAs (row tiles 0-3, then 4-7).  Operands are read from
     // LDS one step ahead, slotted between the MFMAs: during the first half the activations of the second
     // half; during the second half the weights and first-half activations of tile u+1.  Early in the second
-    // half of tile u the wave waits for tile u+1, then requests weights tile u+4 (into the stage tile u
-    // vacated) and, after an odd u, the activation pair (u+3)/2 (into the stage the pair u/2 vacated: every
-    // wavefront holds the rest of that pair in registers by then).  Copies of one wave complete in issue
-    // order, which in steady state reads
-    //   ... B | A B | B | A B | B | A B ...      (A = 2 G copies, B = 2 copies; one group per K-tile)
-    // so "tile u+1 has landed" is vmcnt(2 G + 4) before an odd tile (only its weights are new: the newer
-    // copies are B A B) and vmcnt(4) before an even tile (its activation pair is new: the newer copies are
-    // B B).  Other vector memory operations in flight only make these waits stricter.
+    // half of tile u the wave waits for tile u+1; after that it may request weights tile u+4 (into the stage tile u
+    // vacated) and, after an odd u, copies into the stage of the pair u / 2 (every wavefront holds the rest of that pair
+    // in registers by then).  Copies of one wave complete in issue order, so "tile u+1 has landed" is a fixed count of newer copies:
+    //   G = 2   u even: half of A (pair u/2 + 2) in the first half, wait, B (u+4); u odd: the other half of that A, wait, B (u+4).  Half of A is
+    //           G copies, B 2.  Newer than B (u+1), the last that an odd tile needs: A B A B A = 10; newer than the A that completes an even
+    //           tile's pair: B A B A = 8.
+    //   G = 1   u even: wait, B; u odd: wait, A (pair (u+3)/2), B:
+    //             ... B | A B | B | A B | B | A B ...      (A = 2 copies; one group per K-tile)
+    //           vmcnt(6) before an odd tile (only its weights are new: the newer copies are B A B) and vmcnt(4) before an even
+    //           tile (its activation pair is new: the newer copies are B B).
+    // Other vector memory operations in flight only make these waits stricter.
     // With G = 1 a wavefront has four row tiles, so a K-tile is one group of 16 MFMAs: the wait and the
     // requests come after its first four, and the twelve reads of tile u+1's operands between the others,
     // with the activations double-buffered by tile (x0 even, x1 odd) instead of by half.
-    // requests of the virtual steps -4 .. -1, in steady-state order: B0 A0 B1 B2 A1 B3
-    // NK, where a request of weights is a pair of K-tiles: B0 A0 B1 A1 B2, in steady state A (pair q + 2) B (pair q + 3) in
-    // the odd tile of pair q, after waiting for pair q + 1: of the newer copies, only those of B (pair q + 2) may be in flight
+    // NK, where a request of weights is a pair of K-tiles (pair q: the tiles u = 2 q and u + 1) and the only wait that for pair q + 1 in the odd tile:
+    //   G = 2   even tile: second half of A (q+1), half of B (q+2); odd tile: the other half of B (q+2), wait, first half of A (q+2).  Newer than
+    //           A (q+1): B (q+2) = 4.
+    //   G = 1   odd tile: wait, A (q+2), B (q+3); of the newer copies, only those of B (q+2) may be in flight.
+    // Before the loop the requests of the virtual tiles before the first, in the same order.
     if constexpr (NK) {
-        issue_b();
-        issue_a();
-        issue_b();
-        issue_a();
-        issue_b();
-        wait_copies_and_barrier<2 * B_COPIES + A_COPIES>();
+        issue_b(0, B_COPIES);
+        issue_a(0, A_COPIES);
+        issue_b(0, B_COPIES);
+        issue_a(0, SPREAD ? A_HALF : A_COPIES);
+        if (!SPREAD) issue_b(0, B_COPIES);
+        wait_copies_and_barrier<SPREAD ? B_COPIES + A_HALF : 2 * B_COPIES + A_COPIES>();
+    } else if constexpr (SPREAD) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            issue_a((v & 1) * A_HALF, (v & 1) * A_HALF + A_HALF);
+            issue_b(0, B_COPIES);
+        }
+        wait_copies_and_barrier<3 * B_COPIES + 2 * A_HALF>();           // A0 and B0 have landed
     } else {
-        issue_b();
-        issue_a();
-        issue_b();
-        issue_b();
-        issue_a();
-        issue_b();
+        issue_b(0, B_COPIES);
+        issue_a(0, A_COPIES);
+        issue_b(0, B_COPIES);
+        issue_b(0, B_COPIES);
+        issue_a(0, A_COPIES);
+        issue_b(0, B_COPIES);
         wait_copies_and_barrier<4>();                   // A0 and B0 (and more) have landed
     }
     auto live_tiles = [&](const Task& t) __attribute__((always_inline)) { return DEAL ? uniform((t.rows - t.row0 - wm * 16 + 31) >> 5) : TM; };
@@ -623,32 +649,44 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     for (int i = 0; i < 8; ++i) read_w(i, 0, 0, w0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) read_x(i, 0, 0, 0, x0);
+    int a_stage = 0;                                    // activation stage of the pair being multiplied (AS > 2)
     int sb = 0;                                         // weight stage of tile u
     int k_done = 0;                                     // K-tiles of `cur` multiplied so far
 
-    // First half of a K-tile (weights wf, activations x0), reading the second half's activations into x1.
-    auto first_half = [&](const WFrags& wf, int sa, int h) __attribute__((always_inline)) {
+    // First half of a K-tile (weights wf, activations x0), reading the second half's activations into x1.  `copies`: with two of the
+    // copies, four MFMAs apart and as early as the address unit takes them.
+    auto first_half = [&](const WFrags& wf, int sa, int h, auto copies) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             mma_one(i, 0, wf, x0);
+            if (copies.value && (i == 1 || i == 5)) {
+                const int n = i >> 2, from = NK ? A_HALF : h * A_HALF;
+                if (NK && h == 1) issue_b(2 + n, 3 + n);
+                else issue_a(from + n, from + n + 1);
+            }
             if ((i & 3) == 0) read_x(i >> 2, 1, sa, h, x1);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     // Second half of a K-tile after its first four MFMAs: twelve MFMAs with the twelve reads of the next
     // tile's operands (weights in stage sb_n -> wn_f, activations of its first half -> x0) between them.
-    auto second_half_tail = [&](const WFrags& wf, WFrags& wn_f, int sb_n, int sa_n, int h_n) __attribute__((always_inline)) {
+    auto second_half_tail = [&](const WFrags& wf, WFrags& wn_f, int sb_n, int sa_n, int h_n, auto copies) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 4; i < 16; ++i) {
             mma_one(i, 1, wf, x1);
+            if (copies.value && (i == 4 || i == 8)) {
+                const int n = (i >> 2) - 1;
+                if (NK && h_n == 0) issue_a(n, n + 1);
+                else issue_b(n, n + 1);
+            }
             if (i < 12) read_w(i - 4, sb_n, h_n, wn_f);
             else read_x(i - 12, 0, sa_n, h_n, x0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // One pair of K-tiles (u even, u + 1).  kSteady: u <= U - 6 (NK: U - 8), so every request below exists and the wait
-    // counts above hold; kRowsOnly (NK, u == U - 6): the weights have all been requested; otherwise nothing more is
+    // One pair of K-tiles (u even, u + 1).  kSteady: u <= U - 6 (NK, G = 1: U - 8), so every request below exists and the wait
+    // counts above hold; kRowsOnly (NK, G = 1, u == U - 6): the weights have all been requested; otherwise nothing more is
     // requested and the waits are for everything in flight.  kLast: u + 2 == U, nothing follows.
     // G = 1: the twelve MFMAs of a K-tile after its first four (operands wf, xf), with the twelve reads of
     // the next tile's operands (-> wn_f, xn_f) between them.
@@ -672,35 +710,38 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         constexpr int MODE = decltype(mode_tag)::value;
         constexpr bool STEADY = MODE == kSteady, LAST = MODE == kLast;
         constexpr int LAST_G = G - 1;                   // the half of a K-tile whose first four MFMAs cover the wait
-        const int sa = (u >> 1) & 1;
+        constexpr std::integral_constant<bool, SPREAD && STEADY> spread{};
+        constexpr std::integral_constant<bool, SPREAD && (STEADY || (NK && MODE == kDrain))> spread_even{};     // NK: the rest of the last rows
+        const int sa = AS == 2 ? (u >> 1) & 1 : a_stage, sa_next = AS == 2 ? sa ^ 1 : sa + 1 == AS ? 0 : sa + 1;
+        if (AS > 2) a_stage = sa_next;
         // ---- even tile u ----
-        if (G == 2) first_half(w0, sa, 0);
+        if (G == 2) first_half(w0, sa, 0, spread_even);
         const int sb1 = NK ? sb : (sb + 1) & (B_STAGES - 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i)                     // these cover the wait for tile u+1
             if (!DEAL || live > 0) mma_one(i, LAST_G, w0, G == 2 ? x1 : x0);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!NK) {                            // (the pair's weights arrive together)
-            wait_copies_and_barrier<STEADY ? A_COPIES + 4 : 0>();
-            if (STEADY) issue_b();
+            wait_copies_and_barrier<STEADY ? (SPREAD ? 2 * B_COPIES + 3 * A_HALF : A_COPIES + 4) : 0>();
+            if (STEADY && !SPREAD) issue_b(0, B_COPIES);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (G == 2) second_half_tail(w0, w1, sb1, sa, 1);
+        if (G == 2) second_half_tail(w0, w1, sb1, sa, 1, spread);
         else single_tail(w0, x0, w1, x1, sb1, sa, 1);
         // ---- odd tile u + 1 ----
-        if (G == 2) first_half(w1, sa, 1);
+        if (G == 2) first_half(w1, sa, 1, spread);
         sb = NK ? (sb == B_PAIR_STAGES - 1 ? 0 : sb + 1) : (sb1 + 1) & (B_STAGES - 1);
         if (!LAST) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (!DEAL || live > 0) mma_one(i, LAST_G, w1, x1);
             __builtin_amdgcn_sched_barrier(0);
-            wait_copies_and_barrier<MODE <= kRowsOnly ? 4 : 0>();
-            if (MODE <= kRowsOnly) issue_a();
-            if (STEADY) issue_b();
+            wait_copies_and_barrier<MODE <= kRowsOnly ? (SPREAD && !NK ? 2 * B_COPIES + 2 * A_HALF : 4) : 0>();
+            if (MODE <= kRowsOnly && !SPREAD) issue_a(0, A_COPIES);
+            if (STEADY && !SPREAD) issue_b(0, B_COPIES);
             __builtin_amdgcn_sched_barrier(0);
-            if (G == 2) second_half_tail(w1, w0, sb, sa ^ 1, 0);
-            else single_tail(w1, x1, w0, x0, sb, sa ^ 1, 0);
+            if (G == 2) second_half_tail(w1, w0, sb, sa_next, 0, spread);
+            else single_tail(w1, x1, w0, x0, sb, sa_next, 0);
         } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -711,13 +752,13 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         if (k_done == nk) {
             k_done = 0;
             live = live_tiles(nxt);
-            finish_task();
+            finish_task(AS == 2 ? 2 : sa);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     int u = 0;
-    for (; u <= U - (NK ? 8 : 6); u += 2) pair_of_tiles(u, std::integral_constant<int, kSteady>{});
-    if constexpr (NK) {
+    for (; u <= U - (NK && !SPREAD ? 8 : 6); u += 2) pair_of_tiles(u, std::integral_constant<int, kSteady>{});
+    if constexpr (NK && !SPREAD) {
         pair_of_tiles(u, std::integral_constant<int, kRowsOnly>{});  // u == U - 6
         u += 2;
     }
