@@ -17,10 +17,10 @@
 // rounded no longer cancel, and sums of positive products came out with 4.7e-7.  Values that round to an infinity
 // (above 2^128 - 2^119) give NaN sums and go the way of the infinities, f32_check_sums.
 // Measured, per GEMM of 275 GFLOP (64 experts of about 500 rows, K = N = 2048): 2.17 ms on the fp32 instruction (127
-// TFLOP/s), 1.33 ms here (207 TFLOP/s, i.e. 1.24 PFLOP/s of bf16 products; an 8192^3 bf16 matrix product reaches 1.25 to 1.4 on
+// TFLOP/s), 1.28 ms here (215 TFLOP/s, i.e. 1.29 PFLOP/s of bf16 products; an 8192^3 bf16 matrix product reaches 1.25 to 1.4 on
 // this chip).  Counters of that launch: matrix cores busy 53 % of the cycles, VALU issue 23 %, LDS 38 % (17 of them bank
 // conflicts), so no unit is full: what is left are the waits at the two barriers of a K-tile and the reloads of spilled
-// registers among them (the 256 x 256 bodies use all 256 and spill 9 to 11; the equal-span kernel 44 around its calls).  The
+// registers among them (the 256 x 256 bodies use all 256 and spill 4 to 7; the equal-span kernel 44 around its calls).  The
 // 128 x 128 and 64 x 64 bodies convert more per product: matrix cores 36 and 29 %, VALU 33 and 45 %.
 //
 // Data path, per workgroup of WM x WN wavefronts and K-tile of 32:
@@ -300,18 +300,18 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
     uint32_t b_off[NT ? 2 : 1];
 #pragma unroll
     for (int j = 0; j < (NT ? 2 : 1); ++j) b_off[j] = b_lane_off(j, BK, lane) - (uint32_t)(j * RPC) * (uint32_t)(ldb * 4);
-    auto issue_b = [&](int kt, int stage_off) __attribute__((always_inline)) {
+    auto issue_b = [&](int kt, int stage_off, int first, int last) __attribute__((always_inline)) {
         const int k0 = kt * BK;
         const unsigned char* base = b_grp + (NT ? (size_t)k0 * 4 : (size_t)k0 * ldb * 4);
         const uint32_t d = lds_base + stage_off + C::A_BYTES + wave * (B_COPIES * 1024);
         if (k0 + BK <= K && (!NT || n0 + BN <= N)) {
 #pragma unroll
-            for (int j = 0; j < B_COPIES; ++j) copy_to_lds_stream(base + (size_t)(j * RPC) * ldb * 4, b_off[NT ? j & 1 : 0], d + j * 1024);
+            for (int j = first; j < last; ++j) copy_to_lds_stream(base + (size_t)(j * RPC) * ldb * 4, b_off[NT ? j & 1 : 0], d + j * 1024);
         } else {
             int lane_t = lane;                          // opaque to the compiler: the tail's offsets are computed here, not kept in registers
             asm volatile("" : "+v"(lane_t));
 #pragma unroll
-            for (int j = 0; j < B_COPIES; ++j) copy_to_lds_stream(base, b_lane_off(j, K - k0, lane_t), d + j * 1024);
+            for (int j = first; j < last; ++j) copy_to_lds_stream(base, b_lane_off(j, K - k0, lane_t), d + j * 1024);
         }
     };
 
@@ -377,9 +377,18 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
             if (u + 2 < nk) {
 #pragma unroll
                 for (int i = 0; i < (ONE ? 1 : A_ITEMS); ++i) load_a(kt0 + u + 2, i);
-                issue_b(kt0 + u + 2, s_off);
             }
-            __builtin_amdgcn_sched_barrier(0);
+            if (ONE) __builtin_amdgcn_sched_barrier(0);
+        }
+        // The large tile's copies of B go out over the blocks that are left: together behind the barrier, 32 copies of 16 address cycles hold the
+        // wavefronts up (T = 16384, H = I = 2048, E = 64 2797 -> 2689 us per layer; the smaller tiles lose up to 4 % by it)
+        constexpr int OVER = ONE ? NB - kX : 1;
+        if constexpr (q >= kX && q < kX + OVER) {
+            constexpr int c0 = (q - kX) * B_COPIES / OVER, c1 = (q - kX + 1) * B_COPIES / OVER;
+            if constexpr (c1 > c0) {
+                if (u + 2 < nk) issue_b(kt0 + u + 2, s_off, c0, c1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         if constexpr (LIVE > 0) {
 #pragma unroll
@@ -458,7 +467,7 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
         }
     };
 
-    issue_b(kt0, 0);
+    issue_b(kt0, 0, 0, B_COPIES);
     if (!ONE) {
 #pragma unroll
         for (int i = 0; i < A_ITEMS; ++i) load_a(kt0, i);
@@ -470,7 +479,7 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
     }
     wait_copies_and_barrier<0>();
     if (nk > 1) {
-        issue_b(kt0 + 1, STAGE);
+        issue_b(kt0 + 1, STAGE, 0, B_COPIES);
 #pragma unroll
         for (int i = 0; i < (ONE ? 1 : A_ITEMS); ++i) load_a(kt0 + 1, i);
     }
