@@ -316,18 +316,19 @@ __device__ __forceinline__ void gate_logits_tile(const unsigned char* __restrict
     }
 }
 
-// Logits to memory, selection and combine weights of the tile's tokens from the [64][LP] logits at the start of the dynamic LDS (a
-// wavefront reads the rows of its own 8 tokens); route_counts (optional) receives row `tile`.
-template <int BN>
+// Logits to memory, selection and combine weights of tile `tile` of ROWS tokens from the [ROWS][LP] logits at the start of the dynamic LDS (a
+// wavefront reads the rows of its own tokens); route_counts (optional) receives row `tile` if that is a whole chunk of 64, else the tile's
+// share is added to its chunk's row, which is zero before.
+template <int BN, int ROWS = G_BM, int NTHREADS = G_THREADS>
 __device__ __forceinline__ void gate_select_tile(int T, int E, int k, float* __restrict__ logits, int32_t* __restrict__ topk_expert,
                                                  float* __restrict__ topk_weight, int32_t* __restrict__ route_counts, int tile) {
     constexpr int LP = BN + 4;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), row0 = tile * G_BM;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), row0 = tile * ROWS;
     float* lg = (float*)smem;
 
-    // ---- logits to HBM: each wavefront stores its 8 tokens, full rows ----
-    constexpr int TOK = G_BM / G_WAVES;                 // tokens per wavefront from here on
+    // ---- logits to HBM: each wavefront stores its own tokens, full rows ----
+    constexpr int TOK = ROWS / (NTHREADS / 64);         // tokens per wavefront from here on
     constexpr int LANES_PER_ROW = BN / 4;               // 32 or 64 lanes x 16 B
     constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;
 #pragma unroll
@@ -344,10 +345,10 @@ __device__ __forceinline__ void gate_select_tile(int T, int E, int k, float* __r
     constexpr int kNone = 0x7fffffff;
     constexpr int R = TOK / 4;                           // a wavefront's tokens: 4 at a time x R independent chains
     const int s16 = lane & 15;
-    float* stash = lg + G_BM * LP;                       // [64 tokens][k]
-    int* hist = (int*)(lg + G_BM * (LP + BN));           // [E] picks per expert among this workgroup's tokens
+    float* stash = lg + ROWS * LP;                       // [ROWS tokens][k]
+    int* hist = (int*)(lg + ROWS * (LP + BN));           // [E] picks per expert among this workgroup's tokens
     if (route_counts) {
-        for (int e = tid; e < E; e += G_THREADS) hist[e] = 0;
+        for (int e = tid; e < E; e += NTHREADS) hist[e] = 0;
         __syncthreads();
     }
     float vals[R][VL];
@@ -405,7 +406,10 @@ __device__ __forceinline__ void gate_select_tile(int T, int E, int k, float* __r
     // first step of the slot assignment: this workgroup's tokens are one chunk of the token-order scan
     if (route_counts) {
         __syncthreads();
-        for (int e = tid; e < E; e += G_THREADS) route_counts[(size_t)tile * E + e] = hist[e];
+        for (int e = tid; e < E; e += NTHREADS) {
+            if constexpr (ROWS == G_BM) route_counts[(size_t)tile * E + e] = hist[e];
+            else if (hist[e]) atomicAdd(&route_counts[(size_t)(tile / (G_BM / ROWS)) * E + e], hist[e]);
+        }
     }
 }
 
