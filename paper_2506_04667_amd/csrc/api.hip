@@ -623,7 +623,7 @@ int32_t moe_ffn_schedule(int32_t large_list, int32_t n_units_large, int32_t n_un
     const int n = moe::ffn_slot_count(w, wgs, handicap, ux * ncol);
     const int first = moe::ffn_first_slot(w, wgs, handicap);
     for (int j = 0; j < n && j < max_tasks; ++j)
-        moe::ffn_task_at(moe::ffn_slot_position(first + j * wgs, wgs, handicap), ncol, unit0, unit_step, list_index[j], col_tile[j]);
+        moe::ffn_task_at(moe::ffn_slot_position(first + j * wgs, wgs, handicap), ncol, unit0, unit_step, ux, large_list ? nrow_large : 1, list_index[j], col_tile[j]);
     return n;
 }
 

@@ -143,8 +143,8 @@ __device__ __forceinline__ float swap_8_lanes(float v) {
 }
 
 struct Task {                                           // wave-uniform description of one output tile
-    int unit;                                           // index in the list of live units
-    int grp, row0, n0, rows;
+    int unit;                                           // index in the list of live units (where both GEMMs share a launch)
+    int grp, row0, n0, rows;                            // group; first row and column; end of the live rows of the tile
 };
 
 // One GEMM of the expert FFN: C[g] = act(A[g] B[g] + bias[g]) over the live rows of every group (16-bit storage).
@@ -228,28 +228,30 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     if (my_tasks == 0) return;
     const int first_slot = ffn_first_slot(wg_local, wg_stride, handicap);
     auto position = [&](int slot) __attribute__((always_inline)) { return ffn_slot_position(slot, wg_stride, handicap); };
-    // The unit and the live row count of this workgroup's tasks are fetched 64 tasks at a time, one task per
+    // The unit, the column tile and the live rows of this workgroup's tasks are fetched 64 tasks at a time, one task per
     // lane, so that moving on to the next task costs two lane reads, not two dependent trips to memory.
-    int info_unit = 0, info_rows = 0;                   // of this workgroup's task number j0 + lane
+    int info_unit = 0, info_place = 0;                  // of this workgroup's task number j0 + lane: unit; column tile * 512 + live rows
     auto load_task_info = [&](int j0) __attribute__((always_inline)) {
         const int p = position(first_slot + (j0 + (int)(threadIdx.x & 63)) * wg_stride);
         if (p < xcd_tasks) {
             int li, ct;
-            ffn_task_at(p, ncol, unit0, unit_step, li, ct);
+            ffn_task_at(p, ncol, unit0, unit_step, ux, nrow, li, ct);
             info_unit = units[1 + li];
-            info_rows = min(a.rows_dev[info_unit / nrow], a.rows_cap);
+            info_place = ct * 512 + min(min(a.rows_dev[info_unit / nrow], a.rows_cap) - info_unit % nrow * BM, BM);
         }
     };
     // task number j of this workgroup, in slot first_slot + j * wg_stride, whose position is < xcd_tasks
     auto task_at = [&](int j, int slot, Task& t) __attribute__((always_inline)) {
-        int li, ct;
-        ffn_task_at(position(slot), ncol, unit0, unit_step, li, ct);
-        t.unit = uniform(li);
-        const int unit = __builtin_amdgcn_readlane(info_unit, j & 63);
+        if (COUNT || WAIT) {
+            int li, ct;
+            ffn_task_at(position(slot), ncol, unit0, unit_step, ux, nrow, li, ct);
+            t.unit = uniform(li);
+        }
+        const int unit = __builtin_amdgcn_readlane(info_unit, j & 63), place = __builtin_amdgcn_readlane(info_place, j & 63);
         t.grp = uniform(unit / nrow);
         t.row0 = uniform((unit % nrow) * BM);
-        t.n0 = uniform(ct * BN);
-        t.rows = __builtin_amdgcn_readlane(info_rows, j & 63);
+        t.n0 = (place >> 9) * BN;
+        t.rows = t.row0 + (place & 511);                // up to the tile's end: nobody asks further
     };
     // A second-GEMM task reads what the first-GEMM tasks of its unit stored: wait until all of them (8
     // wavefronts per column tile) have signalled.  First-GEMM tasks never wait, and a workgroup starts on its
