@@ -46,9 +46,10 @@
 //              request is a full line (with 64-byte rows every line crossed from HBM twice: 498 us per GEMM at that shape),
 //              through a ring of 3 stages of 32 KB (256 n x 128 B), requested 2 pairs ahead (128-row tiles: 3).  The third stage
 //              leaves the activations two, and none for the epilogue, which pairs up lanes instead.  One wait and barrier per pair;
-//              Rows of a multiple of 2 KB lie in one or two of the 16 channels of an XCD's L2 at the same k, and all workgroups began at
-//              k = 0: the groups' sums begin at different k instead (k_turn), as a 1 GiB stream of such rows into LDS alone goes from
-//              5.6 to 7.0 TB/s.  The two data gradients at E = 128: 370 -> 330 and 313 -> 270 us;
+//              Every sum runs over k in ascending order, whatever the expert's number, and as in the 128 x 128 tiles.  Rows of a multiple of
+//              2 KB lie in one or two of the 16 channels of an XCD's L2 at the same k; sums of neighbouring experts that begin at different
+//              k spread them (the two data gradients at E = 128: 370 -> 330 and 313 -> 270 us), but then an expert's gradients depend on
+//              its number and on which kernel a layer's size takes;
 //   kLayoutKM  activations stored [k][m] (the weight gradients, whose k runs over an expert's slots): a stage holds
 //              64 k x 256 G B, swizzled and read with the transpose read like the weights' [k][n].
 // Rows at or beyond the live row count are fetched from the last live row (their
@@ -176,11 +177,6 @@ constexpr int A_STAGES_NK = 2, B_PAIR_STAGE = BN * 128, B_PAIR_STAGES = 3;      
 static_assert(A_STAGES_NK * A_STAGE + B_PAIR_STAGES * B_PAIR_STAGE <= LDS_BYTES, "three pairs of [n][k] weights");
 constexpr int kActF32Out = 4;                           // template value of ACT: identity, no bias, C in fp32
 
-// The pair of K-tiles that the sums of group `grp` begin with; they go on from there, around the end of K and up to it.  Groups that an
-// XCD works on together (neighbours, or 8 apart) begin at different eighths.  Where rows are no multiple of 2 KB long they are spread
-// over the L2's channels as they are.
-__device__ __forceinline__ int k_turn(int grp, int K, int pairs) { return K % 1024 == 0 ? ((((grp >> 3) * 2 + grp) & 7) * pairs) >> 3 : 0; }
-
 // The work of one workgroup on one list for one GEMM (phase PH of the arguments, activation ACT): `list` =
 // { fault word, number of live units, ids[cap], completion counters[cap] }; the workgroup is number wg_local of
 // the wg_stride workgroups of XCD `xcd` that walk this list.  COUNT: after storing a tile every wavefront adds
@@ -284,16 +280,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
 
     // ---- addresses of this wavefront's 1 KB copies, per task: uniform base + per-lane byte offset ----
     // activations: 2 G copies of 8 rows x 128 B per K-tile pair; weights: 2 copies of 2 k-rows x 512 B per K-tile
-    const size_t a_step = KM ? (size_t)(2 * BK) * P.lda * 2 : (size_t)128;     // bytes between pairs of K-tiles of the activations
-    const size_t b_step = NK ? (size_t)128 : (size_t)BK * P.ldb * 2;       // bytes between K-tiles of the weights
-    auto turn_of = [&](const Task& t) __attribute__((always_inline)) { return NK ? k_turn(t.grp, P.K, nk / 2) : 0; };
     auto task_bases = [&](const Task& t, const unsigned char*& base_a, const unsigned char*& base_b) __attribute__((always_inline)) {
         base_a = uniform((const unsigned char*)((const elem*)P.A + (P.a_row_index ? (size_t)0 : (size_t)t.grp * P.a_group_stride)));
         base_b = uniform((const unsigned char*)((const elem*)P.B + (size_t)t.grp * P.b_group_stride));
-        if constexpr (NK) {
-            base_a += turn_of(t) * a_step;
-            base_b += turn_of(t) * b_step;
-        }
     };
     auto task_offsets = [&](const Task& t, uint32_t (&oa)[4], uint32_t (&ob)[B_COPIES]) __attribute__((always_inline)) {
         const int32_t* row_index = P.a_row_index;
@@ -352,7 +341,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     }
     const int b_requests = NK ? nk / 2 : nk;            // per task
     int a_left = nk / 2, b_left = b_requests;                   // requests left before a cursor moves to the next task
-    int a_turn = turn_of(cur), b_turn = a_turn;         // as many are left when a cursor is at the end of K
+    const size_t a_step = KM ? (size_t)(2 * BK) * P.lda * 2 : (size_t)128;     // bytes between pairs of K-tiles of the activations
+    const size_t b_step = NK ? (size_t)128 : (size_t)BK * P.ldb * 2;       // bytes between K-tiles of the weights
     const uint32_t lds_base = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
     const uint32_t lds_a_wave = lds_base + wave * (A_COPIES * 1024);
     const uint32_t lds_b_wave = lds_base + B_BASE + wave * (B_COPIES * 1024);
@@ -382,12 +372,10 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         if (--a_left == 0) {
             a_left = nk / 2;
             a_base = na_base;
-            a_turn = turn_of(nxt);
 #pragma unroll
             for (int j = 0; j < A_COPIES; ++j) a_off[j] = na_off[j];
         } else {
             a_base += a_step;
-            if (NK && a_left == a_turn) a_base -= (nk / 2) * a_step;
         }
         a_issue_stage = AS == 2 ? a_issue_stage ^ 1 : a_issue_stage + 1 == AS ? 0 : a_issue_stage + 1;
     };
@@ -407,12 +395,10 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         if (--b_left == 0) {
             b_left = b_requests;
             b_base = nb_base;
-            b_turn = turn_of(nxt);
 #pragma unroll
             for (int j = 0; j < B_COPIES; ++j) b_off[j] = nb_off[j];
         } else {
             b_base += b_step;
-            if (NK && b_left == b_turn) b_base -= (nk / 2) * b_step;
         }
         b_issue_stage = b_issue_stage + 1 == (NK ? B_PAIR_STAGES : B_STAGES) ? 0 : b_issue_stage + 1;
     };

@@ -107,3 +107,30 @@ def test_fp32_sums_end_with_the_live_slots(T, H, I, E, k, C, act, bodies):
     u = 2.0 ** -24
     w = math.sqrt((max(rows) + H) / 8 + 2) * u
     check(g, ref, rows, {"dW1": w, "dW2": w, "db1": w, "dx": math.sqrt((H + I) / 8 + 2) * u})
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("T,H,I,E,C", [(3300, 1024, 2048, 17, 400), (2600, 2048, 1024, 17, 300), (9000, 448, 512, 40, 500)])
+def test_gradients_do_not_depend_on_an_experts_number(T, H, I, E, C, dtype):
+    # the same experts under other numbers (another division of a layer among GPUs): every sum is made in the same order, bit for bit
+    print("case", T, H, I, E, C, dtype, flush=True)
+    k, shift, td = 2, 3, moe.TORCH_DTYPE[dtype]
+    cfg = moe.make_config(T, H, I, E, k, 1.0, "relu", dtype, capacity_override=C)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert {moe.moe_gemm16_kernel(cfg, p, cus) for p in ("dh", "dxe")} == {"stream"}
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    n = lambda scale, *s: (torch.empty(s, device="cuda").normal_(generator=gen) * scale).to(td)
+    x, Wg, W1, W2, dout = n(1, T, H), n(H ** -0.5, H, E), n(H ** -0.5, E, H, I), n(I ** -0.5, E, I, H), n(1, T, H)
+    ex = torch.empty(T, E, device="cuda").uniform_(generator=gen).topk(k, 1).indices.int()
+    w = torch.softmax(torch.empty(T, k, device="cuda").normal_(generator=gen), 1)
+
+    def gradients(Wg, W1, W2, ex):
+        g = [torch.full(s, float("nan"), device="cuda") for s in ((T, H), (H, E), (E,), (E, H, I), (E, I), (E, I, H), (E, H))]
+        ws = torch.empty(moe.moe_backward_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+        moe.moe_backward(cfg, ws, x, Wg, W1, None, W2, None, ex, w, dout, *g)
+        return g
+
+    want = gradients(Wg, W1, W2, ex)
+    got = gradients(Wg.roll(shift, 1), W1.roll(shift, 0), W2.roll(shift, 0), (ex + shift) % E)
+    for name, a, b, axis in zip(("dx", "dWg", "dgb", "dW1", "db1", "dW2", "db2"), want, got, (None, 1, 0, 0, 0, 0, 0)):
+        assert torch.equal(a if axis is None else a.roll(shift, axis), b), name
