@@ -72,6 +72,7 @@
 #include "kernels.h"
 #include "lds_copy.h"
 #include "ffn_units.h"
+#include "stream_stages.h"
 
 #include <type_traits>
 
@@ -377,7 +378,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         } else {
             a_base += a_step;
         }
-        a_issue_stage = AS == 2 ? a_issue_stage ^ 1 : a_issue_stage + 1 == AS ? 0 : a_issue_stage + 1;
+        a_issue_stage = AS == 2 ? a_issue_stage ^ 1 : stream_next_stage(a_issue_stage, AS);
     };
     // copies [first, last) of the next K-tile (NK: pair) of the weights
     auto issue_b = [&](int first, int last) __attribute__((always_inline)) {
@@ -476,8 +477,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     // ---- epilogue of task `cur`: bias, activation, conversion, transposed store; then advance to the next task ----
     auto store_tile = [&](int free_stage) __attribute__((always_inline)) {
         const int lane_e = lane_here();
-        // [32 rows][64 columns], 128 B pitch, in a stage that is free: the third one, or where that is part of the ring the one of the pair that
-        // was multiplied last, where a wavefront's own next copies go and only they
+        // [32 rows][64 columns], 128 B pitch, in a stage that is free (stream_epilogue_stage)
         unsigned char* const epi = smem + free_stage * A_STAGE + wave * EPI_BYTES_PER_WAVE;
         const int r16 = lane_e & 15, kq = lane_e >> 4;
         const int N = P.N;
@@ -718,7 +718,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         constexpr int LAST_G = G - 1;                   // the half of a K-tile whose first four MFMAs cover the wait
         constexpr std::integral_constant<bool, SPREAD && STEADY> spread{};
         constexpr std::integral_constant<bool, SPREAD && (STEADY || (NK && MODE == kDrain))> spread_even{};     // NK: the rest of the last rows
-        const int sa = AS == 2 ? (u >> 1) & 1 : a_stage, sa_next = AS == 2 ? sa ^ 1 : sa + 1 == AS ? 0 : sa + 1;
+        const int sa = AS == 2 ? (u >> 1) & 1 : a_stage, sa_next = AS == 2 ? sa ^ 1 : stream_next_stage(sa, AS);
         if (AS > 2) a_stage = sa_next;
         // ---- even tile u ----
         if (G == 2) first_half(w0, sa, 0, spread_even);
@@ -758,7 +758,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
         if (k_done == nk) {
             k_done = 0;
             live = live_tiles(nxt);
-            finish_task(AS == 2 ? 2 : sa);
+            finish_task(stream_epilogue_stage(AS, sa, LAST));
             __builtin_amdgcn_sched_barrier(0);
         }
     };
