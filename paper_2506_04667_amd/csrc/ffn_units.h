@@ -47,13 +47,13 @@ __host__ __device__ inline void ffn_xcd_share(bool large, int n_units, int nrow,
     ux = blocks ? (int)((long long)n_units * (xcd + 1) / kXcds) - unit0
                 : (n_units > xcd ? (n_units - xcd + kXcds - 1) / kXcds : 0);
 }
-// An XCD's tasks of one FFN GEMM over one list, in order: position p = (unit index inside the XCD) * ncol +
-// column tile; in a contiguous block of the list (unit_step == 1), where neighbours are row tiles of one expert, four units (two, if an expert
-// has two or three) and of them eight (16) column tiles at a time, so that the 32 workgroups of an XCD share four panels of rows and eight of
-// weights through its L2 instead of one and 32.  Layers, us: E = 32, H = 7168, I = 2048, top-8, 4096 tokens 1749 -> 1613; E = 4, H = 4096, I =
-// 14336 1688 -> 1510; E = 16, H = 2048, I = 5632, 8192 tokens 811 -> 775; up to as many column tiles nothing changes.  Workgroup w of the XCD's wgs takes positions w, w + wgs, ...  For the small list, w is the
-// workgroup's number rotated so that the first small-tile task goes to the workgroup after the one that got
-// the XCD's last large-tile task.
+// An XCD's tasks of one FFN GEMM over one list, in order: position p = (unit index inside the XCD) * ncol + column tile, but in a contiguous
+// block of the list (unit_step == 1), where neighbours are row tiles of one expert, four units (two, if an expert has two or three) and of them
+// eight (16) column tiles at a time, so that the 32 workgroups of an XCD share four panels of rows and eight of weights through its L2 instead of
+// one and 32.  Layers, us: E = 32, H = 7168, I = 2048, top-8, 4096 tokens 1749 -> 1613; E = 4, H = 4096, I = 14336 1688 -> 1510; E = 16, H = 2048,
+// I = 5632, 8192 tokens 811 -> 775; up to as many column tiles nothing changes.
+// Workgroup w of the XCD's wgs takes positions w, w + wgs, ...  For the small list, w is the workgroup's number rotated so that the first
+// small-tile task goes to the workgroup after the one that got the XCD's last large-tile task.
 constexpr int kSharers = 32;                            // workgroups of an XCD
 __host__ __device__ inline void ffn_task_at(int p, int ncol, int unit0, int unit_step, int ux, int nrow, int& list_index, int& col_tile) {
     const int at_once = nrow >= 4 ? 4 : 2, width = kSharers / at_once;

@@ -215,8 +215,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int32_t* list, 
     // XCD at the same time and share the expert's weight panels through that L2 as well (E = 16 at 16K tokens:
     // FFN 0.513 -> 0.455 ms).  With at most one unit per expert the share is every 8th unit, which measured
     // 1.5 % faster than blocks at E = 128 (neighbouring experts' weights, 8 MB apart, stream at the same time
-    // instead of regions 128 MB apart).  Inside an XCD the tasks, in order of unit and column tile, are dealt
-    // round-robin to its workgroups.
+    // instead of regions 128 MB apart).  Inside an XCD the tasks are dealt round-robin to its
+    // workgroups, in the order of ffn_task_at: by unit and column tile, wide layers' in blocks of both.
     const int n_units = uniform(units[0]);
     int unit0, unit_step, ux;
     ffn_xcd_share(G == 2, n_units, nrow, xcd, unit0, unit_step, ux);

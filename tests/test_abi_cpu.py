@@ -222,7 +222,9 @@ def test_ffn_tasks_are_dealt_exactly_once_and_single_launch_waits_end(lib, wgs):
     # the shapes a reviewer's replay of the earlier schedule stalled on are among these: 4 one-tile units per
     # XCD with 8 + 8 column tiles and 32 workgroups; fewer first-GEMM than second-GEMM column tiles
     cases = [(0, 32, 0, 8, 8), (16, 0, 1, 8, 8), (128, 0, 1, 8, 8), (0, 32, 0, 1, 8), (0, 32, 0, 2, 8), (0, 32, 0, 16, 8),
-             (40, 7, 3, 3, 5), (1, 1, 2, 1, 1), (5, 33, 1, 8, 2), (0, 0, 0, 4, 4), (14, 53, 2, 8, 8), (9, 3, 4, 2, 16)]
+             (40, 7, 3, 3, 5), (1, 1, 2, 1, 1), (5, 33, 1, 8, 2), (0, 0, 0, 4, 4), (14, 53, 2, 8, 8), (9, 3, 4, 2, 16),
+             # several row tiles to an expert and more column tiles than go at once: whole and partial groups of units, narrower last blocks
+             (75, 5, 4, 13, 28), (50, 0, 2, 17, 33), (41, 3, 3, 35, 16), (70, 7, 9, 9, 56)]
     for n_l, n_s, nrow_l, ncol0, ncol1 in cases:
         progs = _programs(n_l, n_s, nrow_l, ncol0, ncol1, wgs)
         for seed in (0, 1):
@@ -242,6 +244,29 @@ def test_ffn_tasks_are_dealt_exactly_once_and_single_launch_waits_end(lib, wgs):
     # the replay does notice a protocol that cannot make progress: second-GEMM tasks walked first
     stalled, _ = _replay(_programs(0, 32, 0, 8, 8, wgs, t2_first=True), 8, 0)
     assert stalled
+
+
+@pytest.mark.parametrize("nrow,at_once", [(2, 2), (3, 2), (4, 4), (9, 4)])
+@pytest.mark.parametrize("ncol", [8, 9, 16, 17, 24, 28, 33, 56])
+def test_wide_layers_tasks_go_in_blocks_of_row_and_column_tiles(lib, nrow, at_once, ncol):
+    width = 32 // at_once
+    for n in (1, 2, 8, 17, 23, 41, 72):                    # at most 1 to 9 units per XCD, uneven shares among them
+        for wgs in (1, 5, 32):
+            seen = []
+            for xcd in range(8):
+                mine = [moe.moe_ffn_schedule(1, n, 0, nrow, ncol, xcd, wg, wgs) for wg in range(wgs)]
+                seen += [t for w in mine for t in w]
+                # position p of the XCD's sequence is task p // wgs of workgroup p % wgs: as many units at a time as there are, of each as
+                # many column tiles as go at once, and the next column tiles before the next units; up to `width` column tiles unit by unit
+                order = [mine[p % wgs][p // wgs] for p in range(sum(map(len, mine)))]
+                units = [n * xcd // 8 + u for u in range(n * (xcd + 1) // 8 - n * xcd // 8)]
+                if ncol <= width:
+                    want = [(u, c) for u in units for c in range(ncol)]
+                else:
+                    want = [(u, c) for u0 in range(0, len(units), at_once) for c0 in range(0, ncol, width)
+                            for u in units[u0:u0 + at_once] for c in range(c0, min(c0 + width, ncol))]
+                assert order == want, (n, wgs, xcd)
+            assert sorted(seen) == [(u, c) for u in range(n) for c in range(ncol)]
 
 
 def test_ffn_schedule_balances_the_xcds(lib):

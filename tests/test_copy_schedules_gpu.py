@@ -1,7 +1,7 @@
 """Where the order of copies and products inside a tile can go wrong, against float64: 128-row tiles of the weight-streaming kernel at every edge
 of their 16-row MFMA tiles (those beyond the live rows are left out), 256-row tiles of the fewest K-tiles over several tasks per workgroup
-(copies cross from task to task), data gradients of weights whose rows are a multiple of 2 KB long, and fp32 256 x 256 tiles of one to
-seven K-tiles."""
+(copies cross from task to task), layers whose tasks go in blocks of row and column tiles, data gradients of weights whose rows are a multiple
+of 2 KB long, and fp32 256 x 256 tiles of one to seven K-tiles."""
 import math
 
 import pytest
@@ -28,6 +28,15 @@ def test_small_tiles(H, I, act, bias, dtype):
 def test_large_tiles_of_few_k_tiles(H, I, dtype):
     rows = [129, 256, 300, 143, 145, 512, 255, 0, 1, 384] * 50
     check_against_float64(rows, H, I, "identity", False, dtype, ("stream", "stream" if H >= 256 else "128"))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("rows,H,I,on", [
+    ([1024, 700, 256, 0, 1000, 300, 513, 897] * 3, 320, 3208, ("stream", "stream")),    # four row tiles to an expert: blocks of four by eight, 13 column tiles
+    ([600, 512, 300, 257, 0, 129] * 4, 264, 4360, ("stream", "128")),                   # three: blocks of two by sixteen, 18 column tiles
+])
+def test_wide_layers(rows, H, I, on, dtype):
+    check_against_float64(rows, H, I, "gelu_tanh", True, dtype, on)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
