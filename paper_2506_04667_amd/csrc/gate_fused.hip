@@ -88,10 +88,9 @@ __global__ __launch_bounds__(F_WGTHREADS) void gate_finish_kernel(GateArgs a) {
 }
 
 template <int BN> constexpr int finish_lds() { return (F_ROWS * (BN + 4 + BN) + BN) * 4; }
-
-// the kernels' LDS limits on the current device (once per device)
 static_assert(finish_lds<256>() <= 64 * 1024, "no limit to raise");
 
+// the kernels' LDS limits on the current device (once per device)
 template <class S, int BN, bool LIN>
 hipError_t prepare_gate_fused_t() {
     static DeviceFlags whole = {}, slice = {};

@@ -329,6 +329,8 @@ __device__ __forceinline__ void gate_select_tile(int T, int E, int k, float* __r
 
     // ---- logits to HBM: each wavefront stores its own tokens, full rows ----
     constexpr int TOK = ROWS / (NTHREADS / 64);         // tokens per wavefront from here on
+    static_assert(G_BM % ROWS == 0, "a tile's picks belong to one chunk of 64 tokens");
+    static_assert(TOK >= 4 && TOK % 4 == 0 && TOK * (NTHREADS / 64) == ROWS, "a wavefront selects four tokens at a time");
     constexpr int LANES_PER_ROW = BN / 4;               // 32 or 64 lanes x 16 B
     constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;
 #pragma unroll
