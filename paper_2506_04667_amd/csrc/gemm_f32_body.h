@@ -18,10 +18,10 @@
 // (above 2^128 - 2^119) give NaN sums and go the way of the infinities, f32_check_sums.
 // Measured, per GEMM of 275 GFLOP (64 experts of about 500 rows, K = N = 2048): 2.17 ms on the fp32 instruction (127
 // TFLOP/s), 1.28 ms here (215 TFLOP/s, i.e. 1.29 PFLOP/s of bf16 products; an 8192^3 bf16 matrix product reaches 1.25 to 1.4 on
-// this chip).  Counters of that launch: matrix cores busy 53 % of the cycles, VALU issue 23 %, LDS 38 % (17 of them bank
-// conflicts), so no unit is full: what is left are the waits at the two barriers of a K-tile and the reloads of spilled
+// this chip).  Counters of such a launch (1.32 ms in that run): matrix cores busy 59 % of the cycles, VALU issue 26 %, LDS 42 % (19 of
+// them bank conflicts), so no unit is full: what is left are the waits at the two barriers of a K-tile and the reloads of spilled
 // registers among them (the 256 x 256 bodies use all 256 and spill 4 to 7; the equal-span kernel 44 around its calls).  The
-// 128 x 128 and 64 x 64 bodies convert more per product: matrix cores 36 and 29 %, VALU 33 and 45 %.
+// 128 x 128 and 64 x 64 bodies convert more per product: matrix cores 36 and 28 %, VALU 33 and 44 %.
 //
 // Data path, per workgroup of WM x WN wavefronts and K-tile of 32:
 //   * A (activations; through the gather table when there is one) comes to registers a K-tile ahead, is split there
@@ -381,7 +381,8 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, unsigned char* smem,
             if (ONE) __builtin_amdgcn_sched_barrier(0);
         }
         // The large tile's copies of B go out over the blocks that are left: together behind the barrier, 32 copies of 16 address cycles hold the
-        // wavefronts up (T = 16384, H = I = 2048, E = 64 2797 -> 2689 us per layer; the smaller tiles lose up to 4 % by it)
+        // wavefronts up (T = 16384, H = I = 2048, E = 64 2797 -> 2689 us per layer, matrix cores busy 55 -> 59 % of the cycles; the smaller tiles lose
+        // up to 4 % by it, and the equal-span kernel neither gains nor loses on average: E = 24 of 4096 tokens 0.99, E = 8 1.04 times)
         constexpr int OVER = ONE ? NB - kX : 1;
         if constexpr (q >= kX && q < kX + OVER) {
             constexpr int c0 = (q - kX) * B_COPIES / OVER, c1 = (q - kX + 1) * B_COPIES / OVER;

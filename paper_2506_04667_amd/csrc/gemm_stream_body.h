@@ -22,9 +22,10 @@
 //     issued from inline asm and waited for with explicit s_waitcnt vmcnt(n) +
 //     s_barrier: a compiler-visible LDS-DMA makes every later LDS read wait for all
 //     outstanding copies;
-//   * a large tile's copies are issued one at a time between the MFMAs.  A copy takes the CU's address unit 16 cycles; issued together
-//     behind the barrier by eight wavefronts, up to 48 of them held their wavefronts up for 768 cycles of a 1024-cycle K-tile.  Layers,
-//     us: E = 16, 16384 tokens 547 -> 505, E = 32, H = 7168, top-8, 4096 tokens 1815 -> 1715, E = 128 600 -> 571; a deeper ring alone
+//   * a large tile's copies are issued one at a time between the MFMAs.  A copy takes the CU's address unit 16 cycles (64 lanes, four a
+//     cycle): up to 48 of them, issued together behind the barrier by eight wavefronts, kept it busy for 768 cycles of a 1024-cycle
+//     K-tile and held their wavefronts up.  Layers, us: E = 16, 16384 tokens 547 -> 505, E = 32, H = 7168, top-8, 4096 tokens 1815 ->
+//     1715, E = 128 600 -> 571; matrix cores busy 52 -> 59 % of the cycles at E = 16, for the same requests; a deeper ring alone
 //     changes nothing.  128-row tiles have half as many copies and wait for bytes instead: later requests cost them 3 %, so theirs
 //     stay together;
 //   * MFMA operand fragments are double-buffered in registers at half-K-tile
