@@ -277,9 +277,9 @@ hipError_t launch_f32_t(const GemmArgs& a, hipStream_t stream) {
 // Tile choice from the row bound alone (live counts are only known on the device): a launch takes about
 // ceil(tiles / CUs) x tile area / efficiency.  256 x 256 fills a CU by itself; two 128 x 128 or four 64 x 64 tiles share
 // one and read each operand from LDS two and four times as often per product.  The efficiencies are the matrix cores' busy
-// shares at K of 1024 and more, roughly: 53 % (256 x 256, T = 16384, H = I = 2048, E = 64; 59 since its copies are spread over the
-// K-tile, which moves no line), 36 % (128 x 128) and 28 % (64 x 64, both
-// T = 2048, H = 1024, I = 4096, E = 16, whose last round is not full); that of the 64 x 256 tile is an estimate.
+// shares at K of 1024 and more, roughly: 53 % (256 x 256, T = 16384, H = I = 2048, E = 64; 59 % since its copies are spread over the
+// K-tile, the line is still the one laid before), 36 % (128 x 128) and 28 % (64 x 64, both T = 2048, H = 1024, I = 4096, E = 16, whose
+// last round is not full); that of the 64 x 256 tile is an estimate.
 int f32_tile_body(int groups, int max_rows, int N, int cus_) {
     const long long cus = cus_;
     auto cost = [&](int b, double eff) {
